@@ -785,16 +785,18 @@ struct rbp_cut {
   unsigned long long* counter = nullptr;
   int64_t* list = nullptr;
   int64_t cap = 0;
-  int qp_blocks = 0;
+  int n_cu = 1;
+  rbp::CutCtr* ctr = nullptr;   // per edge: centroid and reach (workspace of a run)
   int32_t* pv_off = nullptr;    // vertex table of the polytope obstacles
   double* pv = nullptr;
+  double* pbox = nullptr;       // boxes of their vertices
   hipStream_t last_stream = nullptr;
 };
 
 namespace {
 void free_cut(rbp_cut* c) {
   for (void* p : {static_cast<void*>(c->counter), static_cast<void*>(c->list), static_cast<void*>(c->pv_off),
-                  static_cast<void*>(c->pv)})
+                  static_cast<void*>(c->pv), static_cast<void*>(c->ctr), static_cast<void*>(c->pbox)})
     if (p) (void)hipFree(p);
   delete c;
 }
@@ -882,7 +884,7 @@ int rbp_build_cut(const rbp_cut_desc* d, hipStream_t stream, rbp_cut** out) {
   if (hipGetDevice(&dev) != hipSuccess) return RBP_E_DEVICE;
   // polytope obstacles: rows to the host, vertex enumeration, checks
   std::vector<int32_t> poff, vo(size_t(d->n_polytopes) + 1, 0);
-  std::vector<double> pA, pb, verts;
+  std::vector<double> pA, pb, verts, pbox;
   int rc = RBP_OK;
   if (d->n_polytopes > 0) {
     if ((rc = d2h(poff, d->pob_off, size_t(d->n_polytopes) + 1, stream))) return rc;
@@ -920,6 +922,17 @@ int rbp_build_cut(const rbp_cut_desc* d, hipStream_t stream, rbp_cut** out) {
           }
       if (!(vol > 1e-9 * ext * ext * ext)) return RBP_E_SHAPE;
       vo[size_t(j) + 1] = vo[size_t(j)] + nv;
+      // box of the vertices, widened by more than the 1e-9 to which vertices
+      // and rows agree
+      double lo[3], hi[3], big = 1.0;
+      for (int k = 0; k < 3; ++k) lo[k] = hi[k] = V[k];
+      for (int q = 0; q < 3 * nv; ++q) {
+        lo[q % 3] = std::min(lo[q % 3], V[q]);
+        hi[q % 3] = std::max(hi[q % 3], V[q]);
+        big = std::max(big, std::fabs(V[q]));
+      }
+      for (int k = 0; k < 3; ++k) pbox.push_back(lo[k] - 1e-6 * big);
+      for (int k = 0; k < 3; ++k) pbox.push_back(hi[k] + 1e-6 * big);
     }
   }
   auto* c = new (std::nothrow) rbp_cut();
@@ -927,23 +940,26 @@ int rbp_build_cut(const rbp_cut_desc* d, hipStream_t stream, rbp_cut** out) {
   c->device = dev;
   c->desc = *d;
   c->cap = std::max<int64_t>(pairs, 1);
-  if ((rc = dalloc(&c->counter, 1)) || (rc = dalloc(&c->list, size_t(c->cap))) ||
+  if ((rc = dalloc(&c->counter, 2)) || (rc = dalloc(&c->list, size_t(c->cap))) ||
+      (rc = dalloc(&c->ctr, size_t(std::max(d->n_edges, 1)))) || (rc = dalloc(&c->pbox, std::max<size_t>(pbox.size(), 6))) ||
       (rc = dalloc(&c->pv_off, vo.size())) || (rc = dalloc(&c->pv, std::max<size_t>(verts.size(), 3)))) {
     free_cut(c);
     return rc;
   }
   // the count reads 0 until the first run (which zeroes it with a kernel)
-  if (hipMemsetAsync(c->counter, 0, sizeof(unsigned long long), stream) != hipSuccess ||
+  if (hipMemsetAsync(c->counter, 0, 2 * sizeof(unsigned long long), stream) != hipSuccess ||
       hipMemcpyAsync(c->pv_off, vo.data(), vo.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) ||
       (!verts.empty() &&
        hipMemcpyAsync(c->pv, verts.data(), verts.size() * sizeof(double), hipMemcpyHostToDevice, stream)) ||
+      (!pbox.empty() &&
+       hipMemcpyAsync(c->pbox, pbox.data(), pbox.size() * sizeof(double), hipMemcpyHostToDevice, stream)) ||
       hipStreamSynchronize(stream) != hipSuccess) {
     free_cut(c);
     return RBP_E_DEVICE;
   }
   int n_cu = 0;
   if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1) n_cu = 1;
-  c->qp_blocks = 4 * n_cu;   // grid-stride over the undecided pairs
+  c->n_cu = n_cu;   // sizes the grid-stride launches over the listed pairs
   c->last_stream = stream;
   *out = c;
   return RBP_OK;
@@ -961,8 +977,9 @@ int rbp_cut_run(rbp_cut* c, const double* P, uint8_t* code, uint8_t* step, doubl
   a.P = P; a.box_lo = d.box_lo; a.box_hi = d.box_hi;
   a.pob_off = d.pob_off; a.pob_A = d.pob_A; a.pob_b = d.pob_b; a.pv_off = c->pv_off; a.pv = c->pv;
   a.code = code; a.step = step; a.qp_dist2 = qp_dist2; a.n_collide = n_collide;
+  a.ctr = c->ctr; a.pbox = c->pbox;
   a.counter = c->counter; a.list = c->list; a.list_cap = c->cap;
-  if (rbp::launch_cut(a, stream, c->qp_blocks) != hipSuccess) return RBP_E_DEVICE;
+  if (rbp::launch_cut(a, stream, c->n_cu) != hipSuccess) return RBP_E_DEVICE;
   c->last_stream = stream;
   return RBP_OK;
 }

@@ -176,6 +176,10 @@ struct ChainArgs {
 };
 
 // ---- cutting graph edges against box obstacles (rbp_cut.hip)
+// an edge's centroid and the squared distance beyond which an obstacle is far
+struct alignas(16) CutCtr {
+  double x, y, z, reach2;
+};
 struct CutArgs {
   int n_edges, n_obst, degree;
   int n_box;                 // obstacles 0 .. n_box-1 are boxes, the rest polytopes
@@ -191,11 +195,14 @@ struct CutArgs {
   uint8_t* step;             // nullable [n_obst][n_edges]: 1, 2 or 3 (Alg. 2 step that decided)
   double* qp_dist2;          // nullable [n_obst][n_edges]: |delta*|^2 where step 3 ran, NaN elsewhere
   int32_t* n_collide;        // [n_edges]: obstacles the edge may collide with
-  unsigned long long* counter;   // pairs appended to the list (device scalar)
-  int64_t* list;             // undecided pairs (o << 32 | e)
+  int obst_base;             // first obstacle of a filter launch
+  const double* pbox;        // [n_obst - n_box][6] lower and upper corner of each polytope's vertices
+  CutCtr* ctr;               // [n_edges] workspace
+  unsigned long long* counter;   // device: [0] pairs that reached step 3, [1] pairs in the list
+  int64_t* list;             // pairs that are not far (o << 32 | e)
   int64_t list_cap;
 };
-hipError_t launch_cut(const CutArgs& a, hipStream_t s, int qp_blocks);
+hipError_t launch_cut(const CutArgs& a, hipStream_t s, int n_cu);
 
 // ---- building the graph and adjacent hyperplanes (rbp_graph.hip)
 struct GraphArgs {
