@@ -1008,13 +1008,14 @@ struct rbp_graph {
   double* B = nullptr;
   double* Amin = nullptr;
   double* Bmin = nullptr;
+  uint8_t* tile_nan = nullptr;
   hipStream_t last_stream = nullptr;
 };
 
 namespace {
 void free_graph(rbp_graph* g) {
   for (void* p : {static_cast<void*>(g->A), static_cast<void*>(g->B), static_cast<void*>(g->Amin),
-                  static_cast<void*>(g->Bmin)})
+                  static_cast<void*>(g->Bmin), static_cast<void*>(g->tile_nan)})
     if (p) (void)hipFree(p);
   delete g;
 }
@@ -1037,7 +1038,7 @@ int rbp_build_graph(const rbp_graph_desc* d, hipStream_t stream, rbp_graph** out
   const size_t tm = size_t((d->n_nodes + 63) / 64) * size_t(d->n_rows);
   int rc;
   if ((rc = dalloc(&g->A, nm)) || (rc = dalloc(&g->B, nm)) || (rc = dalloc(&g->Amin, tm)) ||
-      (rc = dalloc(&g->Bmin, tm))) {
+      (rc = dalloc(&g->Bmin, tm)) || (rc = dalloc(&g->tile_nan, size_t(rbp::graph_flag_bytes(d->n_nodes, d->n_rows))))) {
     free_graph(g);
     return rc;
   }
@@ -1054,7 +1055,7 @@ int rbp_graph_run(rbp_graph* g, const double* V, uint32_t* adj, int32_t* degree,
   rbp::GraphArgs a{};
   a.n_nodes = d.n_nodes; a.dim = d.dim; a.m = d.n_rows;
   a.V = V; a.F1 = d.F1; a.F2 = d.F2; a.G = d.G;
-  a.A = g->A; a.B = g->B; a.Amin = g->Amin; a.Bmin = g->Bmin;
+  a.A = g->A; a.B = g->B; a.Amin = g->Amin; a.Bmin = g->Bmin; a.tile_nan = g->tile_nan;
   a.adj = adj; a.degree = degree;
   if (rbp::launch_graph(a, stream) != hipSuccess) return RBP_E_DEVICE;
   g->last_stream = stream;
@@ -1089,6 +1090,7 @@ int rbp_graph_run_noalloc(const rbp_graph_desc* d, const double* V, uint32_t* ad
   a.n_nodes = d->n_nodes; a.dim = d->dim; a.m = d->n_rows;
   a.V = V; a.F1 = d->F1; a.F2 = d->F2; a.G = d->G;
   a.A = ws; a.B = ws + nm; a.Amin = ws + 2 * nm; a.Bmin = ws + 2 * nm + tm;
+  a.tile_nan = reinterpret_cast<uint8_t*>(ws + rbp::kGraphScratchDoubles);
   a.adj = adj; a.degree = degree;
   return rbp::launch_graph(a, stream) == hipSuccess ? RBP_OK : RBP_E_DEVICE;
 }

@@ -4,12 +4,14 @@
 // Edge i -> j when F [v_i; v_j] <= G, i.e. max_k (A_ik + B_jk) <= 0 with the
 // per-node row values A = F1 v (start columns) and B = F2 v - G (end
 // columns): an all-pairs (max, +) product of two N x m matrices followed by a
-// sign test.  The pair kernel tiles it 64 x 64 with 4 x 4 register blocks and
-// 16-row chunks of A and B staged in LDS (odd row stride), in FP64.  A tile
-// is skipped with an exact bound: if min_i A_ik + min_j B_jk > 0 for some row
-// k, every pair of the tile violates row k.  With nodes numbered along a
-// space-filling curve most far-apart tiles go this way, so the work follows
-// the number of near pairs rather than N^2; the result never depends on it.
+// sign test, in FP64.  Two kernels: graph_rows_kernel forms A and B with the
+// minima of every 64-node tile, graph_pairs_kernel the adjacency, one word of
+// 32 end nodes for 64 start nodes (one per lane) at a time.  Exact bounds cut
+// the work: a tile of start nodes and a tile of end nodes are skipped if
+// min_i A_ik + min_j B_jk > 0 for some row k, and a single end node j if
+// min_i A_ik + B_jk > 0.  With nodes numbered along a space-filling curve most
+// far pairs go this way, so the work follows the number of near pairs rather
+// than N^2; the result never depends on it.
 // Output: the adjacency as a row-major bitmask (bit j % 32 of word j / 32 of
 // row i) and out-degrees.
 //
@@ -23,6 +25,7 @@
 #include <mutex>
 
 #include "rbp_internal.hpp"
+#include "rbp_wave.hpp"
 
 namespace rbp {
 
@@ -30,113 +33,167 @@ namespace rbp {
 // a fixed array in device memory, one copy per GPU, held until the process
 // ends.  Host code never uses the name itself as an address: the device
 // address of each GPU's copy comes from hipGetSymbolAddress.
-static __device__ __align__(256) double scratch[kGraphScratchDoubles];
+// The flags after the row values and minima (one byte per 64 nodes and 16 rows,
+// fewer than 65,536 wherever those fit) have room of their own.
+static __device__ __align__(256) double scratch[kGraphScratchDoubles + kGraphFlagDoubles];
 
 namespace {
 
 constexpr int kTile = 64;       // nodes per tile side
-constexpr int kChunk = 16;      // rows of A, B per LDS stage
-constexpr int kLd = kChunk + 1; // odd LDS stride in doubles
-constexpr double kPad = -1e300; // rows beyond m: A + B stays far below 0
+constexpr int kChunk = 16;      // rows of A a lane holds at a time
+constexpr int kWords = 4;       // words (of 32 end nodes) per block
+constexpr int kEnds = 16;       // end nodes per wavefront
+constexpr int kPairWaves = kWords * 32 / kEnds;
+constexpr int kRowsPerBlock = 16;   // rows k per block of graph_rows_kernel
+constexpr int kDimMax = 12;     // RBP_GRAPH_MAX_DIM
 
-__global__ void graph_rows_kernel(GraphArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)a.n_nodes * a.m) return;
-  const int i = (int)(t / a.m), k = (int)(t - (int64_t)i * a.m);
-  double s1 = 0.0, s2 = 0.0;
-  for (int c = 0; c < a.dim; ++c) {
-    const double v = a.V[(int64_t)i * a.dim + c];
-    s1 += a.F1[k * a.dim + c] * v;
-    s2 += a.F2[k * a.dim + c] * v;
+// Row values of one 64-node tile (lane = node) for kRowsPerBlock rows k (A
+// stored by row, so that a lane's node is coalesced; B by node, so that the
+// rows of an end node are), their tile minima, whether an A is NaN (a minimum
+// passes over it), and out-degrees set to 0.  A row's coefficients are uniform,
+// so a row costs 2 dim FMAs, two coalesced stores and two wave minima; tile x
+// row-chunk blocks keep the chip busy although a tile has only 64 nodes.
+// 5,000 nodes x 64 rows: 8.1 us with the minima (before, in two kernels: 24.2 us).
+template <int DIM>
+__global__ __launch_bounds__(256) void graph_rows_kernel(GraphArgs a) {
+  constexpr int kD = DIM > 0 ? DIM : kDimMax;
+  const int dim = DIM > 0 ? DIM : a.dim;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int tile = blockIdx.x, i = tile * kTile + lane;
+  const bool live = i < a.n_nodes;
+  if (blockIdx.y == 0 && wv == 0 && live) a.degree[i] = 0;
+  double v[kD];
+#pragma unroll
+  for (int c = 0; c < kD; ++c) v[c] = (live && c < dim) ? a.V[(int64_t)i * dim + c] : 0.0;
+  bool nan = false;
+#pragma unroll
+  for (int u = 0; u < kRowsPerBlock / 4; ++u) {
+    const int k = blockIdx.y * kRowsPerBlock + 4 * u + wv;
+    if (k >= a.m) break;   // uniform
+    double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+    for (int c = 0; c < kD; ++c) {
+      if (c < dim) {
+        s1 += a.F1[k * dim + c] * v[c];
+        s2 += a.F2[k * dim + c] * v[c];
+      }
+    }
+    s2 -= a.G[k];
+    if (live) {
+      a.A[(int64_t)k * a.n_nodes + i] = s1;
+      a.B[(int64_t)i * a.m + k] = s2;
+      nan |= s1 != s1;
+    }
+    const double ma = wave::min(live ? s1 : __builtin_huge_val());
+    const double mb = wave::min(live ? s2 : __builtin_huge_val());
+    if (lane == 0) {
+      a.Amin[tile * a.m + k] = ma;
+      a.Bmin[tile * a.m + k] = mb;
+    }
   }
-  a.A[t] = s1;
-  a.B[t] = s2 - a.G[k];
+  const int any = __syncthreads_or(nan);
+  if (threadIdx.x == 0) a.tile_nan[tile * gridDim.y + blockIdx.y] = any != 0;
 }
 
-// per tile t and row k: minimum of A and of B over the tile's nodes
-__global__ void graph_bounds_kernel(GraphArgs a, int n_tiles) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_tiles * a.m) return;
-  const int tile = t / a.m, k = t - tile * a.m;
-  const int i0 = tile * kTile, i1 = i0 + kTile < a.n_nodes ? i0 + kTile : a.n_nodes;
-  double ma = __builtin_huge_val(), mb = __builtin_huge_val();
-  for (int i = i0; i < i1; ++i) {
-    ma = fmin(ma, a.A[(int64_t)i * a.m + k]);
-    mb = fmin(mb, a.B[(int64_t)i * a.m + k]);
+// One wavefront: 64 start nodes (one per lane) against the 32 end nodes of one
+// adjacency word.  The sum A_ik + B_jk is positive exactly when A_ik > -B_jk,
+// so a row costs one comparison of a lane's A with a uniform B (a scalar load)
+// and an OR of lane masks on the scalar unit: half the vector instructions of
+// adding and taking maxima, and no LDS.  An end node is dropped as soon as
+// every lane has a violated row; before that the bound min_i A_ik + B_jk,
+// whose rows lie one per lane, drops the end nodes that no start node of the
+// tile can reach (it does not hold where an A is NaN).
+// A block's four words leave through LDS, 16 bytes per row at a time, and are
+// counted into the out-degrees on the way.
+// 5,000 nodes x 64 rows: 95.2 us (64 x 64 tiles in LDS) + 41.7 us (degrees) -> 45 us.
+// What is left is the latency of the few wavefronts with many open end nodes;
+// blocks of four or sixteen wavefronts instead of eight take 62 and 64 us.
+__global__ __launch_bounds__(64 * kPairWaves) void graph_pairs_kernel(GraphArgs a, const double* __restrict__ gA,
+                                                                 const double* __restrict__ gB) {
+  static_assert(kEnds == 16, "two half-words per word");
+  __shared__ uint16_t half[kTile][kPairWaves + 2];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = a.n_nodes, m = a.m, n_words = (n + 31) / 32;
+  const int ti = blockIdx.y, j0 = (blockIdx.x * kPairWaves + wv) * kEnds, tj = j0 / kTile;
+  const int gi = ti * kTile + lane;
+  uint32_t bits = 0u;
+  bool culled = j0 >= n;
+  for (int k0 = 0; k0 < m && !culled; k0 += 64) {
+    const int k = k0 + lane;
+    culled = __ballot(k < m && a.Amin[ti * m + k] + a.Bmin[tj * m + k] > 0.0) != 0ull;
   }
-  a.Amin[t] = ma;
-  a.Bmin[t] = mb;
-}
-
-__global__ __launch_bounds__(256) void graph_pairs_kernel(GraphArgs a) {
-  __shared__ double As[kTile * kLd];
-  __shared__ double Bs[kTile * kLd];
-  __shared__ uint32_t words[kTile * 2];
-  const int ti = blockIdx.y, tj = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int n_words = (a.n_nodes + 31) / 32;
-  // exact cull: a row violated by every pair of the tile
-  bool culled = false;
-  for (int k = 0; k < a.m && !culled; ++k) culled = a.Amin[ti * a.m + k] + a.Bmin[tj * a.m + k] > 0.0;
-  if (tid < 2 * kTile) words[tid] = 0u;
   if (!culled) {
-    const int r0 = (tid >> 4) * 4, c0 = (tid & 15) * 4;   // 4 x 4 block of the tile
-    double acc[4][4];
+    const int nj = n - j0 < kEnds ? n - j0 : kEnds;
+    uint32_t alive = (1u << nj) - 1u;                     // end nodes still open, uniform
+    const int nkc = (m + kRowsPerBlock - 1) / kRowsPerBlock;
+    bool nan = false;
+    for (int c = lane; c < nkc; c += 64) nan |= a.tile_nan[ti * nkc + c] != 0;
+    if (__ballot(nan) == 0ull) {
+      for (int k0 = 0; k0 < m; k0 += 64) {
+        const int k = k0 + lane;
+        const double am = k < m ? a.Amin[ti * m + k] : -__builtin_huge_val();
+        const int kc = k < m ? k : m - 1;
+        double b[kEnds];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+        for (int j = 0; j < kEnds; ++j) b[j] = gB[(int64_t)(j0 + (j < nj ? j : 0)) * m + kc];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) acc[r][c] = -__builtin_huge_val();
-    for (int k0 = 0; k0 < a.m; k0 += kChunk) {
-      __syncthreads();
-      // stage rows k0..k0+15 of the tile's A (start nodes) and B (end nodes)
-      for (int e = tid; e < kTile * kChunk; e += 256) {
-        const int n = e / kChunk, kk = e - n * kChunk, k = k0 + kk;
-        const int gi = ti * kTile + n, gj = tj * kTile + n;
-        As[n * kLd + kk] = (gi < a.n_nodes && k < a.m) ? a.A[(int64_t)gi * a.m + k] : kPad;
-        Bs[n * kLd + kk] = (gj < a.n_nodes && k < a.m) ? a.B[(int64_t)gj * a.m + k] : kPad;
-      }
-      __syncthreads();
-#pragma unroll 4
-      for (int kk = 0; kk < kChunk; ++kk) {
-        double av[4], bv[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) av[r] = As[(r0 + r) * kLd + kk];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) bv[c] = Bs[(c0 + c) * kLd + kk];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int c = 0; c < 4; ++c) acc[r][c] = fmax(acc[r][c], av[r] + bv[c]);
+        for (int j = 0; j < kEnds; ++j)
+          if (__ballot(am + b[j] > 0.0) != 0ull) alive &= ~(1u << j);
       }
     }
-    __syncthreads();
+    const unsigned long long lanes = __ballot(gi < n);
+    uint32_t dead = 0u;                                   // per lane: violated end nodes
+    uint32_t open = alive;
+    for (int kk = 0; kk < m && open; kk += kChunk) {
+      // the last chunk ends at row m (rows seen twice change nothing); with
+      // fewer than kChunk rows the first one is repeated
+      const int k0 = kk + kChunk <= m ? kk : (m >= kChunk ? m - kChunk : 0);
+      double av[kChunk];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int gi = ti * kTile + r0 + r;
-      uint32_t nib = 0u;
+      for (int u = 0; u < kChunk; ++u)
+        av[u] = gA[(int64_t)(k0 + u < m ? k0 + u : 0) * n + (gi < n ? gi : n - 1)];
+      // two end nodes at a time: their scalar loads are in flight together
+      for (uint32_t todo = open; todo;) {
+        const int j1 = __builtin_ctz(todo);
+        todo &= todo - 1u;
+        const int j2 = todo ? __builtin_ctz(todo) : j1;
+        todo &= todo - 1u;
+        const double* p1 = gB + (int64_t)(j0 + j1) * m + k0;
+        const double* p2 = gB + (int64_t)(j0 + j2) * m + k0;
+        unsigned long long v1 = 0ull, v2 = 0ull;
+        if (m >= kChunk) {
+          double b1[kChunk], b2[kChunk];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int gj = tj * kTile + c0 + c;
-        if (acc[r][c] <= 0.0 && gi != gj && gi < a.n_nodes && gj < a.n_nodes) nib |= 1u << c;
+          for (int u = 0; u < kChunk; ++u) { b1[u] = p1[u]; b2[u] = p2[u]; }
+#pragma unroll
+          for (int u = 0; u < kChunk; ++u) {
+            v1 |= __ballot(av[u] > -b1[u]);
+            v2 |= __ballot(av[u] > -b2[u]);
+          }
+        } else {
+          for (int u = 0; u < m; ++u) {
+            const double a1 = gA[(int64_t)u * n + (gi < n ? gi : n - 1)];
+            v1 |= __ballot(a1 > -p1[u]);
+            v2 |= __ballot(a1 > -p2[u]);
+          }
+        }
+        dead |= ((v1 >> lane) & 1ull) ? 1u << j1 : 0u;
+        dead |= ((v2 >> lane) & 1ull) ? 1u << j2 : 0u;
+        if ((__ballot((dead >> j1) & 1u) & lanes) == lanes) open &= ~(1u << j1);
+        if ((__ballot((dead >> j2) & 1u) & lanes) == lanes) open &= ~(1u << j2);
       }
-      if (nib) atomicOr(&words[(r0 + r) * 2 + (c0 >> 5)], nib << (c0 & 31));
     }
+    bits = alive & ~dead;
+    if (gi >= j0 && gi - j0 < kEnds) bits &= ~(1u << (gi - j0));   // no self edge
   }
+  half[lane][wv] = uint16_t(bits);
   __syncthreads();
-  if (tid < 2 * kTile) {
-    const int row = tid >> 1, w = 2 * tj + (tid & 1);
-    const int gi = ti * kTile + row;
-    if (gi < a.n_nodes && w < n_words) a.adj[(int64_t)gi * n_words + w] = words[tid];
+  const int row = tid / kWords, wl = tid % kWords, gr = ti * kTile + row, gw = blockIdx.x * kWords + wl;
+  if (row < kTile && gr < n && gw < n_words) {
+    const uint32_t out = half[row][2 * wl] | (uint32_t(half[row][2 * wl + 1]) << 16);
+    a.adj[(int64_t)gr * n_words + gw] = out;
+    if (out) atomicAdd(&a.degree[gr], __popc(out));
   }
-}
-
-__global__ void graph_degree_kernel(GraphArgs a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= a.n_nodes) return;
-  const int n_words = (a.n_nodes + 31) / 32;
-  int d = 0;
-  for (int w = 0; w < n_words; ++w) d += __popc(a.adj[(int64_t)i * n_words + w]);
-  a.degree[i] = d;
 }
 
 __global__ void hyperplane_kernel(int n, const double* __restrict__ X, int n_obst, const double* __restrict__ lo,
@@ -167,12 +224,16 @@ __global__ void hyperplane_kernel(int n, const double* __restrict__ X, int n_obs
 
 hipError_t launch_graph(const GraphArgs& a, hipStream_t s) {
   if (a.n_nodes <= 0) return hipSuccess;
-  const int64_t nm = (int64_t)a.n_nodes * a.m;
-  hipLaunchKernelGGL(graph_rows_kernel, dim3((unsigned)((nm + 255) / 256)), dim3(256), 0, s, a);
   const int n_tiles = (a.n_nodes + kTile - 1) / kTile;
-  hipLaunchKernelGGL(graph_bounds_kernel, dim3((n_tiles * a.m + 255) / 256), dim3(256), 0, s, a, n_tiles);
-  hipLaunchKernelGGL(graph_pairs_kernel, dim3(n_tiles, n_tiles), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(graph_degree_kernel, dim3((a.n_nodes + 255) / 256), dim3(256), 0, s, a);
+  const dim3 rg(n_tiles, (a.m + kRowsPerBlock - 1) / kRowsPerBlock);
+  // positions, and positions with velocities: a row's coefficients then come
+  // in one or two scalar loads instead of one per component
+  if (a.dim == 3) hipLaunchKernelGGL(graph_rows_kernel<3>, rg, dim3(256), 0, s, a);
+  else if (a.dim == 6) hipLaunchKernelGGL(graph_rows_kernel<6>, rg, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(graph_rows_kernel<0>, rg, dim3(256), 0, s, a);
+  const int n_words = (a.n_nodes + 31) / 32;
+  hipLaunchKernelGGL(graph_pairs_kernel, dim3((n_words + kWords - 1) / kWords, n_tiles), dim3(64 * kPairWaves), 0, s, a,
+                     a.A, a.B);
   return hipGetLastError();
 }
 

@@ -211,16 +211,20 @@ struct GraphArgs {
   const double* F1;          // [m][dim] columns of F on the start node
   const double* F2;          // [m][dim] columns of F on the end node
   const double* G;           // [m]
-  double* A;                 // [n_nodes][m] F1 v (workspace)
+  double* A;                 // [m][n_nodes] F1 v (workspace)
   double* B;                 // [n_nodes][m] F2 v - G (workspace)
   double* Amin;              // [n_tiles][m] tile minima (workspace)
   double* Bmin;
+  uint8_t* tile_nan;         // [n_tiles][ceil(m / 16)] 1: an A of the tile is NaN (workspace)
   uint32_t* adj;             // [n_nodes][ceil(n_nodes / 32)] bitmask
   int32_t* degree;           // [n_nodes]
 };
 hipError_t launch_graph(const GraphArgs& a, hipStream_t s);
 // Fixed device workspace of rbp_graph_run_noalloc, in doubles (8 MiB).
 constexpr int64_t kGraphScratchDoubles = int64_t(1) << 20;
+constexpr int64_t kGraphFlagDoubles = 8192;   // 64 KB of tile_nan behind them
+// bytes of GraphArgs::tile_nan
+inline int64_t graph_flag_bytes(int64_t n, int64_t m) { return ((n + 63) / 64) * ((m + 15) / 16); }
 // Device address of the current GPU's copy of that workspace (looked up once
 // per device with hipGetSymbolAddress, then cached).
 hipError_t graph_scratch(double** out);
