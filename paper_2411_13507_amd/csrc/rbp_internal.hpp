@@ -26,9 +26,9 @@ struct LdsDims {
   int nf_cap;  // max faces
   int m_cap;   // max rows
   // byte offsets
-  int o_Hd, o_Af, o_rowval, o_ybuf, o_vec, o_scal, o_acte, o_lam, o_actid, o_actside, o_cst, o_Rd, o_region;
-  int o_Hf, o_Aff, o_vbuf, o_xb1, o_xb2, o_Kx;   // ADMM part of region
-  int o_Q1, o_R, o_Ri;                            // polish part of region
+  int o_Hd, o_Af, o_ybuf, o_vec, o_scal, o_acte, o_lam, o_actid, o_actside, o_cst, o_region;
+  int o_Hf, o_Aff, o_rsc, o_vbuf, o_xb1, o_xb2, o_Kx;   // ADMM part of region (Kx over vbuf, xb1, xb2)
+  int o_Q1, o_Ri;                                 // polish part of region
   int bytes;
 };
 
@@ -77,7 +77,7 @@ struct SolveArgs {
   int32_t* st_id;            // [N * nmax] row ids
   int32_t* st_side;          // [N * nmax] sides
   double* st_lam;            // [N * st_stride] multipliers
-  double* st_qr;             // [N * 2 st_stride^2] final factor: q rows of Q1, then the q x q R block
+  double* st_qr;             // [N * 2 st_stride^2] final factor: q rows of Q1, then R^-1 packed by columns
   int st_stride;             // entries per instance in st_id / st_side / st_lam
   // forward results kept for the backward pass (written when store is set)
   int32_t* fw_status;        // [N]

@@ -41,9 +41,8 @@ LdsDims make_dims(int pmax, int r_cap, int nf_cap, int real_bytes, bool admm) {
   d.m_cap = (pmax - 1) * d.nf_cap + 6 * pmax - 3 + d.r_cap;
   int o = 0;
   auto take = [&](int bytes) { const int at = o; o += (bytes + 15) & ~15; return at; };
-  d.o_Hd = take(d.r_cap * (d.ncol | 1) * 8);
+  d.o_Hd = take(d.r_cap * (d.nmax | 1) * 8);
   d.o_Af = take(d.nf_cap * 3 * 8);
-  d.o_rowval = take(d.m_cap * 8);
   d.o_ybuf = take(2 * d.ncol * 8);
   d.o_vec = take(5 * d.nmax * 8);   // vA..vE
   d.o_scal = take(16 * 8);
@@ -51,8 +50,7 @@ LdsDims make_dims(int pmax, int r_cap, int nf_cap, int real_bytes, bool admm) {
   d.o_lam = take(d.nmax * 8);
   d.o_actid = take(d.nmax * 4);
   d.o_actside = take(d.nmax * 4);
-  d.o_cst = take(((admm ? 2 : 1) * kMaxFree * kMaxFree + kMaxPts * kMaxPts) * 8);
-  d.o_Rd = take(d.nmax * 8);
+  d.o_cst = take(kMaxFree * kMaxFree * 8);
   d.o_region = o;
   // iteration scratch in the precision of the iterations
   const int hs = d.r_cap | 1;
@@ -62,18 +60,21 @@ LdsDims make_dims(int pmax, int r_cap, int nf_cap, int real_bytes, bool admm) {
   if (admm) {
     d.o_Hf = take_r(d.nmax * hs * rb);
     d.o_Aff = take_r(d.nf_cap * 4 * rb);
+    d.o_rsc = take_r(d.r_cap * 8);
+    // the matrix Kx is done with before the first iteration
+    d.o_Kx = a;
     d.o_vbuf = take_r(d.m_cap * rb);
     d.o_xb1 = take_r(d.nmax * rb);
     d.o_xb2 = take_r(d.nmax * rb);
-    d.o_Kx = take_r(d.nmax * d.nmax * rb);
+    const int kx_end = (d.o_Kx + d.nmax * d.nmax * rb + 15) & ~15;
+    if (kx_end > a) a = kx_end;
   } else {
-    d.o_Hf = d.o_Aff = d.o_vbuf = d.o_xb1 = d.o_xb2 = d.o_Kx = d.o_region;   // unused
+    d.o_Hf = d.o_Aff = d.o_rsc = d.o_vbuf = d.o_xb1 = d.o_xb2 = d.o_Kx = d.o_region;   // unused
   }
   int b = d.o_region;
   auto take_p = [&](int bytes) { const int at = b; b += (bytes + 15) & ~15; return at; };
   d.o_Q1 = take_p(d.nmax * (d.nmax | 1) * 8);
-  d.o_R = take_p(d.nmax * (d.nmax | 1) * 8);
-  d.o_Ri = take_p(d.nmax * (d.nmax | 1) * 8);
+  d.o_Ri = take_p(d.nmax * (d.nmax + 1) / 2 * 8);
   d.bytes = a > b ? a : b;
   return d;
 }
@@ -102,9 +103,9 @@ LdsDims make_back_dims(int pmax, int nf_cap) {
   d.o_actside = take(d.nmax * 4);
   d.o_cst = take(kMaxFree * kMaxFree * 8);
   d.o_Q1 = take(d.nmax * (d.nmax | 1) * 8);
-  d.o_R = take(d.nmax * (d.nmax | 1) * 8);
-  d.o_rowval = d.o_acte = d.o_Rd = d.o_Ri = 0;
-  d.o_region = d.o_Hf = d.o_Aff = d.o_vbuf = d.o_xb1 = d.o_xb2 = d.o_Kx = 0;
+  d.o_Ri = take(d.nmax * (d.nmax + 1) / 2 * 8);
+  d.o_acte = 0;
+  d.o_region = d.o_Hf = d.o_Aff = d.o_rsc = d.o_vbuf = d.o_xb1 = d.o_xb2 = d.o_Kx = 0;
   d.bytes = o;
   return d;
 }

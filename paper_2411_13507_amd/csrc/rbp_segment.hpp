@@ -34,6 +34,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "rbp_internal.hpp"
 #include "rbp_wave.hpp"
@@ -80,12 +81,13 @@ __device__ __forceinline__ double sel3(int c, double a, double b, double d) {
 
 template <typename Real>
 struct Lds {
-  double *Hd, *Af, *rowval, *ybuf, *qbuf, *vA, *vB, *vC, *vD, *vE, *scal, *acte, *actc, *lam;
+  double *Hd, *Af, *ybuf, *qbuf, *vA, *vB, *vC, *vD, *vE, *scal, *acte, *actc, *lam;
   int *actid, *actside;
   Real *HfT, *Aff, *vbuf, *xb1, *xb2, *Kx;
-  double *Q1, *Rm;
-  double *cL1i, *cQ1, *cGd, *Rd;   // staged degree tables; reciprocal diagonal of R
-  double *Ri;                      // R^-1 (upper triangular, same stride as R)
+  double *rsc;                     // reachable-row scalings (ADMM set-up)
+  double *Q1;
+  double *cL1i;                    // staged degree table L1^-1
+  double *Ri;                      // R^-1, upper triangle packed by columns: (i, j) at j (j + 1) / 2 + i
 };
 
 template <typename Real>
@@ -93,7 +95,6 @@ __device__ Lds<Real> carve(char* s, const LdsDims& D) {
   Lds<Real> L;
   L.Hd = (double*)(s + D.o_Hd);
   L.Af = (double*)(s + D.o_Af);
-  L.rowval = (double*)(s + D.o_rowval);
   L.ybuf = (double*)(s + D.o_ybuf);
   L.qbuf = L.ybuf + D.ncol;
   L.vA = (double*)(s + D.o_vec);
@@ -114,11 +115,8 @@ __device__ Lds<Real> carve(char* s, const LdsDims& D) {
   L.xb2 = (Real*)(s + D.o_xb2);
   L.Kx = (Real*)(s + D.o_Kx);
   L.Q1 = (double*)(s + D.o_Q1);
-  L.Rm = (double*)(s + D.o_R);
+  L.rsc = (double*)(s + D.o_rsc);
   L.cL1i = (double*)(s + D.o_cst);
-  L.cQ1 = L.cL1i + kMaxFree * kMaxFree;
-  L.cGd = L.cQ1 + kMaxPts * kMaxPts;
-  L.Rd = (double*)(s + D.o_Rd);
   L.Ri = (double*)(s + D.o_Ri);
   return L;
 }
@@ -179,14 +177,15 @@ struct Inst {
   static constexpr int ND = 6 * P - 3;    // difference rows (velocity, acceleration)
   // odd row strides (in doubles) of the LDS copies read one row per lane,
   // so that a lane-strided 64-bit access touches distinct banks
-  static constexpr int NS = N | 1;        // basis Q1 and factor R
-  static constexpr int HDS = NC | 1;      // reachable rows
+  static constexpr int NS = N | 1;        // basis Q1
+  static constexpr int HDS = N | 1;       // reachable rows (their columns on the interior points)
   double T, T15, iT3, sv, sa, vmax, amax;
   double x0[6], P0[3], dg[3];
   int nf, r, F, RB, m, f0;
   int64_t r0, hb, po;
 
-  // coefficient of row ``id`` on full-vector entry e = 3*pt + c (pt = 0..P)
+  // coefficient of row ``id`` on entry 3*pt + c of the full vector: pt = 0..P
+  // for faces and differences, an interior point for a reachable row
   __device__ double coef(int id, int pt, int c, const double* Af, const double* Hd) const {
     if (id < F) {
       const int s = id / nf, j = id - s * nf;
@@ -202,7 +201,7 @@ struct Inst {
       if (cc != c) return 0.0;
       return sa * (double(pt == k + 2) - 2.0 * double(pt == k + 1) + double(pt == k));
     }
-    return Hd[(id - RB) * HDS + 3 * pt + c];
+    return Hd[(id - RB) * HDS + 3 * (pt - 1) + c];
   }
 
   // Entry i = 3t + c (t < P - 1) of the whitened normal L^-1 a of row ``id``
@@ -232,14 +231,15 @@ struct Inst {
       }
       return c == cc ? T15 * u : 0.0;
     }
-    return whiten_at<P>(Li0, T15, Hd + (id - RB) * HDS + 3, i);
+    return whiten_at<P>(Li0, T15, Hd + (id - RB) * HDS, i);
   }
 };
 
 // Copy n doubles (rows of RL values) from global memory into LDS rows of
-// stride LD, with eight loads in flight per lane before the first store (the
-// instance's rows arrive in one or two HBM round trips instead of one per
-// element).  Returns true if a value is not finite.
+// stride LD, without the first and last three columns (the pinned points),
+// with eight loads in flight per lane before the first store (the instance's
+// rows arrive in one or two HBM round trips instead of one per element).
+// Returns true if a value is not finite.
 template <int RL, int LD>
 __device__ __forceinline__ bool stage_rows(double* dst, const double* __restrict__ src, int n, int lane) {
   bool bad = false;
@@ -253,8 +253,9 @@ __device__ __forceinline__ bool stage_rows(double* dst, const double* __restrict
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int e = base + u * kWave + lane;
+      const int row = e / RL, col = e - RL * row - 3;
       if (e < n) {
-        dst[e + (e / RL) * (LD - RL)] = v[u];
+        if (col >= 0 && col < RL - 6) dst[row * LD + col] = v[u];
         bad |= !isfinite(v[u]);
       }
     }
@@ -262,18 +263,25 @@ __device__ __forceinline__ bool stage_rows(double* dst, const double* __restrict
   return bad;
 }
 
-// Sum of x[i] * v[i], i < n: x a per-lane LDS row, v an LDS vector; every
-// load is issued before the first product (the scheduler would otherwise
-// keep only a few in flight at this register pressure).
+// Sum of x[i] * v[i], i < n: x a per-lane LDS row, v an LDS vector; loads are
+// issued half a row at a time, ahead of their products (the scheduler would
+// otherwise keep only a few in flight; a whole row at once takes registers
+// that a third wavefront per SIMD needs).
 template <int n>
 __device__ __forceinline__ double dot_row(const double* x, const double* v) {
-  double a[n], b[n];
-#pragma unroll
-  for (int i = 0; i < n; ++i) { a[i] = x[i]; b[i] = v[i]; }
-  __builtin_amdgcn_sched_barrier(0);
+  constexpr int h = (n + 1) / 2;
   double acc = 0.0;
 #pragma unroll
-  for (int i = 0; i < n; ++i) acc += a[i] * b[i];
+  for (int i0 = 0; i0 < n; i0 += h) {
+    double a[h], b[h];
+#pragma unroll
+    for (int u = 0; u < h; ++u)
+      if (i0 + u < n) { a[u] = x[i0 + u]; b[u] = v[i0 + u]; }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < h; ++u)
+      if (i0 + u < n) acc += a[u] * b[u];
+  }
   return acc;
 }
 // acc - sum over k < q of col[k * stride] * v[k] (q uniform), subtracted in
@@ -295,16 +303,17 @@ __device__ __forceinline__ double colsub_q(double acc, const double* col, int st
   }
   return acc;
 }
-// Sum over lane <= k < q of row[k] * v[k] (the upper-triangular part of a
-// row), in order, loads issued six at a time.
-__device__ __forceinline__ double rowsum_upper_q(const double* row, const double* v, int lane, int q) {
+// Entry ``lane`` of S v, S upper triangular, packed by columns (the entries
+// of a column lie one per lane): the sum over lane <= k < q of S(lane, k) v[k],
+// in order, loads issued six at a time.
+__device__ __forceinline__ double upper_times_q(const double* S, const double* v, int lane, int q) {
   double acc = 0.0;
   for (int k0 = 0; k0 < q; k0 += 6) {
     double a[6], b[6];
 #pragma unroll
     for (int u = 0; u < 6; ++u) {
       const int k = k0 + u < q ? k0 + u : q - 1;
-      a[u] = row[k];
+      a[u] = S[k * (k + 1) / 2 + (lane <= k ? lane : k)];
       b[u] = v[k];
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -313,6 +322,22 @@ __device__ __forceinline__ double rowsum_upper_q(const double* row, const double
       if (k0 + u < q && k0 + u >= lane) acc += a[u] * b[u];
   }
   return acc;
+}
+
+// 1 / sqrt(x) (x > 0) and a / b (b > 0) from the hardware approximations,
+// refined by Newton steps to full precision
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  const double hx = 0.5 * x;
+  r = r * fma(-hx * r, r, 1.5);
+  return r * fma(-hx * r, r, 1.5);
+}
+__device__ __forceinline__ double div_nr(double a, double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = fma(fma(-b, r, 1.0), r, r);
+  r = fma(fma(-b, r, 1.0), r, r);
+  const double t = a * r;
+  return fma(fma(-b, t, a), r, t);
 }
 
 // ==========================================================================
@@ -372,7 +397,7 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
 
   // per-lane inputs of the row set-up, loaded ahead of the staging
   const double bj_in = lane < nf ? A.b_face[in.f0 + lane] : 0.0;
-  double h0_in[2] = {0.0, 0.0}, g_in[2][6];
+  double h0_in[2] = {0.0, 0.0}, g_in[2][6], hp_in[2][6];
 #pragma unroll
   for (int sl = 0; sl < 2; ++sl) {
     const int l = lane + kWave * sl;
@@ -380,6 +405,13 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     h0_in[sl] = on ? A.h0[in.r0 + l] : 0.0;
 #pragma unroll
     for (int e = 0; e < 6; ++e) g_in[sl][e] = on ? A.G[6 * (in.r0 + l) + e] : 0.0;
+    // the row's coefficients on the pinned points (not kept in LDS)
+    const double* hp = A.H + in.hb + (int64_t)l * NC;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      hp_in[sl][e] = on ? hp[e] : 0.0;
+      hp_in[sl][3 + e] = on ? hp[3 * P + e] : 0.0;
+    }
   }
 
   // debug option: poison the workgroup's LDS first, so that a read of a
@@ -396,13 +428,9 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     const int pt = lane / 3, c = lane - 3 * (lane / 3);
     L.ybuf[lane] = (pt == P) ? sel3(c, in.dg[0], in.dg[1], in.dg[2]) : 0.0;
   }
-  // degree tables read with lane-dependent indices (the Hessian and the
-  // difference-row Gram only for the ADMM matrix)
+  // the degree table read with lane-dependent indices in every step (the
+  // others, read once, come from constant memory)
   for (int e = lane; e < kMaxFree * kMaxFree; e += kWave) L.cL1i[e] = (&K.L1inv[0][0])[e];
-  for (int e = lane; e < kMaxPts * kMaxPts; e += kWave) L.cQ1[e] = (&K.Q1[0][0])[e];
-  if constexpr (kAdmm) {
-    for (int e = lane; e < kMaxFree * kMaxFree; e += kWave) L.cGd[e] = (&K.Gdiff[0][0])[e];
-  }
   bsync<kWS>();
 
   // ---- face rows: lane j < nf owns face j on every interior point
@@ -462,22 +490,24 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
       const double* hr = L.Hd + l * HDS;
       double b = h0_in[sl];
       for (int e = 0; e < 6; ++e) b += g_in[sl][e] * in.x0[e];
-      double s0 = 0, s1 = 0, s2 = 0;
-      for (int k = 0; k <= P; ++k) { s0 += hr[3 * k]; s1 += hr[3 * k + 1]; s2 += hr[3 * k + 2]; }
+      const double* hp = hp_in[sl];
+      double s0 = hp[0], s1 = hp[1], s2 = hp[2];
+      for (int k = 0; k < NFP; ++k) { s0 += hr[3 * k]; s1 += hr[3 * k + 1]; s2 += hr[3 * k + 2]; }
+      s0 += hp[3]; s1 += hp[4]; s2 += hp[5];
       b -= s0 * in.P0[0] + s1 * in.P0[1] + s2 * in.P0[2];
       ru[sl] = b;
       bad |= !isfinite(b);
-      rcst[sl] = hr[3 * P] * in.dg[0] + hr[3 * P + 1] * in.dg[1] + hr[3 * P + 2] * in.dg[2];
+      rcst[sl] = hp[3] * in.dg[0] + hp[4] * in.dg[1] + hp[5] * in.dg[2];
       double nn = 0.0;
       for (int c = 0; c < 3; ++c)
         for (int t = 0; t < NFP; ++t) {
           double w = 0.0;
-          for (int t2 = 0; t2 <= t; ++t2) w += K.L1inv[t][t2] * hr[3 * (t2 + 1) + c];
+          for (int t2 = 0; t2 <= t; ++t2) w += K.L1inv[t][t2] * hr[3 * t2 + c];
           nn += w * w;
         }
       const double wn = in.T15 * sqrt(nn);
       rdn[sl] = wn > 1e-300 ? 1.0 / wn : 0.0;
-      L.rowval[RB + l] = rdn[sl];   // scratch use: row scalings for the Gram below
+      if constexpr (kAdmm) L.rsc[l] = rdn[sl];   // row scalings for the Gram below
     }
   }
   if (wany(bad)) { finish_nan(kInvalid); return; }
@@ -516,9 +546,10 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
       // stage FP-Real copies of the rows used by the iteration
       for (int e = lane; e < r * N; e += kWave) {
         const int l = e / N, i = e - N * (e / N);
-        L.HfT[i * HS + l] = Real(L.Hd[l * HDS + 3 + i]);
+        L.HfT[i * HS + l] = Real(L.Hd[l * HDS + i]);
       }
       if (fl) { L.Aff[4 * lane] = Real(fa0); L.Aff[4 * lane + 1] = Real(fa1); L.Aff[4 * lane + 2] = Real(fa2); }
+      bsync<kWS>();
       {
         // Gram sum_l d_l^2 h_l h_l^T over reachable rows with v_mfma_f32_32x32x2f32:
         // A = B^T = scaled rows, two rows per instruction (lanes 0-31: row 2t,
@@ -530,7 +561,7 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
         for (int t = 0; 2 * t < r; ++t) {
           const int l = 2 * t + half;
           float av = 0.0f;
-          if (l < r && col < N) av = float(L.rowval[RB + l] * L.Hd[l * HDS + 3 + col]);
+          if (l < r && col < N) av = float(L.rsc[l] * L.Hd[l * HDS + col]);
           acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, av, acc, 0, 0, 0);
         }
 #pragma unroll
@@ -552,12 +583,13 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
           if (vl) {
             double v = 0.0;
             if (ci == vc)
-              v = in.iT3 * (2.0 * L.cQ1[kMaxPts * (si + 1) + vs + 1] + double(A.rho) * L.cGd[kMaxFree * si + vs]);
+              v = in.iT3 * (2.0 * K.Q1[si + 1][vs + 1] + double(A.rho) * K.Gdiff[si][vs]);
             if (si == vs) v += double(A.rho) * in.iT3 / K.kappa[si] * (ci == 0 ? gfa : (ci == 1 ? gfb : gfc));
             kc[i] = Real(v) + L.Kx[i * N + lane];
           }
         }
       }
+      bsync<kWS>();   // Kx is done with: vbuf, xb1 and xb2 share its LDS
       // Gauss-Jordan sweep on the register columns (K is symmetric positive
       // definite: no pivoting); afterwards kc = column ``lane`` of -K^{-1}
 #pragma unroll
@@ -577,7 +609,7 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
       if (vl) {
 #pragma unroll
         for (int j = 0; j < N; ++j) Mrow[j] = -kc[j];
-        qd = 2.0 * in.iT3 * L.cQ1[kMaxPts * (vs + 1) + P] * sel3(vc, in.dg[0], in.dg[1], in.dg[2]);
+        qd = 2.0 * in.iT3 * K.Q1[vs + 1][P] * sel3(vc, in.dg[0], in.dg[1], in.dg[2]);
       }
     }
     const Real qr = Real(qd);
@@ -771,7 +803,7 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     if (vl) {
 #pragma unroll
       for (int t = 0; t < NFP; ++t) {
-        const double qv = L.cQ1[kMaxPts * (vs + 1) + t + 1];
+        const double qv = K.Q1[vs + 1][t + 1];
         pc += qv * L.vD[3 * t + vc];
         pw += fabs(qv) * L.vE[3 * t + vc];
       }
@@ -805,19 +837,18 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   };
 
   // c = Q1 a, z = a - Q1^T c by classical Gram-Schmidt (a: vA in LDS and
-  // a_own, the lane's entry), then r = R^-1 c; lane i < N keeps z_i, lane
-  // k < q keeps c_k and r_k (c also in vC).  One pass leaves z orthogonal to
-  // the basis up to about eps |a| / |z|; a second pass re-orthogonalises when
-  // |z|^2 < 1e-2 |a|^2, i.e. when that loss could exceed about 10 eps (the
-  // "twice is enough" threshold of 1/2 would take it on nearly half of the
-  // steps here: face rows on neighbouring points are close in the whitened
-  // metric).
-  auto project = [&](double a_own, double& zz, double& aa, double& z_own, double& r_own, double& c_own) {
-    c_own = lane < q ? dot_row<N>(L.Q1 + lane * NS, L.vA) : 0.0;
+  // a_own, the lane's entry; aa = |a|^2), then r = R^-1 c; lane i < N keeps
+  // z_i, lane k < q keeps c_k and r_k (c also in vC).  One pass leaves z
+  // orthogonal to the basis up to about eps |a| / |z|; a second pass
+  // re-orthogonalises when |z|^2 < 1e-2 |a|^2, i.e. when that loss could
+  // exceed about 10 eps (the "twice is enough" threshold of 1/2 would take it
+  // on nearly half of the steps here: face rows on neighbouring points are
+  // close in the whitened metric).
+  auto project = [&](double a_own, double aa, double& zz, double& z_own, double& r_own) {
+    double c_own = lane < q ? dot_row<N>(L.Q1 + lane * NS, L.vA) : 0.0;
     if (lane < q) L.vC[lane] = c_own;
     bsync<kWS>();
     z_own = vl ? colsub_q(a_own, L.Q1 + lane, NS, L.vC, q) : 0.0;
-    aa = wsum(a_own * a_own);
     zz = wsum(z_own * z_own);
     if (zz < 1e-2 * aa && q > 0) {
       if (vl) L.vB[lane] = z_own;
@@ -831,41 +862,16 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
       zz = wsum(z_own * z_own);
       bsync<kWS>();
     }
-    r_own = lane < q ? rowsum_upper_q(L.Ri + lane * NS, L.vC, lane, q) : 0.0;
+    r_own = lane < q ? upper_times_q(L.Ri, L.vC, lane, q) : 0.0;
   };
 
-  // R^-1 rebuilt by back substitution after a downdate: lane j builds column
-  // j (entries i <= j); each lane reads back only its own column
-  auto ri_rebuild = [&]() {
-    for (int i = q - 1; i >= 0; --i) {
-      double acc = (i == lane) ? 1.0 : 0.0;
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        const double rik = L.Rm[i * NS + k], xk = L.Ri[k * NS + lane];
-        acc -= (k > i && k <= lane && k < q) ? rik * xk : 0.0;
-      }
-      if (lane < q && i <= lane) L.Ri[i * NS + lane] = acc * L.Rd[i];
-    }
-    bsync<kWS>();
-  };
-
-  // append the projected direction as a new basis column (R gets c and |z|;
-  // R^-1 gets -R^-1 c / |z| and 1/|z|, with rv = R^-1 c and c_own = c on
-  // lanes < q, z_own = z on lanes < N)
-  auto append = [&](double nz, int id, int side, double e_full, double c_full, double rv, double z_own,
-                    double c_own) {
-    const double inz = 1.0 / nz;
+  // append the projected direction as a new basis column: Q1 gets z / |z|,
+  // R^-1 the column (-R^-1 c, 1) / |z|, with rv = R^-1 c on lanes < q, z_own =
+  // z on lanes < N and inz = 1 / |z|
+  auto append = [&](double inz, int id, int side, double e_full, double c_full, double rv, double z_own) {
     if (vl) L.Q1[q * NS + lane] = z_own * inz;
-    if (lane < q) {
-      L.Rm[lane * NS + q] = c_own;
-      L.Ri[lane * NS + q] = -rv * inz;
-    }
-    if (lane == 0) {
-      L.Rm[q * NS + q] = nz;
-      L.Rd[q] = inz;
-      L.Ri[q * NS + q] = inz;
-      L.actid[q] = id; L.actside[q] = side; L.acte[q] = e_full; L.actc[q] = c_full;
-    }
+    if (lane <= q) L.Ri[q * (q + 1) / 2 + lane] = lane == q ? inz : -rv * inz;
+    if (lane == 0) { L.actid[q] = id; L.actside[q] = side; L.acte[q] = e_full; L.actc[q] = c_full; }
     int ol, bit;
     slot_of(id, ol, bit);
     if (lane == ol) act_bits |= (1u << bit);
@@ -873,88 +879,90 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     bsync<kWS>();
   };
 
-  // remove basis column kd: shift R columns, restore triangular form with
-  // Givens rotations applied to R rows and Q1 columns, shift active data
+  // Remove working-set row kd.  Row kd of S = R^-1, s, gives the direction of
+  // the basis that only this row needs (Q1^T s is orthogonal to the other
+  // normals), so the new basis is its complement: Givens rotations of the
+  // columns (kd, kd+1), (kd+1, kd+2), ... gather s in the last one, which is
+  // dropped together with row kd of S.  With P_j = s_kd^2 + .. + s_j^2 the
+  // rotation of (j, j+1) has sine sqrt(P_j / P_{j+1}) and cosine s_{j+1} /
+  // sqrt(P_{j+1}): lane j forms its pair from the running sums, and the loop
+  // carries one basis entry and one entry of a row of S per lane from column to
+  // column (no rotation waits for another's result in LDS, and S needs no
+  // rebuilding: against rotating R and inverting it again a drop takes a
+  // fraction of the time).  The signs keep the diagonal of S positive.
   auto drop = [&](int kd) {
-    constexpr int EPL = (N * N + kWave - 1) / kWave;
-    const int ln = opaque(lane);
     {
       int own, bit;
       slot_of(L.actid[kd], own, bit);
       if (lane == own) act_bits &= ~(1u << bit);
     }
-    double tmp[EPL];
-#pragma unroll
-    for (int u = 0; u < EPL; ++u) {
-      const int e = ln + kWave * u;
-      const int row = e / N, col = e - N * (e / N);
-      tmp[u] = (e < N * N && row < q && col >= kd && col < q - 1) ? L.Rm[row * NS + col + 1] : 0.0;
-    }
+    const bool mid = lane >= kd && lane < q;
+    const double sj = mid ? L.Ri[lane * (lane + 1) / 2 + kd] : 0.0;
+    const double sn1 = (mid && lane < q - 1) ? L.Ri[(lane + 1) * (lane + 2) / 2 + kd] : 0.0;   // s_{j+1}
     int id_n = 0, sd_n = 0;
     double e_n = 0, c_n = 0;
     if (lane >= kd && lane < q - 1) {
       id_n = L.actid[lane + 1]; sd_n = L.actside[lane + 1]; e_n = L.acte[lane + 1]; c_n = L.actc[lane + 1];
     }
     const double lam_n = __shfl(lamr, (lane + 1) & 63, kWave);
-    bsync<kWS>();
-#pragma unroll
-    for (int u = 0; u < EPL; ++u) {
-      const int e = ln + kWave * u;
-      const int row = e / N, col = e - N * (e / N);
-      if (e < N * N && row < q && col >= kd && col < q - 1) L.Rm[row * NS + col] = tmp[u];
+    double run = 0.0, pj = 1.0, pn = 1.0;
+    const double s2 = sj * sj;
+    for (int j = kd; j < q; ++j) {
+      run += wave::bcast(s2, j);
+      if (lane == j) pj = run;
+      if (lane + 1 == j) pn = run;
     }
+    const double ipn = rsqrt_nr(pn);
+    const double cosv = sn1 * ipn, sinv = (pj * rsqrt_nr(pj)) * ipn;
+    bsync<kWS>();
     if (lane >= kd && lane < q - 1) {
       L.actid[lane] = id_n; L.actside[lane] = sd_n; L.acte[lane] = e_n; L.actc[lane] = c_n;
       lamr = lam_n;
     }
-    bsync<kWS>();
+    const int li = lane < N ? lane : 0;                  // basis entry of this lane
+    const int lr = lane < q ? lane : q - 1;              // row of S of this lane
+    const int lw = lane > kd ? lane - 1 : lane;          // its new place (row kd goes)
+    double qa = L.Q1[kd * NS + li];
+    double sa = lr <= kd ? L.Ri[kd * (kd + 1) / 2 + lr] : 0.0;
+    double qb = L.Q1[(kd + 1 < q ? kd + 1 : kd) * NS + li];
+    double sb = kd + 1 < q ? L.Ri[(kd + 1) * (kd + 2) / 2 + (lr <= kd + 1 ? lr : 0)] : 0.0;
     for (int j = kd; j < q - 1; ++j) {
-      const double a = L.Rm[j * NS + j], b = L.Rm[(j + 1) * NS + j];
-      const double rr_ = hypot(a, b);
-      const double cg = rr_ > 0.0 ? a / rr_ : 1.0, sg = rr_ > 0.0 ? b / rr_ : 0.0;
-      double r1 = 0, r2 = 0, qa = 0, qb = 0;
-      if (lane >= j && lane < q - 1) { r1 = L.Rm[j * NS + lane]; r2 = L.Rm[(j + 1) * NS + lane]; }
-      if (vl) { qa = L.Q1[j * NS + lane]; qb = L.Q1[(j + 1) * NS + lane]; }
-      bsync<kWS>();
-      if (lane >= j && lane < q - 1) {
-        L.Rm[j * NS + lane] = cg * r1 + sg * r2;
-        L.Rm[(j + 1) * NS + lane] = -sg * r1 + cg * r2;
-      }
-      if (vl) {
-        L.Q1[j * NS + lane] = cg * qa + sg * qb;
-        L.Q1[(j + 1) * NS + lane] = -sg * qa + cg * qb;
-      }
-      bsync<kWS>();
+      const int jn = j + 2 < q ? j + 2 : j + 1;          // next column, loaded ahead
+      const double qn = L.Q1[jn * NS + li];
+      const double sn = L.Ri[jn * (jn + 1) / 2 + (lr <= jn ? lr : 0)];
+      const double c = wave::bcast(cosv, j), w = wave::bcast(sinv, j);
+      const double sbm = lr <= j + 1 ? sb : 0.0;
+      if (vl) L.Q1[j * NS + lane] = w * qb - c * qa;
+      qa = w * qa + c * qb;
+      if (lane < q && lane != kd && lw <= j) L.Ri[j * (j + 1) / 2 + lw] = w * sbm - c * sa;
+      sa = w * sa + c * sbm;
+      qb = qn;
+      sb = sn;
     }
     --q;
     if (lane >= q) lamr = 0.0;
-    if (lane < q) L.Rd[lane] = 1.0 / L.Rm[lane * NS + lane];
     bsync<kWS>();
-    ri_rebuild();
   };
 
   // multipliers of the current working set at the minimiser on its face:
-  // R^T w = e_free, R lam = Q1^T v0 - w   (lane k holds entry k)
+  // R^T w = e_free, E = Q1^T v0 - w, R lam = E (lane k holds entry k; E stays
+  // in vE)
   auto solve_lambda = [&]() {
-    double w = (lane < q) ? (L.acte[lane] - L.actc[lane]) : 0.0;
-    for (int k = 0; k < q; ++k) {
-      const double wk = wave::bcast(w, k) * L.Rd[k];
-      if (lane == k) w = wk;
-      else if (lane > k && lane < q) w -= L.Rm[k * NS + lane] * wk;
-    }
+    if (lane < q) L.vC[lane] = L.acte[lane] - L.actc[lane];
     if (vl) L.vD[lane] = v0;
     bsync<kWS>();
-    double u = 0.0;
     if (lane < q) {
-      for (int i = 0; i < N; ++i) u += L.Q1[lane * NS + i] * L.vD[i];
-      u -= w;
+      const double* col = L.Ri + lane * (lane + 1) / 2;   // column ``lane`` of R^-1
+      double w = 0.0;
+#pragma unroll 6
+      for (int j = 0; j < N; ++j) {
+        const double a = col[j <= lane ? j : 0], e = L.vC[j < q ? j : 0];
+        w += j <= lane ? a * e : 0.0;
+      }
+      L.vE[lane] = dot_row<N>(L.Q1 + lane * NS, L.vD) - w;
     }
-    for (int k = q - 1; k >= 0; --k) {
-      const double lk = wave::bcast(u, k) * L.Rd[k];
-      if (lane == k) u = lk;
-      else if (lane < k) u -= L.Rm[lane * NS + k] * lk;
-    }
-    lamr = (lane < q) ? u : 0.0;
+    bsync<kWS>();
+    lamr = lane < q ? upper_times_q(L.Ri, L.vE, lane, q) : 0.0;
     bsync<kWS>();
   };
 
@@ -997,9 +1005,10 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     bsync<kWS>();
     const double e_full = L.scal[0], c_full = L.scal[1];
     const double a_own = build_normal(id, side);
-    double zz, aa, z_own, r_own, c_own;
-    project(a_own, zz, aa, z_own, r_own, c_own);
-    if (zz > 1e-16 * aa && q < N) append(sqrt(zz), id, side, e_full, c_full, r_own, z_own, c_own);
+    double zz, z_own, r_own;
+    const double aa = wsum(a_own * a_own);
+    project(a_own, aa, zz, z_own, r_own);
+    if (zz > 1e-16 * aa && q < N) append(rsqrt_nr(zz), id, side, e_full, c_full, r_own, z_own);
   }
   if (q == 0) {
     // no warm start: the unconstrained minimiser
@@ -1014,103 +1023,101 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
       if (q == 0 || mn >= 0.0) break;
       drop(kd);
     }
-    // v = v0 - Q1 R lam
-    if (lane < q) L.vD[lane] = lamr;
-    bsync<kWS>();
-    if (lane < q) {
-      double acc = 0.0;
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        const double rk = L.Rm[lane * NS + k], dk = L.vD[k];
-        acc += (k >= lane && k < q) ? rk * dk : 0.0;
-      }
-      L.vE[lane] = acc;
-    }
-    bsync<kWS>();
-    if (vl) {
-      double acc = v0;
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        const double qk = L.Q1[k * NS + lane], ek = L.vE[k];
-        acc -= (k < q) ? qk * ek : 0.0;
-      }
-      vw = acc;
-    }
+    // v = v0 - Q1 R lam (R lam in vE from the last solve_lambda)
+    if (vl) vw = colsub_q(v0, L.Q1 + lane, NS, L.vE, q);
     bsync<kWS>();
   }
 
   // ---- main loop
-  // Evaluate every owned row at the current point (row values to rowval) and
-  // return the lane's most violated inactive row as (score, key).
-  // Each lane also keeps, for its own best candidate, the violation
-  // side * value - e_full and the row's e_full and c_full, which the owning
-  // lane hands to the others afterwards (no second evaluation).  The free
-  // entries of the point are uniform: they are loaded once, together with
-  // the lane's reachable-row coefficients, before any of them is used (the
-  // pinned entries of y~ are 0 at P_0 and the goal offset, whose product
-  // with a reachable row is the constant rcst).
-  auto eval_rows = [&](double& best, int& key, double& sv_b, double& e_b, double& c_b) {
+  // Evaluate every owned row at the current point and return the lane's most
+  // violated inactive row as (score, key), with the violation side * value -
+  // e_full, the row's e_full and c_full and its scaling 1 / |L^-1 a|, which the
+  // owning lane hands to the others afterwards (no second evaluation).  The
+  // free entries of the point are uniform; they are loaded half at a time,
+  // together with the lane's reachable-row coefficients, before any of them is
+  // used (the pinned entries of y~ are 0 at P_0 and the goal offset, whose
+  // product with a reachable row is the constant rcst).
+  // kLast: no candidates; the largest excess over the bounds and the largest
+  // magnitude of values and bounds instead.
+  constexpr int HP = (NFP + 1) / 2;              // interior points per half
+  auto eval_rows = [&](auto last, double& best, int& key, double& sv_b, double& e_b, double& c_b, double& d_b,
+                       double& pres, double& pscale) {
+    constexpr bool kLast = decltype(last)::value;
     const int ln = opaque(lane);   // addresses formed here, not held across the loop
-    best = -1.0; key = 0x7fffffff; sv_b = 0.0; e_b = 0.0; c_b = 0.0;
-    double y[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) y[i] = L.ybuf[3 + i];
+    best = -1.0; key = 0x7fffffff; sv_b = 0.0; e_b = 0.0; c_b = 0.0; d_b = 0.0;
+    pres = 0.0; pscale = 0.0;
     // difference rows: lane-dependent entries, branch-free (a velocity lane
     // reads its first entry twice and gives it weight 0)
     const int di0 = 3 * dk + dc, di1 = di0 + 3, di2 = dvel ? di0 : di0 + 6;
     const double yd0 = dl ? L.ybuf[di0] : 0.0, yd1 = dl ? L.ybuf[di1] : 0.0, yd2 = dl ? L.ybuf[di2] : 0.0;
     // reachable row ``lane`` (row 0 stands in on lanes without one)
-    double hv[N];
-    {
-      const double* hr = L.Hd + (ln < r ? ln : 0) * HDS + 3;
+    const double* hr = L.Hd + (ln < r ? ln : 0) * HDS;
+    const double* hr2 = L.Hd + (ln + kWave < r ? ln + kWave : 0) * HDS;
+    double acc = 0.0, acc2 = 0.0;
 #pragma unroll
-      for (int i = 0; i < N; ++i) hv[i] = hr[i];
-    }
-    if (fl) {
+    for (int s0 = 0; s0 < NFP; s0 += HP) {
+      double y[3 * HP], hv[3 * HP];
 #pragma unroll
-      for (int s = 0; s < NFP; ++s) {
-        const double v = fa0 * y[3 * s] + fa1 * y[3 * s + 1] + fa2 * y[3 * s + 2];
-        const int id = s * nf + lane;
-        L.rowval[s * nf + ln] = v;
-        const double viol = v - fu;
-        if (!((act_bits >> s) & 1u) && viol > ftol * (1.0 + fabs(fu))) {
-          const double sc = viol * (ifan * K.rkappa[s]);
-          if (sc > best) { best = sc; key = 2 * id + 1; sv_b = viol; e_b = fu; c_b = 0.0; }
+      for (int i = 0; i < 3 * HP; ++i)
+        if (3 * s0 + i < N) { y[i] = L.ybuf[3 + 3 * s0 + i]; hv[i] = hr[3 * s0 + i]; }
+#pragma unroll
+      for (int u = 0; u < HP; ++u) {
+        const int s = s0 + u;
+        if (s < NFP && fl) {
+          const double v = fa0 * y[3 * u] + fa1 * y[3 * u + 1] + fa2 * y[3 * u + 2];
+          const double viol = v - fu;
+          if constexpr (kLast) {
+            pres = fmax(pres, viol);
+            pscale = fmax(pscale, fmax(fabs(v), fabs(fu)));
+          } else if (!((act_bits >> s) & 1u) && viol > ftol * (1.0 + fabs(fu))) {
+            const double dn = ifan * K.rkappa[s];
+            const double sc = viol * dn;
+            if (sc > best) { best = sc; key = 2 * (s * nf + lane) + 1; sv_b = viol; e_b = fu; c_b = 0.0; d_b = dn; }
+          }
         }
+      }
+#pragma unroll
+      for (int i = 0; i < 3 * HP; ++i)
+        if (3 * s0 + i < N) acc += hv[i] * y[i];
+      if (r > kWave) {   // second reachable slot: rows 64..127
+#pragma unroll
+        for (int i = 0; i < 3 * HP; ++i)
+          if (3 * s0 + i < N) hv[i] = hr2[3 * s0 + i];
+#pragma unroll
+        for (int i = 0; i < 3 * HP; ++i)
+          if (3 * s0 + i < N) acc2 += hv[i] * y[i];
       }
     }
     if (dl) {
       const double v = dvel ? dsc * (yd1 - yd0) : dsc * (yd2 - 2.0 * yd1 + yd0);
-      L.rowval[F + ln] = v;
-      if (!((act_bits >> NFP) & 1u)) {
-        const double vu = v - dbd, vlo = dlo_of(dbd) - v, dtol = ftol * (1.0 + fabs(dbd));
-        if (vu > dtol && vu * ddn > best) { best = vu * ddn; key = 2 * (F + lane) + 1; sv_b = vu; e_b = dbd; c_b = dcst; }
+      const double vu = v - dbd, vlo = dlo_of(dbd) - v;
+      if constexpr (kLast) {
+        pres = fmax(pres, fmax(vu, vlo));
+        pscale = fmax(pscale, fmax(fabs(v), fabs(dbd)));
+      } else if (!((act_bits >> NFP) & 1u)) {
+        const double dtol = ftol * (1.0 + fabs(dbd));
+        if (vu > dtol && vu * ddn > best) {
+          best = vu * ddn; key = 2 * (F + lane) + 1; sv_b = vu; e_b = dbd; c_b = dcst; d_b = ddn;
+        }
         if (vlo > dtol && vlo * ddn > best) {
-          best = vlo * ddn; key = 2 * (F + lane); sv_b = vlo; e_b = -dlo_of(dbd); c_b = -dcst;
+          best = vlo * ddn; key = 2 * (F + lane); sv_b = vlo; e_b = -dlo_of(dbd); c_b = -dcst; d_b = ddn;
         }
       }
     }
-    auto reach_row = [&](int sl, const double (&h)[N]) {
+    auto reach_row = [&](int sl, double a) {
       const int l = lane + kWave * sl;
-      const int lo = ln + kWave * sl;
-      double acc = 0.0;
-#pragma unroll
-      for (int i = 0; i < N; ++i) acc += h[i] * y[i];
-      const double v = acc + rcst[sl];
-      L.rowval[RB + lo] = v;
+      const double v = a + rcst[sl];
       const double viol = v - ru[sl];
-      if (!((act_bits >> (NFP + 1 + sl)) & 1u) && viol > ftol * (1.0 + fabs(ru[sl]))) {
+      if constexpr (kLast) {
+        pres = fmax(pres, viol);
+        pscale = fmax(pscale, fmax(fabs(v), fabs(ru[sl])));
+      } else if (!((act_bits >> (NFP + 1 + sl)) & 1u) && viol > ftol * (1.0 + fabs(ru[sl]))) {
         const double sc = rdn[sl] > 0.0 ? viol * rdn[sl] : __builtin_huge_val();
-        if (sc > best) { best = sc; key = 2 * (RB + l) + 1; sv_b = viol; e_b = ru[sl]; c_b = rcst[sl]; }
+        if (sc > best) { best = sc; key = 2 * (RB + l) + 1; sv_b = viol; e_b = ru[sl]; c_b = rcst[sl]; d_b = rdn[sl]; }
       }
     };
-    if (lane < r) reach_row(0, hv);
-    if (r > kWave) {   // second reachable slot: rows 64..127
-      const double* hr = L.Hd + (ln + kWave < r ? ln + kWave : 0) * HDS + 3;
-#pragma unroll
-      for (int i = 0; i < N; ++i) hv[i] = hr[i];
-      if (lane + kWave < r) reach_row(1, hv);
-    }
+    if (lane < r) reach_row(0, acc);
+    if (r > kWave && lane + kWave < r) reach_row(1, acc2);
   };
   // x-space point from the whitened one; vD holds vw (written after every
   // update of vw, ahead of a barrier)
@@ -1160,47 +1167,46 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   bool certified_infeasible = false;
   while (true) {
     refresh_y();
-    double best, sv_b, e_b, c_b;
+    double best, sv_b, e_b, c_b, d_b, un0, un1;
     int key;
-    eval_rows(best, key, sv_b, e_b, c_b);   // the last pass leaves the solution's row values
+    eval_rows(std::false_type{}, best, key, sv_b, e_b, c_b, d_b, un0, un1);
     // the largest score; among equal scores the lowest lane's candidate
-    const double gbest = wmax(best);
-    if (!(gbest > 0.0)) { status = kSolved; break; }
-    const int owner = __builtin_ctzll(__ballot(best == gbest));
+    const int owner = wave::argmax_positive(best);
+    if (owner < 0) { status = kSolved; break; }
     key = __builtin_amdgcn_readlane(key, owner);
     if (steps >= max_steps || key < 0 || (key >> 1) >= m) { status = kPolishFailed; break; }
     const int id = key >> 1, side = (key & 1) ? 1 : -1;
     // the owning lane hands over its violation (> 0), full-row bound and
-    // constant
+    // constant, and the norm of the whitened normal
     double splus = wave::bcast(sv_b, owner);
     const double e_full = wave::bcast(e_b, owner), c_full = wave::bcast(c_b, owner);
+    const double dn = wave::bcast(d_b, owner);
+    const double aa = dn > 0.0 ? div_nr(1.0, dn * dn) : 0.0;
     const double a_own = build_normal(id, side);
     double lamp = 0.0;
     bool added = false;
     while (!added) {
       ++steps;
-      double zz, aa, z_own, rv, c_own;   // |z|^2, |a|^2, z_i, r = R^-1 c and c on lanes < q
-      project(a_own, zz, aa, z_own, rv, c_own);
+      double zz, z_own, rv;   // |z|^2, z_i, r = R^-1 c on lanes < q
+      project(a_own, aa, zz, z_own, rv);
       // step to the first multiplier that reaches 0: the smallest lam_k / r_k
-      // over r_k > 1e-13 max |r|.  The arg-min over every r_k > 0 and the
-      // maximum are reduced together; only when the winner's r_k is below
-      // the threshold (rare) is the arg-min taken again over the others.
+      // over r_k > 1e-13 max |r|.  The arg-min is taken over every r_k > 0 and
+      // only when the winner's r_k is below the threshold (rare) again over
+      // the others.
       double t1 = __builtin_huge_val();
-      int kd = lane;
+      int kd = 0;
       if (q > 0) {
-        double rmax = (lane < q) ? fabs(rv) : 0.0;
-        if (lane < q && rv > 0.0) t1 = lamr / rv;
-        rmax = wmax(rmax);
-        wargmin(t1, kd);
-        if (t1 < __builtin_huge_val() && !(wave::bcast(rv, kd) > 1e-13 * rmax)) {
-          t1 = __builtin_huge_val();
-          kd = lane;
-          if (lane < q && rv > 1e-13 * rmax) t1 = lamr / rv;
-          wargmin(t1, kd);
+        const double rmax = wave::max_abs_hi(lane < q ? rv : 0.0);
+        double tk = (lane < q && rv > 0.0) ? div_nr(lamr, rv) : __builtin_huge_val();
+        kd = wave::argmin_lane(tk);
+        if (!(wave::bcast(rv, kd) > 1e-13 * rmax)) {
+          if (!(lane < q && rv > 1e-13 * rmax)) tk = __builtin_huge_val();
+          kd = wave::argmin_lane(tk);
         }
+        t1 = wave::bcast(tk, kd);
       }
       const bool zfull = zz > 1e-20 * aa;
-      const double t2 = zfull ? splus / zz : __builtin_huge_val();
+      const double t2 = zfull ? div_nr(splus, zz) : __builtin_huge_val();
       if (!(t1 < 1e300) && !(t2 < 1e300)) {
         // infeasible: Farkas weights 1 on the entering constraint, -r_k >= 0 on the working set
         if (lane < q) L.lam[lane] = fmax(-rv, 0.0);
@@ -1256,7 +1262,7 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
         }
       }
       if (t2 <= t1) {
-        append(sqrt(zz), id, side, e_full, c_full, rv, z_own, c_own);
+        append(rsqrt_nr(zz), id, side, e_full, c_full, rv, z_own);
         if (lane == q - 1) lamr = lamp;
         added = true;
       } else {
@@ -1275,40 +1281,23 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   }
 
   // ---- solution, KKT residuals, cost
-  // ybuf and rowval hold the solution and its row values from the main
-  // loop's last pass (no row was violated there).  Every lane forms its
-  // partial values first; the reductions then run together.
+  // ybuf holds the solution (the main loop's last pass found no violated
+  // row).  Every lane forms its partial values first; the reductions then
+  // run together.
   bsync<kWS>();
   // primal residual and scale over all rows (owners)
-  double pres = 0.0, pscale = 0.0;
-  if (fl) {
-#pragma unroll
-    for (int s = 0; s < NFP; ++s) {
-      const double v = L.rowval[s * nf + lane];
-      pres = fmax(pres, v - fu);
-      pscale = fmax(pscale, fmax(fabs(v), fabs(fu)));
-    }
-  }
-  if (dl) {
-    const double v = L.rowval[F + lane];
-    pres = fmax(pres, fmax(v - dbd, dlo_of(dbd) - v));
-    pscale = fmax(pscale, fmax(fabs(v), fabs(dbd)));
-  }
-#pragma unroll
-  for (int sl = 0; sl < 2; ++sl) {
-    const int l = lane + kWave * sl;
-    if (l < r) {
-      const double v = L.rowval[RB + l];
-      pres = fmax(pres, v - ru[sl]);
-      pscale = fmax(pscale, fmax(fabs(v), fabs(ru[sl])));
-    }
+  double pres, pscale;
+  {
+    double u0, u1, u2, u3, u4;
+    int uk;
+    eval_rows(std::true_type{}, u0, uk, u1, u2, u3, u4, pres, pscale);
   }
   // (Q y~)_e for every full coefficient, cost = y~^T Q y~
   double qy = 0.0, yq = 0.0;
   if (lane < NC) {
     const int pt = lane / 3, c = lane - 3 * (lane / 3);
 #pragma unroll
-    for (int b = 0; b <= P; ++b) qy += L.cQ1[kMaxPts * pt + b] * L.ybuf[3 * b + c];
+    for (int b = 0; b <= P; ++b) qy += K.Q1[pt][b] * L.ybuf[3 * b + c];
     qy *= in.iT3;
     L.qbuf[lane] = qy;
     yq = qy * L.ybuf[lane];
@@ -1318,8 +1307,20 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   double cres = 0.0, lmax = 0.0;
   if (lane < q) {
     L.lam[lane] = lam_own;
+    // value of working-set row ``lane``
     const int id = L.actid[lane];
-    const double slack = L.acte[lane] - double(L.actside[lane]) * L.rowval[id];
+    double v;
+    if (id < F) {
+      const int s = id / nf, j = id - s * nf;
+      v = L.Af[3 * j] * L.ybuf[3 * s + 3] + L.Af[3 * j + 1] * L.ybuf[3 * s + 4] + L.Af[3 * j + 2] * L.ybuf[3 * s + 5];
+    } else if (id < RB) {
+      const int l = id - F, e = l < 3 * P ? l : l - 3 * P;   // 3 k + c, of y~ too
+      v = l < 3 * P ? in.sv * (L.ybuf[e + 3] - L.ybuf[e])
+                    : in.sa * (L.ybuf[e + 6] - 2.0 * L.ybuf[e + 3] + L.ybuf[e]);
+    } else {
+      v = dot_row<N>(L.Hd + (id - RB) * HDS, L.ybuf + 3) + L.actc[lane];
+    }
+    const double slack = L.acte[lane] - double(L.actside[lane]) * v;
     cres = lam_own * fabs(slack);
     lmax = lam_own;
   }
@@ -1336,11 +1337,26 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   if (vl) {
     const int pt = vs + 1;
     sq = 2.0 * L.qbuf[3 + lane];
-    for (int k = 0; k < q; ++k) {
-      const int idk = __builtin_amdgcn_readlane(id_r, k);
-      const double ls = wave::bcast(ls_r, k);
-      sac += ls * in.coef(idk, pt, vc, L.Af, L.Hd);
-      if (A.store) spin += ls * in.coef(idk, ppt, pc, L.Af, L.Hd);
+    for (int k0 = 0; k0 < q; k0 += 6) {
+      // a reachable row's coefficients on the pinned points come from global
+      // memory (lanes 0..5), six rows in flight
+      double hp[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+      if (A.store && lane < 6) {
+#pragma unroll
+        for (int u = 0; u < 6; ++u) {
+          const int idk = __builtin_amdgcn_readlane(id_r, k0 + u < q ? k0 + u : k0);
+          if (idk >= RB) hp[u] = A.H[in.hb + (int64_t)(idk - RB) * NC + 3 * ppt + pc];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        if (k0 + u < q) {
+          const int idk = __builtin_amdgcn_readlane(id_r, k0 + u);
+          const double ls = wave::bcast(ls_r, k0 + u);
+          sac += ls * in.coef(idk, pt, vc, L.Af, L.Hd);
+          if (A.store) spin += ls * (idk >= RB ? hp[u] : in.coef(idk < RB ? idk : 0, ppt, pc, L.Af, L.Hd));
+        }
+      }
     }
     st = sq + sac;
   }
@@ -1374,10 +1390,9 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     A.st_lam[b + lane] = L.lam[lane];
   }
   // the factor of the final working set for the backward pass, packed:
-  // rows k < q of Q1 (N entries each), then the q x q block of R (upper
-  // triangle written), element-parallel
+  // rows k < q of Q1 (N entries each), then R^-1 as in LDS, element-parallel
   if (A.store) {
-    constexpr int EPL = (N * N + kWave - 1) / kWave;
+    constexpr int EPL = (N * N + kWave - 1) / kWave, TPL = (N * (N + 1) / 2 + kWave - 1) / kWave;
     const int S = A.st_stride;
     double* qr = A.st_qr + (int64_t)inst * 2 * S * S;
     const int ln = opaque(lane);
@@ -1385,10 +1400,12 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     for (int u = 0; u < EPL; ++u) {
       const int e = ln + kWave * u;
       const int k = e / N, i = e - N * (e / N);
-      if (k < q) {
-        qr[k * N + i] = L.Q1[k * NS + i];
-        if (i >= k && i < q) qr[q * N + k * q + i] = L.Rm[k * NS + i];
-      }
+      if (k < q) qr[e] = L.Q1[k * NS + i];
+    }
+#pragma unroll
+    for (int u = 0; u < TPL; ++u) {
+      const int e = ln + kWave * u;
+      if (e < q * (q + 1) / 2) qr[q * N + e] = L.Ri[e];
     }
   }
 }
@@ -1487,27 +1504,29 @@ __device__ void backward_instance(const BackArgs& A, const InstDesc& idesc, char
       if (dst[u] >= 0) L.Hd[dst[u]] = v[u];
   }
   // the factor of the final working set (packed by the forward pass: rows
-  // k < q of Q1, then the q x q block of R)
+  // k < q of Q1, then R^-1)
   {
-    constexpr int EPL = (N * N + kWave - 1) / kWave;
+    constexpr int EPL = (N * N + kWave - 1) / kWave, TPL = (N * (N + 1) / 2 + kWave - 1) / kWave;
     const int S = A.st_stride;
     const double* qr = A.st_qr + (int64_t)inst * 2 * S * S;
 #pragma unroll
     for (int u = 0; u < EPL; ++u) {
       const int e = lane + kWave * u;
       const int k = e / N, i = e - N * (e / N);
-      if (k < q) {
-        L.Q1[k * NS + i] = qr[k * N + i];
-        if (i >= k && i < q) L.Rm[k * NS + i] = qr[q * N + k * q + i];
-      }
+      if (k < q) L.Q1[k * NS + i] = qr[e];
+    }
+#pragma unroll
+    for (int u = 0; u < TPL; ++u) {
+      const int e = lane + kWave * u;
+      if (e < q * (q + 1) / 2) L.Ri[e] = qr[q * N + e];
     }
   }
   __syncthreads();
   const bool vl = lane < N;
   const int vs = lane / 3, vc = lane - 3 * (lane / 3);
   // the factor of the active normals (whitened, in stored order), kept by
-  // the forward pass; a diagonal entry near 0 flags dependent active rows
-  const bool dep = wany(lane < q && !(L.Rm[lane * NS + lane] > 1e-10));
+  // the forward pass; a diagonal entry of R near 0 flags dependent active rows
+  const bool dep = wany(lane < q && !(L.Ri[lane * (lane + 1) / 2 + lane] < 1e10));
   // whitened upstream gradient on the free variables
   if (vl) L.vD[lane] = L.qbuf[3 + lane];
   __syncthreads();
@@ -1518,12 +1537,7 @@ __device__ void backward_instance(const BackArgs& A, const InstDesc& idesc, char
   const double cv = lane < q ? dot_row<N>(L.Q1 + lane * NS, L.vA) : 0.0;
   if (lane < q) L.vE[lane] = cv;
   __syncthreads();
-  double om = cv;
-  for (int k = q - 1; k >= 0; --k) {
-    const double ok = wave::bcast(om, k) / L.Rm[k * NS + k];
-    if (lane == k) om = ok;
-    else if (lane < k) om -= L.Rm[lane * NS + k] * ok;
-  }
+  const double om = lane < q ? upper_times_q(L.Ri, L.vE, lane, q) : 0.0;
   if (vl) L.vB[lane] = colsub_q(gh, L.Q1 + lane, NS, L.vE, q);
   __syncthreads();
   if (vl) L.vC[lane] = unwhiten_at<P>(L.cL1i, in.T15, L.vB, lane);   // w on the free vars

@@ -125,6 +125,56 @@ __device__ __forceinline__ void arg_reduce(double& v, int& id) {
 __device__ __forceinline__ void argmax(double& v, int& id) { arg_reduce<true>(v, id); }
 __device__ __forceinline__ void argmin(double& v, int& id) { arg_reduce<false>(v, id); }
 
+// 32-bit maxima: the exchange within a row is part of the instruction
+__device__ __forceinline__ int max_i32(int v) {
+  auto mx = [](int a, int b) { return a > b ? a : b; };
+  v = mx(v, dpp_i32<kXor1>(v));
+  v = mx(v, dpp_i32<kXor2>(v));
+  v = mx(v, dpp_i32<kHalfMirror>(v));
+  v = mx(v, dpp_i32<kMirror>(v));
+  PairI p = swap16_i32(v);
+  v = mx(p.a, p.b);
+  p = swap32_i32(v);
+  return __builtin_amdgcn_readfirstlane(mx(p.a, p.b));
+}
+__device__ __forceinline__ unsigned max_u32(unsigned v) {
+  return static_cast<unsigned>(max_i32(static_cast<int>(v ^ 0x80000000u))) ^ 0x80000000u;
+}
+// Lane of the largest 64-bit key among the lanes (the lowest of equal ones):
+// the high words first, a quarter of the instructions of a 64-bit maximum,
+// and the low words only where high words tie.
+__device__ __forceinline__ int argmax_key(int hi, unsigned lo, int himax) {
+  unsigned long long at = __ballot(hi == himax);
+  if (at & (at - 1ull)) {
+    const unsigned lmax = max_u32(hi == himax ? lo : 0u);
+    at = __ballot(hi == himax && lo == lmax);
+  }
+  return __builtin_ctzll(at);
+}
+// lane of the largest v > 0, the lowest of equal ones; -1 where none is
+__device__ __forceinline__ int argmax_positive(double v) {
+  const long long b = __double_as_longlong(v);
+  const int hi = v > 0.0 ? int(b >> 32) : -1;
+  const int himax = max_i32(hi);
+  if (himax < 0) return -1;
+  return argmax_key(hi, unsigned(b & 0xffffffffll), himax);
+}
+// lane of the smallest v (no NaN), the lowest of equal ones
+__device__ __forceinline__ int argmin_lane(double v) {
+  // the order of doubles as that of integers, reversed: negatives have their
+  // value bits flipped, then all bits are
+  const long long b = __double_as_longlong(v);
+  const int s = int(b >> 32) >> 31;
+  const int hi = ~(int(b >> 32) ^ (s & 0x7fffffff));
+  const unsigned lo = ~(unsigned(b & 0xffffffffll) ^ unsigned(s));
+  return argmax_key(hi, lo, max_i32(hi));
+}
+// largest |v| over the lanes, rounded down to 20 bits of mantissa
+__device__ __forceinline__ double max_abs_hi(double v) {
+  const int hi = max_i32(int(__double_as_longlong(v) >> 32) & 0x7fffffff);
+  return __longlong_as_double(static_cast<long long>(hi) << 32);
+}
+
 // value of lane k (k uniform across the wave)
 __device__ __forceinline__ float bcast(float v, int k) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
