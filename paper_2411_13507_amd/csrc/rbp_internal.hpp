@@ -26,8 +26,8 @@ struct LdsDims {
   int nf_cap;  // max faces
   int m_cap;   // max rows
   // byte offsets
-  int o_Hd, o_Af, o_ybuf, o_vec, o_scal, o_acte, o_lam, o_actid, o_actside, o_cst, o_region;
-  int o_Hf, o_Aff, o_rsc, o_vbuf, o_xb1, o_xb2, o_Kx;   // ADMM part of region (Kx over vbuf, xb1, xb2)
+  int o_Hd, o_Af, o_ru, o_ybuf, o_vec, o_scal, o_acte, o_lam, o_actid, o_actside, o_cst, o_region;
+  int o_Hf, o_Aff, o_vbuf, o_xb1, o_xb2, o_Kx;   // ADMM part of region (Kx over vbuf, xb1, xb2)
   int o_Q1, o_Ri;                                 // polish part of region
   int bytes;
 };

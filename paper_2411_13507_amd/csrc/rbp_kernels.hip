@@ -7,10 +7,18 @@
 namespace rbp {
 namespace {
 
+// Wavefronts per SIMD that the registers are budgeted for.  The solve is bound
+// by the latency of each wavefront's chain of small steps, so a third
+// wavefront pays as long as nothing spills: up to degree 7 (154 of the 168
+// registers; 50,000 degree-7 edges, forward + backward: 792 us with two, 667
+// us with three).  Degrees 8 and 9 and the iterations in FP64 would spill at 168.
+template <typename Real, int P>
+constexpr int kWavesPerSimd = sizeof(Real) == 4 && P <= 7 ? 3 : 2;
+
 // One launch per degree P: block b solves order[inst_base + b]; instances
 // are grouped by degree in the work order.
 template <typename Real, int P, bool kAdmm>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void solve_kernel(SolveArgs A) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWavesPerSimd<Real, P>))) void solve_kernel(SolveArgs A) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int b = blockIdx.x + A.inst_base;
   if (b >= A.N) return;
@@ -43,6 +51,7 @@ LdsDims make_dims(int pmax, int r_cap, int nf_cap, int real_bytes, bool admm) {
   auto take = [&](int bytes) { const int at = o; o += (bytes + 15) & ~15; return at; };
   d.o_Hd = take(d.r_cap * (d.nmax | 1) * 8);
   d.o_Af = take(d.nf_cap * 3 * 8);
+  d.o_ru = take(3 * d.r_cap * 8);   // bounds, constants, scalings
   d.o_ybuf = take(2 * d.ncol * 8);
   d.o_vec = take(5 * d.nmax * 8);   // vA..vE
   d.o_scal = take(16 * 8);
@@ -60,7 +69,6 @@ LdsDims make_dims(int pmax, int r_cap, int nf_cap, int real_bytes, bool admm) {
   if (admm) {
     d.o_Hf = take_r(d.nmax * hs * rb);
     d.o_Aff = take_r(d.nf_cap * 4 * rb);
-    d.o_rsc = take_r(d.r_cap * 8);
     // the matrix Kx is done with before the first iteration
     d.o_Kx = a;
     d.o_vbuf = take_r(d.m_cap * rb);
@@ -69,7 +77,7 @@ LdsDims make_dims(int pmax, int r_cap, int nf_cap, int real_bytes, bool admm) {
     const int kx_end = (d.o_Kx + d.nmax * d.nmax * rb + 15) & ~15;
     if (kx_end > a) a = kx_end;
   } else {
-    d.o_Hf = d.o_Aff = d.o_rsc = d.o_vbuf = d.o_xb1 = d.o_xb2 = d.o_Kx = d.o_region;   // unused
+    d.o_Hf = d.o_Aff = d.o_vbuf = d.o_xb1 = d.o_xb2 = d.o_Kx = d.o_region;   // unused
   }
   int b = d.o_region;
   auto take_p = [&](int bytes) { const int at = b; b += (bytes + 15) & ~15; return at; };
@@ -104,8 +112,8 @@ LdsDims make_back_dims(int pmax, int nf_cap) {
   d.o_cst = take(kMaxFree * kMaxFree * 8);
   d.o_Q1 = take(d.nmax * (d.nmax | 1) * 8);
   d.o_Ri = take(d.nmax * (d.nmax + 1) / 2 * 8);
-  d.o_acte = 0;
-  d.o_region = d.o_Hf = d.o_Aff = d.o_rsc = d.o_vbuf = d.o_xb1 = d.o_xb2 = d.o_Kx = 0;
+  d.o_acte = d.o_ru = 0;
+  d.o_region = d.o_Hf = d.o_Aff = d.o_vbuf = d.o_xb1 = d.o_xb2 = d.o_Kx = 0;
   d.bytes = o;
   return d;
 }

@@ -84,7 +84,7 @@ struct Lds {
   double *Hd, *Af, *ybuf, *qbuf, *vA, *vB, *vC, *vD, *vE, *scal, *acte, *actc, *lam;
   int *actid, *actside;
   Real *HfT, *Aff, *vbuf, *xb1, *xb2, *Kx;
-  double *rsc;                     // reachable-row scalings (ADMM set-up)
+  double *ru, *rcst, *rdn;         // reachable rows: bound, constant part, scaling 1 / |L^-1 a|
   double *Q1;
   double *cL1i;                    // staged degree table L1^-1
   double *Ri;                      // R^-1, upper triangle packed by columns: (i, j) at j (j + 1) / 2 + i
@@ -115,7 +115,9 @@ __device__ Lds<Real> carve(char* s, const LdsDims& D) {
   L.xb2 = (Real*)(s + D.o_xb2);
   L.Kx = (Real*)(s + D.o_Kx);
   L.Q1 = (double*)(s + D.o_Q1);
-  L.rsc = (double*)(s + D.o_rsc);
+  L.ru = (double*)(s + D.o_ru);
+  L.rcst = L.ru + D.r_cap;
+  L.rdn = L.rcst + D.r_cap;
   L.cL1i = (double*)(s + D.o_cst);
   L.Ri = (double*)(s + D.o_Ri);
   return L;
@@ -132,6 +134,14 @@ __device__ __forceinline__ int opaque(int x) {
   asm volatile("" : "+v"(x));
   return x;
 }
+__device__ __forceinline__ double opaque(double x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// The value of x, the same in every lane, in scalar registers (results of the
+// vector unit stay in vector registers otherwise, one per lane).
+__device__ __forceinline__ double uniform(double x) { return wave::bcast(x, 0); }
 
 // whitening: (L^-1 a)_i for var i = 3s + c, a given on the free vars in ``a``;
 // Li = rows of L1inv (stride kMaxFree, in LDS or constant memory; lower
@@ -281,6 +291,8 @@ __device__ __forceinline__ double dot_row(const double* x, const double* v) {
 #pragma unroll
     for (int u = 0; u < h; ++u)
       if (i0 + u < n) acc += a[u] * b[u];
+    acc = opaque(acc);
+    asm volatile("" ::: "memory");   // the next loads stay after this
   }
   return acc;
 }
@@ -377,11 +389,11 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   for (int e = 0; e < 6; ++e) { in.x0[e] = A.x0[6 * (int64_t)inst + e]; bad |= !isfinite(in.x0[e]); }
   double gl[3];
   for (int e = 0; e < 3; ++e) { gl[e] = A.goal[3 * (int64_t)inst + e]; bad |= !isfinite(gl[e]); }
-  for (int c = 0; c < 3; ++c) { in.P0[c] = in.x0[c]; in.dg[c] = gl[c] - in.x0[c]; }
-  in.T15 = in.T * sqrt(in.T);
-  in.iT3 = 1.0 / (in.T * in.T * in.T);
-  in.sv = double(P) / in.T;
-  in.sa = double(P) * (P - 1) / (in.T * in.T);
+  for (int c = 0; c < 3; ++c) { in.P0[c] = in.x0[c]; in.dg[c] = uniform(gl[c] - in.x0[c]); }
+  in.T15 = uniform(in.T * sqrt(in.T));
+  in.iT3 = uniform(1.0 / (in.T * in.T * in.T));
+  in.sv = uniform(double(P) / in.T);
+  in.sa = uniform(double(P) * (P - 1) / (in.T * in.T));
   const int nf = in.nf, r = in.r, F = in.F, RB = in.RB, m = in.m;
 
   auto finish_nan = [&](int status) {
@@ -397,22 +409,21 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
 
   // per-lane inputs of the row set-up, loaded ahead of the staging
   const double bj_in = lane < nf ? A.b_face[in.f0 + lane] : 0.0;
-  double h0_in[2] = {0.0, 0.0}, g_in[2][6], hp_in[2][6];
-#pragma unroll
-  for (int sl = 0; sl < 2; ++sl) {
-    const int l = lane + kWave * sl;
+  // right-hand side, its dependence on x0 and the coefficients on the pinned
+  // points (not kept in LDS) of reachable row l
+  struct RowIn { double h0, g[6], hp[6]; };
+  auto row_in = [&](int l) -> RowIn {
+    RowIn w;
     const bool on = l < r;
-    h0_in[sl] = on ? A.h0[in.r0 + l] : 0.0;
-#pragma unroll
-    for (int e = 0; e < 6; ++e) g_in[sl][e] = on ? A.G[6 * (in.r0 + l) + e] : 0.0;
-    // the row's coefficients on the pinned points (not kept in LDS)
+    w.h0 = on ? A.h0[in.r0 + l] : 0.0;
     const double* hp = A.H + in.hb + (int64_t)l * NC;
 #pragma unroll
-    for (int e = 0; e < 3; ++e) {
-      hp_in[sl][e] = on ? hp[e] : 0.0;
-      hp_in[sl][3 + e] = on ? hp[3 * P + e] : 0.0;
-    }
-  }
+    for (int e = 0; e < 6; ++e) w.g[e] = on ? A.G[6 * (in.r0 + l) + e] : 0.0;
+#pragma unroll
+    for (int e = 0; e < 6; ++e) w.hp[e] = on ? hp[e < 3 ? e : 3 * P + e - 3] : 0.0;
+    return w;
+  };
+  const RowIn row0 = row_in(lane);
 
   // debug option: poison the workgroup's LDS first, so that a read of a
   // value never written turns the outputs into NaN
@@ -482,34 +493,31 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   // P_p - P_0 by vmax T: beyond that the instance is infeasible
   if (lane < 3) fixed_viol |= fabs(sel3(lane, in.dg[0], in.dg[1], in.dg[2])) > in.vmax * in.T * (1.0 + 1e-12);
   // ---- reachable rows: lane l owns rows l and l + 64
-  double ru[2] = {0, 0}, rcst[2] = {0, 0}, rdn[2] = {0, 0};
-#pragma unroll
-  for (int sl = 0; sl < 2; ++sl) {
-    const int l = lane + kWave * sl;
+  auto set_row = [&](int l, const RowIn& w) {
     if (l < r) {
       const double* hr = L.Hd + l * HDS;
-      double b = h0_in[sl];
-      for (int e = 0; e < 6; ++e) b += g_in[sl][e] * in.x0[e];
-      const double* hp = hp_in[sl];
-      double s0 = hp[0], s1 = hp[1], s2 = hp[2];
+      double b = w.h0;
+      for (int e = 0; e < 6; ++e) b += w.g[e] * in.x0[e];
+      double s0 = w.hp[0], s1 = w.hp[1], s2 = w.hp[2];
       for (int k = 0; k < NFP; ++k) { s0 += hr[3 * k]; s1 += hr[3 * k + 1]; s2 += hr[3 * k + 2]; }
-      s0 += hp[3]; s1 += hp[4]; s2 += hp[5];
+      s0 += w.hp[3]; s1 += w.hp[4]; s2 += w.hp[5];
       b -= s0 * in.P0[0] + s1 * in.P0[1] + s2 * in.P0[2];
-      ru[sl] = b;
+      L.ru[l] = b;
       bad |= !isfinite(b);
-      rcst[sl] = hp[3] * in.dg[0] + hp[4] * in.dg[1] + hp[5] * in.dg[2];
+      L.rcst[l] = w.hp[3] * in.dg[0] + w.hp[4] * in.dg[1] + w.hp[5] * in.dg[2];
       double nn = 0.0;
       for (int c = 0; c < 3; ++c)
         for (int t = 0; t < NFP; ++t) {
-          double w = 0.0;
-          for (int t2 = 0; t2 <= t; ++t2) w += K.L1inv[t][t2] * hr[3 * t2 + c];
-          nn += w * w;
+          double w1 = 0.0;
+          for (int t2 = 0; t2 <= t; ++t2) w1 += K.L1inv[t][t2] * hr[3 * t2 + c];
+          nn += w1 * w1;
         }
       const double wn = in.T15 * sqrt(nn);
-      rdn[sl] = wn > 1e-300 ? 1.0 / wn : 0.0;
-      if constexpr (kAdmm) L.rsc[l] = rdn[sl];   // row scalings for the Gram below
+      L.rdn[l] = wn > 1e-300 ? 1.0 / wn : 0.0;
     }
-  }
+  };
+  set_row(lane, row0);
+  if (r > kWave) set_row(lane + kWave, row_in(lane + kWave));
   if (wany(bad)) { finish_nan(kInvalid); return; }
   if (wany(fixed_viol)) { finish_nan(kInfeasible); return; }
 
@@ -561,7 +569,7 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
         for (int t = 0; 2 * t < r; ++t) {
           const int l = 2 * t + half;
           float av = 0.0f;
-          if (l < r && col < N) av = float(L.rsc[l] * L.Hd[l * HDS + col]);
+          if (l < r && col < N) av = float(L.rdn[l] * L.Hd[l * HDS + col]);
           acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, av, acc, 0, 0, 0);
         }
 #pragma unroll
@@ -643,8 +651,8 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl) {
       const int l = lane + kWave * sl;
-      rr[sl] = Real(rdn[sl]);
-      rhi[sl] = (l < r) ? Real(rdn[sl] * (ru[sl] - rcst[sl])) : Real(kBigF);
+      rr[sl] = l < r ? Real(L.rdn[l]) : Real(0);
+      rhi[sl] = (l < r) ? Real(L.rdn[l] * (L.ru[l] - L.rcst[l])) : Real(kBigF);
       zr[sl] = 0; yr[sl] = 0;
     }
     auto upd = [&](Real& z, Real& y, Real zh, Real lo, Real hi) {
@@ -813,7 +821,7 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     bsync<kWS>();
     return fmin(0.5 * rt * rt, 3.0 * in.amax * in.amax * in.T * (1.0 + 1e-12));
   };
-  double Uw = box_bound();
+  const double Uw = uniform(box_bound());
 
   // --- owner helpers: key = 2*id + (side>0)
   auto slot_of = [&](int id_in, int& own_lane, int& bit) {   // id uniform
@@ -827,10 +835,11 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   // to vA), lanes i >= N get 0.  ``id`` is uniform.
   auto build_normal = [&](int id_in, int side) -> double {
     const int id = __builtin_amdgcn_readfirstlane(id_in);
+    const int ln = opaque(lane), t = ln / 3;
     double a = 0.0;
-    if (vl) {
-      a = double(side) * in.whitened(id, vs, vc, lane, L.cL1i, L.Af, L.Hd);
-      L.vA[lane] = a;
+    if (ln < N) {
+      a = double(side) * in.whitened(id, t, ln - 3 * t, ln, L.cL1i, L.Af, L.Hd);
+      L.vA[ln] = a;
     }
     bsync<kWS>();
     return a;
@@ -845,36 +854,38 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   // on nearly half of the steps here: face rows on neighbouring points are
   // close in the whitened metric).
   auto project = [&](double a_own, double aa, double& zz, double& z_own, double& r_own) {
-    double c_own = lane < q ? dot_row<N>(L.Q1 + lane * NS, L.vA) : 0.0;
-    if (lane < q) L.vC[lane] = c_own;
+    const int ln = opaque(lane);
+    double c_own = ln < q ? dot_row<N>(L.Q1 + ln * NS, L.vA) : 0.0;
+    if (ln < q) L.vC[ln] = c_own;
     bsync<kWS>();
-    z_own = vl ? colsub_q(a_own, L.Q1 + lane, NS, L.vC, q) : 0.0;
+    z_own = ln < N ? colsub_q(a_own, L.Q1 + ln, NS, L.vC, q) : 0.0;
     zz = wsum(z_own * z_own);
     if (zz < 1e-2 * aa && q > 0) {
-      if (vl) L.vB[lane] = z_own;
+      if (ln < N) L.vB[ln] = z_own;
       bsync<kWS>();
-      const double e_own = lane < q ? dot_row<N>(L.Q1 + lane * NS, L.vB) : 0.0;
-      if (lane < q) L.vE[lane] = e_own;
+      const double e_own = ln < q ? dot_row<N>(L.Q1 + ln * NS, L.vB) : 0.0;
+      if (ln < q) L.vE[ln] = e_own;
       bsync<kWS>();
-      z_own = vl ? colsub_q(z_own, L.Q1 + lane, NS, L.vE, q) : 0.0;
+      z_own = ln < N ? colsub_q(z_own, L.Q1 + ln, NS, L.vE, q) : 0.0;
       c_own += e_own;
-      if (lane < q) L.vC[lane] = c_own;
+      if (ln < q) L.vC[ln] = c_own;
       zz = wsum(z_own * z_own);
       bsync<kWS>();
     }
-    r_own = lane < q ? upper_times_q(L.Ri, L.vC, lane, q) : 0.0;
+    r_own = ln < q ? upper_times_q(L.Ri, L.vC, ln, q) : 0.0;
   };
 
   // append the projected direction as a new basis column: Q1 gets z / |z|,
   // R^-1 the column (-R^-1 c, 1) / |z|, with rv = R^-1 c on lanes < q, z_own =
   // z on lanes < N and inz = 1 / |z|
   auto append = [&](double inz, int id, int side, double e_full, double c_full, double rv, double z_own) {
-    if (vl) L.Q1[q * NS + lane] = z_own * inz;
-    if (lane <= q) L.Ri[q * (q + 1) / 2 + lane] = lane == q ? inz : -rv * inz;
-    if (lane == 0) { L.actid[q] = id; L.actside[q] = side; L.acte[q] = e_full; L.actc[q] = c_full; }
+    const int ln = opaque(lane);
+    if (ln < N) L.Q1[q * NS + ln] = z_own * inz;
+    if (ln <= q) L.Ri[q * (q + 1) / 2 + ln] = ln == q ? inz : -rv * inz;
+    if (ln == 0) { L.actid[q] = id; L.actside[q] = side; L.acte[q] = e_full; L.actc[q] = c_full; }
     int ol, bit;
     slot_of(id, ol, bit);
-    if (lane == ol) act_bits |= (1u << bit);
+    if (ln == ol) act_bits |= (1u << bit);
     ++q;
     bsync<kWS>();
   };
@@ -995,10 +1006,9 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
           sc_d = -1.0f;
           L.scal[0] = side > 0 ? dbd : -dlo_of(dbd);  // side*bound: u = dbd and -l
           L.scal[1] = double(side) * dcst;
-        } else if (bit == NFP + 1) {
-          sc_r[0] = -1.0f; L.scal[0] = ru[0]; L.scal[1] = rcst[0];
         } else {
-          sc_r[1] = -1.0f; L.scal[0] = ru[1]; L.scal[1] = rcst[1];
+          if (bit == NFP + 1) sc_r[0] = -1.0f; else sc_r[1] = -1.0f;
+          L.scal[0] = L.ru[id - RB]; L.scal[1] = L.rcst[id - RB];
         }
       }
     }
@@ -1033,46 +1043,52 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   // violated inactive row as (score, key), with the violation side * value -
   // e_full, the row's e_full and c_full and its scaling 1 / |L^-1 a|, which the
   // owning lane hands to the others afterwards (no second evaluation).  The
-  // free entries of the point are uniform; they are loaded half at a time,
+  // free entries of the point are uniform; they are loaded a third at a time,
   // together with the lane's reachable-row coefficients, before any of them is
   // used (the pinned entries of y~ are 0 at P_0 and the goal offset, whose
   // product with a reachable row is the constant rcst).
   // kLast: no candidates; the largest excess over the bounds and the largest
   // magnitude of values and bounds instead.
-  constexpr int HP = (NFP + 1) / 2;              // interior points per half
+  constexpr int HP = (NFP + 2) / 3;              // interior points at a time
   auto eval_rows = [&](auto last, double& best, int& key, double& sv_b, double& e_b, double& c_b, double& d_b,
                        double& pres, double& pscale) {
     constexpr bool kLast = decltype(last)::value;
-    const int ln = opaque(lane);   // addresses formed here, not held across the loop
+    // addresses and products of per-lane constants are formed here, not held
+    // in registers across the loop
+    const int ln = opaque(lane);
+    const double fuo = opaque(fu), ifo = opaque(ifan), dbo = opaque(dbd);
     best = -1.0; key = 0x7fffffff; sv_b = 0.0; e_b = 0.0; c_b = 0.0; d_b = 0.0;
     pres = 0.0; pscale = 0.0;
     // difference rows: lane-dependent entries, branch-free (a velocity lane
     // reads its first entry twice and gives it weight 0)
     const int di0 = 3 * dk + dc, di1 = di0 + 3, di2 = dvel ? di0 : di0 + 6;
     const double yd0 = dl ? L.ybuf[di0] : 0.0, yd1 = dl ? L.ybuf[di1] : 0.0, yd2 = dl ? L.ybuf[di2] : 0.0;
-    // reachable row ``lane`` (row 0 stands in on lanes without one)
+    // reachable row ``lane`` and ``lane`` + 64 (row 0 stands in on lanes without one)
     const double* hr = L.Hd + (ln < r ? ln : 0) * HDS;
     const double* hr2 = L.Hd + (ln + kWave < r ? ln + kWave : 0) * HDS;
     double acc = 0.0, acc2 = 0.0;
+    const double* af = L.Af + 3 * (ln < nf ? ln : 0);
+    const double a0 = af[0], a1 = af[1], a2 = af[2];
 #pragma unroll
     for (int s0 = 0; s0 < NFP; s0 += HP) {
       double y[3 * HP], hv[3 * HP];
 #pragma unroll
       for (int i = 0; i < 3 * HP; ++i)
         if (3 * s0 + i < N) { y[i] = L.ybuf[3 + 3 * s0 + i]; hv[i] = hr[3 * s0 + i]; }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < HP; ++u) {
         const int s = s0 + u;
         if (s < NFP && fl) {
-          const double v = fa0 * y[3 * u] + fa1 * y[3 * u + 1] + fa2 * y[3 * u + 2];
-          const double viol = v - fu;
+          const double v = a0 * y[3 * u] + a1 * y[3 * u + 1] + a2 * y[3 * u + 2];
+          const double viol = v - fuo;
           if constexpr (kLast) {
             pres = fmax(pres, viol);
-            pscale = fmax(pscale, fmax(fabs(v), fabs(fu)));
-          } else if (!((act_bits >> s) & 1u) && viol > ftol * (1.0 + fabs(fu))) {
-            const double dn = ifan * K.rkappa[s];
+            pscale = fmax(pscale, fmax(fabs(v), fabs(fuo)));
+          } else if (!((act_bits >> s) & 1u) && viol > ftol * (1.0 + fabs(fuo))) {
+            const double dn = ifo * K.rkappa[s];
             const double sc = viol * dn;
-            if (sc > best) { best = sc; key = 2 * (s * nf + lane) + 1; sv_b = viol; e_b = fu; c_b = 0.0; d_b = dn; }
+            if (sc > best) { best = sc; key = 2 * (s * nf + ln) + 1; sv_b = viol; e_b = fuo; c_b = 0.0; d_b = dn; }
           }
         }
       }
@@ -1087,33 +1103,35 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
         for (int i = 0; i < 3 * HP; ++i)
           if (3 * s0 + i < N) acc2 += hv[i] * y[i];
       }
+      acc = opaque(acc);   // formed here (not where it is used, with every operand held until then)
     }
     if (dl) {
-      const double v = dvel ? dsc * (yd1 - yd0) : dsc * (yd2 - 2.0 * yd1 + yd0);
-      const double vu = v - dbd, vlo = dlo_of(dbd) - v;
+      const double v = dvel ? in.sv * (yd1 - yd0) : in.sa * (yd2 - 2.0 * yd1 + yd0);
+      const double vu = v - dbo, vlo = dlo_of(dbo) - v;
       if constexpr (kLast) {
         pres = fmax(pres, fmax(vu, vlo));
-        pscale = fmax(pscale, fmax(fabs(v), fabs(dbd)));
+        pscale = fmax(pscale, fmax(fabs(v), fabs(dbo)));
       } else if (!((act_bits >> NFP) & 1u)) {
-        const double dtol = ftol * (1.0 + fabs(dbd));
+        const double dtol = ftol * (1.0 + fabs(dbo));
         if (vu > dtol && vu * ddn > best) {
-          best = vu * ddn; key = 2 * (F + lane) + 1; sv_b = vu; e_b = dbd; c_b = dcst; d_b = ddn;
+          best = vu * ddn; key = 2 * (F + ln) + 1; sv_b = vu; e_b = dbo; c_b = dcst; d_b = ddn;
         }
         if (vlo > dtol && vlo * ddn > best) {
-          best = vlo * ddn; key = 2 * (F + lane); sv_b = vlo; e_b = -dlo_of(dbd); c_b = -dcst; d_b = ddn;
+          best = vlo * ddn; key = 2 * (F + ln); sv_b = vlo; e_b = -dlo_of(dbo); c_b = -dcst; d_b = ddn;
         }
       }
     }
     auto reach_row = [&](int sl, double a) {
-      const int l = lane + kWave * sl;
-      const double v = a + rcst[sl];
-      const double viol = v - ru[sl];
+      const int l = ln + kWave * sl;
+      const double rc = L.rcst[l], rb = L.ru[l], rd = L.rdn[l];
+      const double v = a + rc;
+      const double viol = v - rb;
       if constexpr (kLast) {
         pres = fmax(pres, viol);
-        pscale = fmax(pscale, fmax(fabs(v), fabs(ru[sl])));
-      } else if (!((act_bits >> (NFP + 1 + sl)) & 1u) && viol > ftol * (1.0 + fabs(ru[sl]))) {
-        const double sc = rdn[sl] > 0.0 ? viol * rdn[sl] : __builtin_huge_val();
-        if (sc > best) { best = sc; key = 2 * (RB + l) + 1; sv_b = viol; e_b = ru[sl]; c_b = rcst[sl]; d_b = rdn[sl]; }
+        pscale = fmax(pscale, fmax(fabs(v), fabs(rb)));
+      } else if (!((act_bits >> (NFP + 1 + sl)) & 1u) && viol > ftol * (1.0 + fabs(rb))) {
+        const double sc = rd > 0.0 ? viol * rd : __builtin_huge_val();
+        if (sc > best) { best = sc; key = 2 * (RB + l) + 1; sv_b = viol; e_b = rb; c_b = rc; d_b = rd; }
       }
     };
     if (lane < r) reach_row(0, acc);
@@ -1181,7 +1199,7 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     double splus = wave::bcast(sv_b, owner);
     const double e_full = wave::bcast(e_b, owner), c_full = wave::bcast(c_b, owner);
     const double dn = wave::bcast(d_b, owner);
-    const double aa = dn > 0.0 ? div_nr(1.0, dn * dn) : 0.0;
+    const double aa = uniform(dn > 0.0 ? div_nr(1.0, dn * dn) : 0.0);
     const double a_own = build_normal(id, side);
     double lamp = 0.0;
     bool added = false;
