@@ -496,7 +496,7 @@ int rbp_adjacent_hyperplanes(int32_t n_nodes, const double* X, int32_t n_obstacl
  * hyperplanes of the reference nodes (rbp_adjacent_hyperplanes): one SQP
  * iteration, as in Sec. IV.
  *
- * Solver: one wavefront per instance, primal-dual interior point in FP64
+ * Solver: one workgroup per instance, primal-dual interior point in FP64
  * with Riccati-structured Newton systems.  Instances are independent.
  */
 #define RBP_MPC_MAX_HORIZON 64

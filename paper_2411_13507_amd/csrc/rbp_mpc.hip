@@ -1,5 +1,5 @@
-// Batched MPC refinement QP (eq. MPC, Sec. III-D): one 64-lane wave per
-// instance, primal-dual interior point (Mehrotra predictor-corrector), FP64.
+// Batched MPC refinement QP (eq. MPC, Sec. III-D): one workgroup of four
+// wavefronts per instance, primal-dual interior point (Mehrotra predictor-corrector), FP64.
 //
 // Stage variables z_k = (x_k, u_k), k = 0..N-1, with x = (position, velocity)
 // and u = acceleration; x_{k+1} = A x_k + B u_k is the exact discretisation of
@@ -37,6 +37,9 @@ namespace rbp {
 namespace {
 
 constexpr int kW = 64;
+constexpr int kWaves = 4;              // wavefronts per instance
+constexpr int kT = kW * kWaves;
+constexpr int kRing = 6;               // stages of barrier Hessians per batch of the factorisation
 constexpr int kSolved = 0, kInfeasible = 1, kMaxIter = 2, kNumerical = 4, kInvalid = 5;
 
 // LDS carve, in doubles.  The per-row state (slack, multiplier, primal
@@ -50,6 +53,9 @@ struct MpcSm {
   double *prm, *z, *g, *dz, *ref, *pl, *X, *Lc, *Y, *yv, *rho, *P, *tmp;
   // scratch of the factorisation, inside the gradient buffer (free while it runs)
   double *Ht, *Qh, *HtT;
+  double *ring;   // 2 x kRing x 45: barrier Hessians of the stages ahead (upper triangles)
+  double *part;   // 64: running sums handed from wavefront to wavefront
+  double *red;    // 4 per reduction in flight: one value per wavefront
 };
 
 // the gradient / direction buffer also holds the factorisation's scratch
@@ -60,7 +66,8 @@ __host__ __device__ inline int mpc_lds_doubles(int N, int m) {
   const MpcLayout L = mpc_param_layout(m);
   const int RT = N * (m + 4);
   return L.total + 9 * N /*z*/ + mpc_g_doubles(N) /*g = dz*/ + 6 * (N + 1) /*ref*/ + 4 * N /*pl*/ +
-         RT /*X*/ + 6 * N /*Lc*/ + 18 * N /*Y*/ + 3 * N /*yv*/ + 3 * N /*rho*/ + 36 /*P*/ + 16 /*tmp*/;
+         RT /*X*/ + 6 * N /*Lc*/ + 18 * N /*Y*/ + 3 * N /*yv*/ + 3 * N /*rho*/ + 36 /*P*/ + 12 /*tmp*/ +
+         2 * kRing * 45 /*ring*/ + kW /*part*/ + 2 * kWaves /*red*/;
 }
 
 __device__ inline MpcSm carve_mpc(double* base, int N, int m) {
@@ -81,12 +88,23 @@ __device__ inline MpcSm carve_mpc(double* base, int N, int m) {
   S.yv = p; p += 3 * N;
   S.rho = p; p += 3 * N;
   S.P = p; p += 36;
-  S.tmp = p;
+  S.tmp = p; p += 12;
+  S.ring = p; p += 2 * kRing * 45;
+  S.part = p; p += kW;
+  S.red = p;
   return S;
 }
 
 // tmp layout: [0, 6) start state, [8] factorisation flag
 constexpr int kTmpFlag = 8;
+
+// The value of x, opaque to the optimiser: what is derived from it (addresses,
+// indices) is formed where it is used, instead of being hoisted out of the
+// iteration loop and held in registers throughout.
+__device__ __forceinline__ int opq(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
 
 // Column b of [A B] (6 x 9) has at most two non-zeros: row q0 with weight w0
 // and row q1 with weight w1 (q1 < 0: none).
@@ -115,25 +133,111 @@ __device__ inline double div_nr(double a, double b) {
   return fma(fma(-b, q, a), r, q);
 }
 
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ double uni(double x) { return wave::bcast(x, 0); }
+
 struct MpcCtx {
   const MpcArgs& A;
   MpcSm S;
   MpcLayout Ly;
-  int N, m, mr, RT, lane;
+  int N, m, mr, RT, lane, wv, tid;
   double dt;
   int ua, ub;          // upper-triangle entry (ua <= ub) of a 9 x 9 matrix owned by lanes < 45
+  int spw;             // passes of reachable rows per wavefront
+  double h2, a11, a12, a22, det;   // dt^2 / 2; normal equations of the terminal costate (the same every time)
+  int pa, pb;          // upper-triangle entry (pa <= pb) of the 6 x 6 cost-to-go owned by lanes < 21
+  int pidx[4];         // entries of the cost-to-go in entry (ua, ub) of [A B]' P [A B], and their weights
+  double pw[4];
+
+  __device__ __forceinline__ void init_lane() {
+    h2 = uni(0.5 * dt * dt);
+    double s11 = 0.0, s12 = 0.0;
+    for (int k = 0; k < N; ++k) {
+      const double al = dt * dt * (N - k - 0.5);
+      s11 += al * al;
+      s12 += dt * al;
+    }
+    a11 = uni(s11);
+    a12 = uni(s12);
+    a22 = uni(N * dt * dt);
+    det = uni(a11 * a22 - a12 * a12);
+    ua = 0;
+    int t = lane < 45 ? lane : 0;
+    while (t >= 9 - ua) { t -= 9 - ua; ++ua; }
+    ub = ua + t;
+    pa = 0;
+    t = lane < 21 ? lane : 0;
+    while (t >= 6 - pa) { t -= 6 - pa; ++pa; }
+    pb = pa + t;
+    int qa[2], qb[2];
+    double wa[2], wb[2];
+    ab_col(ua, dt, qa[0], wa[0], qa[1], wa[1]);
+    ab_col(ub, dt, qb[0], wb[0], qb[1], wb[1]);
+    if (qa[1] < 0) qa[1] = qa[0];
+    if (qb[1] < 0) qb[1] = qb[0];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int lo = qa[i] < qb[j] ? qa[i] : qb[j], hi = qa[i] < qb[j] ? qb[j] : qa[i];
+        pidx[2 * i + j] = 6 * lo + hi;
+        pw[2 * i + j] = wa[i] * wb[j];
+      }
+  }
+
+  // orders LDS accesses between the lanes of this wavefront only (its LDS
+  // operations execute in program order)
+  __device__ __forceinline__ void wsync() const {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  }
+  // largest / smallest value over the instance's wavefronts
+  __device__ __forceinline__ double bmax(double v) const {
+    v = wave::max(v);
+    if (lane == 0) S.red[wv] = v;
+    __syncthreads();
+    v = fmax(fmax(S.red[0], S.red[1]), fmax(S.red[2], S.red[3]));
+    __syncthreads();
+    return uni(v);
+  }
+  __device__ __forceinline__ double bmin(double v) const { return -bmax(-v); }
+  __device__ __forceinline__ void bmax2(double& a, double& b) const {
+    a = wave::max(a);
+    b = wave::max(b);
+    if (lane == 0) { S.red[wv] = a; S.red[kWaves + wv] = b; }
+    __syncthreads();
+    a = fmax(fmax(S.red[0], S.red[1]), fmax(S.red[2], S.red[3]));
+    b = fmax(fmax(S.red[4], S.red[5]), fmax(S.red[6], S.red[7]));
+    __syncthreads();
+  }
+  // Sum over the rows: add(acc) continues a lane's running sum over the rows
+  // its wavefront holds, in order; the wavefronts take turns, so that the
+  // order is that of one wavefront walking every slot (how far an unsolvable
+  // horizon gets depends on the last bits of these sums).
+  template <typename F>
+  __device__ __forceinline__ double chain_sum(F&& add) const {
+    for (int w = 0; w < kWaves; ++w) {
+      if (wv == w) S.part[lane] = add(w == 0 ? 0.0 : S.part[lane]);
+      __syncthreads();
+    }
+    const double v = wave::sum(S.part[lane]);
+    __syncthreads();
+    return uni(v);
+  }
 
   // component a of C_k' w for per-row weights w (rows of stage k at w[0..mr))
   __device__ __forceinline__ double ct_times(int k, int a, const double* w) const {
     const double* c = S.prm + Ly.Cr + a * Ly.cs;
     double t = 0.0, t1 = 0.0;
     int i = 0;
-    for (; i + 8 <= m; i += 8) {         // loads of eight rows issued together
-      double x[8], y[8];
+    const int m8 = m & ~7;
+    for (; i < m8; i += 4) {             // loads of four rows issued together
+      double x[4], y[4];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) { x[q] = c[i + q]; y[q] = w[i + q]; }
+      for (int q = 0; q < 4; ++q) { x[q] = c[i + q]; y[q] = w[i + q]; }
 #pragma unroll
-      for (int q = 0; q < 8; q += 2) {
+      for (int q = 0; q < 4; q += 2) {
         t += x[q] * y[q];
         t1 += x[q + 1] * y[q + 1];
       }
@@ -156,32 +260,32 @@ struct MpcCtx {
   // upper entry (ua, ub) of Ht_k = H_k + sum_i sigma_i c_i c_i', with the
   // barrier weights sigma of stage k's rows in S.X
   __device__ __forceinline__ double ht_entry(int k) const {
+    const int ua = opq(this->ua), ub = opq(this->ub);
     const double* sg = S.X + k * mr;
     const double* ca = S.prm + Ly.Cr + ua * Ly.cs;
     const double* cb = S.prm + Ly.Cr + ub * Ly.cs;
-    // the operands outside the row loop are loaded first, so they are in
-    // flight together with the first rows
-    const double* fa = S.prm + Ly.pf + ua / 3;
-    const double* fb = S.prm + Ly.pf + ub / 3;
-    const double hv = Hk(k)[9 * ua + ub];
-    const double s0 = sg[m], s1 = sg[m + 1], s2 = sg[m + 2], s3 = sg[m + 3];
-    const double fa0 = fa[0], fa3 = fa[3], fa6 = fa[6], fa9 = fa[9];
-    const double fb0 = fb[0], fb3 = fb[3], fb6 = fb[6], fb9 = fb[9];
-    const double pla = S.pl[4 * k + ua % 3], plb = S.pl[4 * k + ub % 3];
-    double v = hv, v1 = 0.0;
+    double v = Hk(k)[9 * ua + ub], v1 = 0.0;
     int i = 0;
-    for (; i + 8 <= m; i += 8) {         // loads of eight rows issued together
-      double w[8], x[8], y[8];
+    const int m8 = m & ~7;
+    for (; i < m8; i += 4) {             // loads of four rows issued together
+      double w[4], x[4], y[4];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) { w[q] = sg[i + q]; x[q] = ca[i + q]; y[q] = cb[i + q]; }
+      for (int q = 0; q < 4; ++q) { w[q] = sg[i + q]; x[q] = ca[i + q]; y[q] = cb[i + q]; }
 #pragma unroll
-      for (int q = 0; q < 8; q += 2) {
+      for (int q = 0; q < 4; q += 2) {
         v += w[q] * x[q] * y[q];
         v1 += w[q + 1] * x[q + 1] * y[q + 1];
       }
     }
     for (; i < m; ++i) v += sg[i] * ca[i] * cb[i];
     v += v1;
+    asm volatile("" : "+v"(v) : : "memory");   // the plane rows' operands are not held across the rows
+    const double* fa = S.prm + Ly.pf + ua / 3;
+    const double* fb = S.prm + Ly.pf + ub / 3;
+    const double s0 = sg[m], s1 = sg[m + 1], s2 = sg[m + 2], s3 = sg[m + 3];
+    const double fa0 = fa[0], fa3 = fa[3], fa6 = fa[6], fa9 = fa[9];
+    const double fb0 = fb[0], fb3 = fb[3], fb6 = fb[6], fb9 = fb[9];
+    const double pla = S.pl[4 * k + ua % 3], plb = S.pl[4 * k + ub % 3];
     const double tp = s0 * fa0 * fb0 + s1 * fa3 * fb3 + s2 * fa6 * fb6 + s3 * fa9 * fb9;
     return v + pla * plb * tp;
   }
@@ -190,18 +294,49 @@ struct MpcCtx {
   // (zero weights: H_k alone).  Returns false (uniformly) when a pivot of
   // some Quu is not positive.
   __device__ __forceinline__ bool factor() {
-    if (lane == 0) S.tmp[kTmpFlag] = 0.0;
-    // terminal block: P = T2' Ht_{N-2} T2 + T1' Ht_{N-1} T1
+    // The barrier Hessians do not depend on the recursion: they are formed
+    // kRing stages at a time, the first batch by every wavefront, each next one
+    // by wavefronts 1..3 while wavefront 0 runs the recursion over the batch
+    // before it.
+    auto batch = [&](int b, int first) {       // stages N-1 - kRing b, going down
+      for (int u = wv - first; u < kRing; u += kWaves - first) {
+        const int k = N - 1 - (kRing * b + u);
+        if (u >= 0 && k >= 0 && lane < 45) S.ring[((b & 1) * kRing + u) * 45 + lane] = ht_entry(k);
+      }
+    };
+    if (tid == 0) S.tmp[kTmpFlag] = 0.0;
+    batch(0, 0);
+    __syncthreads();
+    const int nb = (N + kRing - 1) / kRing;
+    for (int b = 0; b < nb; ++b) {
+      if (wv == 0) {
+        const double* ring = S.ring + (b & 1) * kRing * 45;
+        if (b == 0) terminal(ring);
+        for (int u = b == 0 ? 2 : 0; u < kRing; ++u) {
+          const int k = N - 1 - (kRing * b + u);
+          if (k < 0) break;
+          stage(k, ring + u * 45);
+        }
+      } else if (b + 1 < nb) {
+        batch(b + 1, 1);
+      }
+      __syncthreads();
+    }
+    return S.tmp[kTmpFlag] == 0.0;
+  }
+
+  // terminal block (wavefront 0): P = T2' Ht_{N-2} T2 + T1' Ht_{N-1} T1
+  __device__ __forceinline__ void terminal(const double* ring) {
+    const int lane = opq(this->lane), ua = opq(this->ua), ub = opq(this->ub);
     for (int e = lane; e < 36; e += kW) S.P[e] = 0.0;
     for (int t = 0; t < 2; ++t) {
-      const int k = N - 2 + t;
       const double* T = S.prm + (t == 0 ? Ly.T2 : Ly.T1);
       if (lane < 45) {
-        const double v = ht_entry(k);
+        const double v = ring[(1 - t) * 45 + lane];
         S.Ht[9 * ua + ub] = v;
         S.Ht[9 * ub + ua] = v;
       }
-      __syncthreads();
+      wsync();
       // Ht T (9 x 6)
       for (int e = lane; e < 54; e += kW) {
         const int a = e / 6, c = e - 6 * (e / 6);
@@ -209,14 +344,14 @@ struct MpcCtx {
         for (int b = 0; b < 9; ++b) v += S.Ht[9 * a + b] * T[6 * b + c];
         S.HtT[e] = v;
       }
-      __syncthreads();
+      wsync();
       for (int e = lane; e < 36; e += kW) {
         const int c = e / 6, d = e - 6 * (e / 6);
         double v = 0.0;
         for (int a = 0; a < 9; ++a) v += T[6 * a + c] * S.HtT[6 * a + d];
         S.P[e] += v;
       }
-      __syncthreads();
+      wsync();
     }
     for (int e = lane; e < 36; e += kW) {
       const int a = e / 6, b = e - 6 * (e / 6);
@@ -225,210 +360,259 @@ struct MpcCtx {
         S.P[e] = v; S.P[6 * b + a] = v;
       }
     }
-    __syncthreads();
-    for (int k = N - 3; k >= 0; --k) {
-      // Qh = Ht + [A B]' P [A B] (symmetric: lanes own the upper triangle)
-      if (lane < 45) {
-        int qa0, qa1, qb0, qb1;
-        double wa0, wa1, wb0, wb1;
-        ab_col(ua, dt, qa0, wa0, qa1, wa1);
-        ab_col(ub, dt, qb0, wb0, qb1, wb1);
-        // absent second terms have weight 0 (ab_col): their loads use a
-        // valid entry instead of a branch, so all four are issued together
-        const int qa1c = qa1 >= 0 ? qa1 : qa0, qb1c = qb1 >= 0 ? qb1 : qb0;
-        const double p00 = S.P[6 * qa0 + qb0], p01 = S.P[6 * qa0 + qb1c];
-        const double p10 = S.P[6 * qa1c + qb0], p11 = S.P[6 * qa1c + qb1c];
-        double v = wa0 * wb0 * p00;
-        v += wa0 * wb1 * p01;
-        v += wa1 * wb0 * p10;
-        v += wa1 * wb1 * p11;
-        v += ht_entry(k);
-        S.Qh[9 * ua + ub] = v;
-        S.Qh[9 * ub + ua] = v;
-      }
-      __syncthreads();
-      // Quu = L L' and the columns of Y = L^-1 Qux that entry (a, b) of the
-      // next cost-to-go P = Qxx - Y'Y needs, all in the lane of that entry
-      // (lanes < 21); lanes 0..5 (entries (0, c)) store column c of Y, lane 0
-      // stores L as (1/l00, l10, 1/l11, l20, l21, 1/l22).
-      if (lane < 21) {
-        int a = 0, t = lane;
-        while (t >= 6 - a) { t -= 6 - a; ++a; }
-        const int b = a + t;
-        // every entry this lane reads, loaded before the pivot chain starts
-        const double q60 = S.Qh[60], q69 = S.Qh[69], q78 = S.Qh[78], q70 = S.Qh[70], q79 = S.Qh[79],
-                     q80 = S.Qh[80];
-        const double qa0 = S.Qh[54 + a], qa1 = S.Qh[63 + a], qa2 = S.Qh[72 + a];
-        const double qb0 = S.Qh[54 + b], qb1 = S.Qh[63 + b], qb2 = S.Qh[72 + b];
-        const double qab = S.Qh[9 * a + b];
-        const double d0 = q60;
-        const double i00 = rsqrt_nr(d0);
-        const double l10 = q69 * i00, l20 = q78 * i00;
-        const double d1 = q70 - l10 * l10;
-        const double i11 = rsqrt_nr(d1);
-        const double l21 = (q79 - l20 * l10) * i11;
-        const double d2 = q80 - l20 * l20 - l21 * l21;
-        const double i22 = rsqrt_nr(d2);
-        const double ya0 = qa0 * i00;
-        const double ya1 = (qa1 - l10 * ya0) * i11;
-        const double ya2 = (qa2 - l20 * ya0 - l21 * ya1) * i22;
-        const double yb0 = qb0 * i00;
-        const double yb1 = (qb1 - l10 * yb0) * i11;
-        const double yb2 = (qb2 - l20 * yb0 - l21 * yb1) * i22;
-        if (lane < 6) {
-          double* Y = S.Y + 18 * k;
-          Y[b] = yb0; Y[6 + b] = yb1; Y[12 + b] = yb2;
-        }
-        if (lane == 0) {
-          double* L = S.Lc + 6 * k;
-          L[0] = i00; L[1] = l10; L[2] = i11; L[3] = l20; L[4] = l21; L[5] = i22;
-          if (!(d0 > 0.0 && d1 > 0.0 && d2 > 0.0) || !isfinite(i00 * i11 * i22)) S.tmp[kTmpFlag] = 1.0;
-        }
-        if (k > 0) {
-          const double v = qab - (ya0 * yb0 + ya1 * yb1 + ya2 * yb2);
-          S.P[6 * a + b] = v;
-          S.P[6 * b + a] = v;
-        }
-      }
-      __syncthreads();
+    wsync();
+  }
+
+  // one stage of the recursion (wavefront 0), with the stage's barrier Hessian
+  __device__ __forceinline__ void stage(int k, const double* ht) {
+    const int lane = opq(this->lane), pa = opq(this->pa), pb = opq(this->pb), ua = opq(this->ua), ub = opq(this->ub);
+    // Qh = Ht + [A B]' P [A B] (symmetric: lanes own the upper triangle; the
+    // four entries of P and their weights are the lane's own, see pidx, pw;
+    // absent terms have weight 0 and load a valid entry)
+    double vq = 0.0;
+    if (lane < 45) {
+      const double p00 = S.P[pidx[0]], p01 = S.P[pidx[1]], p10 = S.P[pidx[2]], p11 = S.P[pidx[3]];
+      const double h = ht[lane];
+      double v = pw[0] * p00;
+      v += pw[1] * p01;
+      v += pw[2] * p10;
+      v += pw[3] * p11;
+      v += h;
+      vq = v;
+      S.Qh[ub >= 6 ? 9 * ub + ua : 9 * ua + ub] = v;   // where it is read below
     }
-    return S.tmp[kTmpFlag] == 0.0;
+    // the entries of Quu come straight from their lanes (39..44), so that the
+    // pivots do not wait for the other entries' way through LDS
+    const double q60 = wave::bcast(vq, 39), q69 = wave::bcast(vq, 40), q78 = wave::bcast(vq, 41),
+                 q70 = wave::bcast(vq, 42), q79 = wave::bcast(vq, 43), q80 = wave::bcast(vq, 44);
+    wsync();
+    // Quu = L L' and the columns of Y = L^-1 Qux that entry (a, b) of the
+    // next cost-to-go P = Qxx - Y'Y needs, all in the lane of that entry
+    // (lanes < 21); lanes 0..5 (entries (0, c)) store column c of Y, lane 0
+    // stores L as (1/l00, l10, 1/l11, l20, l21, 1/l22).
+    if (lane < 21) {
+      const int a = pa, b = pb;
+      // every entry this lane reads, loaded before the pivot chain starts
+      const double qa0 = S.Qh[54 + a], qa1 = S.Qh[63 + a], qa2 = S.Qh[72 + a];
+      const double qb0 = S.Qh[54 + b], qb1 = S.Qh[63 + b], qb2 = S.Qh[72 + b];
+      const double qab = S.Qh[9 * a + b];
+      const double d0 = q60;
+      const double i00 = rsqrt_nr(d0);
+      const double l10 = q69 * i00, l20 = q78 * i00;
+      const double d1 = q70 - l10 * l10;
+      const double i11 = rsqrt_nr(d1);
+      const double l21 = (q79 - l20 * l10) * i11;
+      const double d2 = q80 - l20 * l20 - l21 * l21;
+      const double i22 = rsqrt_nr(d2);
+      const double ya0 = qa0 * i00;
+      const double ya1 = (qa1 - l10 * ya0) * i11;
+      const double ya2 = (qa2 - l20 * ya0 - l21 * ya1) * i22;
+      const double yb0 = qb0 * i00;
+      const double yb1 = (qb1 - l10 * yb0) * i11;
+      const double yb2 = (qb2 - l20 * yb0 - l21 * yb1) * i22;
+      if (lane < 6) {
+        double* Y = S.Y + 18 * k;
+        Y[b] = yb0; Y[6 + b] = yb1; Y[12 + b] = yb2;
+      }
+      if (lane == 0) {
+        double* L = S.Lc + 6 * k;
+        L[0] = i00; L[1] = l10; L[2] = i11; L[3] = l20; L[4] = l21; L[5] = i22;
+        if (!(d0 > 0.0 && d1 > 0.0 && d2 > 0.0) || !isfinite(i00 * i11 * i22)) S.tmp[kTmpFlag] = 1.0;
+      }
+      if (k > 0) {
+        S.P[6 * a + b] = qab - (ya0 * yb0 + ya1 * yb1 + ya2 * yb2);   // a <= b: the upper triangle is read
+      }
+    }
+    wsync();
   }
 
   // Solve the factorised LQ for the gradients in S.g; the direction replaces
   // them (S.dz aliases S.g: the backward sweep reads every g_k before the
-  // forward sweep writes dz_k).  Sequential over stages in lane 0.
+  // forward sweep writes dz_k).  Sequential over stages in wavefront 0, each
+  // stage's operands loaded while the stage before it is worked on.
   __device__ __forceinline__ void lq_solve() {
-    const double* T2 = S.prm + Ly.T2;
-    const double* T1 = S.prm + Ly.T1;
-    const double h2 = 0.5 * dt * dt;
-    // backward sweep, one costate component per lane: lane c < 6 holds p_c;
-    // the u-part of [A B]'p needs p_{c+3} and the x-part p_{c-3}, both a DPP
-    // row shift by three lanes away, and y = L^-1 qu takes qu from lanes 0..2
-    {
-      const int c = lane < 6 ? lane : 5;
-      const int cu = lane < 3 ? lane : 2;
-      double pc = 0.0;
-      for (int a = 0; a < 9; ++a) pc += T2[6 * a + c] * S.g[9 * (N - 2) + a] + T1[6 * a + c] * S.g[9 * (N - 1) + a];
-      for (int k = N - 3; k >= 0; --k) {
-        const double gx = S.g[9 * k + c], gu = S.g[9 * k + 6 + cu];
-        const double Y0 = S.Y[18 * k + c], Y1 = S.Y[18 * k + 6 + c], Y2 = S.Y[18 * k + 12 + c];
-        double L[6];
+    if (wv == 0) {
+      const int lane = opq(this->lane);
+      const double* T2 = S.prm + Ly.T2;
+      const double* T1 = S.prm + Ly.T1;
+      // backward sweep, one costate component per lane: lane c < 6 holds p_c;
+      // the u-part of [A B]'p needs p_{c+3} and the x-part p_{c-3}, both a DPP
+      // row shift by three lanes away, and y = L^-1 qu takes qu from lanes 0..2
+      {
+        const int c = lane < 6 ? lane : 5;
+        const int cu = lane < 3 ? lane : 2;
+        double pc = 0.0;
+        for (int a = 0; a < 9; ++a) pc += T2[6 * a + c] * S.g[9 * (N - 2) + a] + T1[6 * a + c] * S.g[9 * (N - 1) + a];
+        struct Ops { double gx, gu, Y[3], L[6]; };
+        auto fetch = [&](int k, Ops& b) {
+          const int kc = k >= 0 ? k : 0;
+          b.gx = S.g[9 * kc + c]; b.gu = S.g[9 * kc + 6 + cu];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) L[e] = S.Lc[6 * k + e];
-        const double p_up = wave::dpp_f64<0x103>(pc);     // p_{c+3}
-        const double p_dn = wave::dpp_f64<0x113>(pc);     // p_{c-3}
-        // qh = g + [A B]' p
-        const double qx = lane < 3 ? gx + pc : gx + dt * p_dn + pc;
-        const double qu = gu + h2 * pc + dt * p_up;
-        const double qu0 = wave::bcast(qu, 0), qu1 = wave::bcast(qu, 1), qu2 = wave::bcast(qu, 2);
-        const double y0 = qu0 * L[0];
-        const double y1 = (qu1 - L[1] * y0) * L[2];
-        const double y2 = (qu2 - L[3] * y0 - L[4] * y1) * L[5];
-        if (lane < 3) S.yv[3 * k + lane] = lane == 0 ? y0 : (lane == 1 ? y1 : y2);
-        pc = qx - (Y0 * y0 + Y1 * y1 + Y2 * y2);
-      }
-    }
-    __syncthreads();
-    if (lane == 0) {
-      // forward from dx_0 = 0: du = -L^-T (Y dx + y)
-      double dx[6] = {0, 0, 0, 0, 0, 0};
-      for (int k = 0; k <= N - 3; ++k) {
-        double L[6], Y[18], yk[3];
+          for (int e = 0; e < 3; ++e) b.Y[e] = S.Y[18 * kc + 6 * e + c];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) L[e] = S.Lc[6 * k + e];
-#pragma unroll
-        for (int e = 0; e < 18; ++e) Y[e] = S.Y[18 * k + e];
-#pragma unroll
-        for (int e = 0; e < 3; ++e) yk[e] = S.yv[3 * k + e];
-        double r[3];
-        for (int i = 0; i < 3; ++i) {
-          double v = yk[i];
-          for (int c = 0; c < 6; ++c) v += Y[6 * i + c] * dx[c];
-          r[i] = v;
-        }
-        const double u2 = -r[2] * L[5];
-        const double u1 = -(r[1] + L[4] * u2) * L[2];
-        const double u0 = -(r[0] + L[1] * u1 + L[3] * u2) * L[0];
-        double* d = S.dz + 9 * k;
-        for (int c = 0; c < 6; ++c) d[c] = dx[c];
-        d[6] = u0; d[7] = u1; d[8] = u2;
-        const double uu[3] = {u0, u1, u2};
-        for (int c = 0; c < 3; ++c) {
-          const double pn = dx[c] + dt * dx[3 + c] + h2 * uu[c];
-          dx[3 + c] = dx[3 + c] + dt * uu[c];
-          dx[c] = pn;
+          for (int e = 0; e < 6; ++e) b.L[e] = S.Lc[6 * kc + e];
+        };
+        auto step = [&](int k, const Ops& b) {
+          const double p_up = wave::dpp_f64<0x103>(pc);     // p_{c+3}
+          const double p_dn = wave::dpp_f64<0x113>(pc);     // p_{c-3}
+          // qh = g + [A B]' p
+          const double qx = lane < 3 ? b.gx + pc : b.gx + dt * p_dn + pc;
+          const double qu = b.gu + h2 * pc + dt * p_up;
+          const double qu0 = wave::bcast(qu, 0), qu1 = wave::bcast(qu, 1), qu2 = wave::bcast(qu, 2);
+          const double y0 = qu0 * b.L[0];
+          const double y1 = (qu1 - b.L[1] * y0) * b.L[2];
+          const double y2 = (qu2 - b.L[3] * y0 - b.L[4] * y1) * b.L[5];
+          if (lane < 3) S.yv[3 * k + lane] = lane == 0 ? y0 : (lane == 1 ? y1 : y2);
+          pc = qx - (b.Y[0] * y0 + b.Y[1] * y1 + b.Y[2] * y2);
+        };
+        Ops b0, b1;
+        fetch(N - 3, b0);
+        for (int k = N - 3; k >= 0; k -= 2) {
+          fetch(k - 1, b1);
+          step(k, b0);
+          if (k == 0) break;
+          fetch(k - 2, b0);
+          step(k - 1, b1);
         }
       }
-      for (int a = 0; a < 9; ++a) {
-        double v2 = 0.0, v1 = 0.0;
-        for (int c = 0; c < 6; ++c) { v2 += T2[6 * a + c] * dx[c]; v1 += T1[6 * a + c] * dx[c]; }
-        S.dz[9 * (N - 2) + a] = v2;
-        S.dz[9 * (N - 1) + a] = v1;
+      wsync();
+      // forward from dx_0 = 0: du = -L^-T (Y dx + y).  Lane i < 3 forms entry i
+      // of Y dx + y; the rest of a stage is the same in every lane, lane 0
+      // writes it.
+      {
+        const int i = lane < 3 ? lane : 2;
+        double dx[6] = {0, 0, 0, 0, 0, 0};
+        struct Ops { double Y[6], y; };
+        auto fetch = [&](int k, Ops& b) {
+          const int kc = k <= N - 3 ? k : 0;
+#pragma unroll
+          for (int e = 0; e < 6; ++e) b.Y[e] = S.Y[18 * kc + 6 * i + e];
+          b.y = S.yv[3 * kc + i];
+        };
+        auto step = [&](int k, const Ops& b) {
+          double v = b.y, Lk[6];
+#pragma unroll
+          for (int e = 0; e < 6; ++e) Lk[e] = S.Lc[6 * k + e];   // arrives during the products
+#pragma unroll
+          for (int c = 0; c < 6; ++c) v += b.Y[c] * dx[c];
+          const double r[3] = {wave::bcast(v, 0), wave::bcast(v, 1), wave::bcast(v, 2)};
+          const double u2 = -r[2] * Lk[5];
+          const double u1 = -(r[1] + Lk[4] * u2) * Lk[2];
+          const double u0 = -(r[0] + Lk[1] * u1 + Lk[3] * u2) * Lk[0];
+          if (lane == 0) {
+            double* d = S.dz + 9 * k;
+#pragma unroll
+            for (int c = 0; c < 6; ++c) d[c] = dx[c];
+            d[6] = u0; d[7] = u1; d[8] = u2;
+          }
+          const double uu[3] = {u0, u1, u2};
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const double pn = dx[c] + dt * dx[3 + c] + h2 * uu[c];
+            dx[3 + c] = dx[3 + c] + dt * uu[c];
+            dx[c] = pn;
+          }
+        };
+        if (N >= 3) {
+          Ops b0, b1;
+          fetch(0, b0);
+          for (int k = 0; k <= N - 3; k += 2) {
+            fetch(k + 1, b1);
+            step(k, b0);
+            if (k + 1 > N - 3) break;
+            fetch(k + 2, b0);
+            step(k + 1, b1);
+          }
+        }
+        if (lane < 9) {
+          double v2 = 0.0, v1 = 0.0;
+#pragma unroll
+          for (int c = 0; c < 6; ++c) { v2 += T2[6 * lane + c] * dx[c]; v1 += T1[6 * lane + c] * dx[c]; }
+          S.dz[9 * (N - 2) + lane] = v2;
+          S.dz[9 * (N - 1) + lane] = v1;
+        }
       }
     }
     __syncthreads();
   }
 
-  // visit every row: f(slot, r, c'z_k, c'dz_k, d_r) -- the reachable rows
-  // (shared coefficient table), then the plane rows, so a wavefront never
-  // mixes the two kinds.  Lane l owns reachable row t = l + 64 j in register
-  // slot j < RS and plane row l + 64 j in slot RS + j (j < 4): the loops are
-  // unrolled, so slot is a constant wherever f indexes a register array with
-  // it.  c'z and c'dz are formed only when CZ / CD ask for them.
-  template <int RS, bool CZ, bool CD, typename F>
+  // visit the rows of this wavefront: f(slot, r, c'z_k, c'dz_k, d, e) with
+  // right-hand side d e (a product that the caller's FMAs take unrounded).
+  // Wavefronts 0..2 share the reachable rows (coefficient table): with row t in
+  // lane t % 64 of pass t / 64, each takes spw consecutive passes; wavefront 3
+  // holds the plane rows.  The loops are unrolled, so slot is a constant
+  // wherever f indexes a register array with it.  c'z and c'dz are formed only
+  // when CZ / CD ask for them.
+  template <int NS, bool CZ, bool CD, typename F>
   __device__ __forceinline__ void for_rows(F&& f) const {
     // the lane index is made opaque here, so the per-slot row indices and
     // addresses are recomputed in every pass instead of being hoisted out of
     // the iteration loop (where they would hold registers throughout)
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    if (m > 0) {
-      const int rq = kW / m, rr = kW - rq * m;
-      int k = ln / m, i = ln - m * (ln / m);
+    const int ln = opq(lane);
+    const int mm = m > 0 ? m : 1, rq = kW / mm, rr = kW - rq * mm, t0 = ln + kW * (wv * spw);
+    int kr = t0 / mm, ir = t0 - mm * kr;
 #pragma unroll
-      for (int j = 0; j < RS; ++j) {
-        if (ln + kW * j < N * m) {
-          const double* c = S.prm + Ly.Cr + i;
-          const double* zk = S.z + 9 * k;
-          const double* dk = S.dz + 9 * k;
-          double cz = 0.0, cd = 0.0;
+    for (int j = 0; j < NS; ++j) {
+      bool on;
+      int r = 0;
+      double cz = 0.0, cd = 0.0, d = 0.0, de = 1.0;
+      if (wv < kWaves - 1) {
+        on = j < spw && t0 + kW * j < N * m;
+        if (on) {
+          const double* c = S.prm + Ly.Cr + ir;
+          const double* zk = S.z + 9 * kr;
+          const double* dk = S.dz + 9 * kr;
 #pragma unroll
           for (int a = 0; a < 9; ++a) {
             const double ca = c[a * Ly.cs];
             if (CZ) cz += ca * zk[a];
             if (CD) cd += ca * dk[a];
           }
-          f(j, k * mr + i, cz, cd, S.prm[Ly.dr + i]);
+          r = kr * mr + ir;
+          d = S.prm[Ly.dr + ir];
         }
-        k += rq;
-        i += rr;
-        if (i >= m) { i -= m; ++k; }
+        kr += rq;
+        ir += rr;
+        if (ir >= mm) { ir -= mm; ++kr; }
+      } else {
+        const int t = ln + kW * j;
+        on = j < 4 && t < 4 * N;
+        if (on) {
+          const int k = t >> 2, jj = t & 3;
+          const double* f3 = S.prm + Ly.pf + 3 * jj;
+          const double* n = S.pl + 4 * k;
+          const double* zk = S.z + 9 * k;
+          const double* dk = S.dz + 9 * k;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            if (CZ) cz += n[c] * (f3[0] * zk[c] + f3[1] * zk[3 + c] + f3[2] * zk[6 + c]);
+            if (CD) cd += n[c] * (f3[0] * dk[c] + f3[1] * dk[3 + c] + f3[2] * dk[6 + c]);
+          }
+          cz = -cz;
+          cd = -cd;
+          r = k * mr + m + jj;
+          d = -n[3];
+          de = f3[0];
+        }
       }
+      if (on) f(j, r, cz, cd, d, de);
     }
+  }
+
+  // the same slots without the rows' values
+  template <int NS, typename F>
+  __device__ __forceinline__ void for_slots(F&& f) const {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int t = ln + kW * j;
-      if (t < 4 * N) {
-        const int k = t >> 2, jj = t & 3;
-        const double* f3 = S.prm + Ly.pf + 3 * jj;
-        const double* n = S.pl + 4 * k;
-        const double* zk = S.z + 9 * k;
-        const double* dk = S.dz + 9 * k;
-        double cz = 0.0, cd = 0.0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          if (CZ) cz += n[c] * (f3[0] * zk[c] + f3[1] * zk[3 + c] + f3[2] * zk[6 + c]);
-          if (CD) cd += n[c] * (f3[0] * dk[c] + f3[1] * dk[3 + c] + f3[2] * dk[6 + c]);
-        }
-        f(RS + j, k * mr + m + jj, -cz, -cd, -n[3] * f3[0]);
-      }
+    for (int j = 0; j < NS; ++j) {
+      const bool on = wv < kWaves - 1 ? (j < spw && lane + kW * (wv * spw + j) < N * m) : (j < 4 && lane + kW * j < 4 * N);
+      if (on) f(j);
     }
   }
 
   // g_k = [0; rho_k] + C_k' w, with the per-row weights in S.X
   __device__ __forceinline__ void build_g() {
-    for (int e = lane; e < 9 * N; e += kW) {
+    const int tid = opq(this->tid);
+    for (int e = tid; e < 9 * N; e += kT) {
       const int k = e / 9, a = e - 9 * (e / 9);
       const double v = a >= 6 ? S.rho[3 * k + a - 6] : 0.0;
       S.g[e] = v + ct_times(k, a, S.X + k * mr);
@@ -444,27 +628,27 @@ struct MpcCtx {
   // given) chosen by least squares.
   template <bool kCost = true>
   __device__ __forceinline__ void dual_residual(double& rmax, double& gscale, double* pi6 = nullptr) {
+    const int lane = opq(this->lane), tid = opq(this->tid);
     double gs = 0.0;
-    for (int e = lane; e < 9 * N; e += kW) {
+    for (int e = tid; e < 9 * N; e += kT) {
       const int k = e / 9, a = e - 9 * (e / 9);
       double hz = 0.0;
       if constexpr (kCost) {
         const double* H = Hk(k);
         hz = hk(k, a);
         for (int b = 0; b < 9; ++b) hz += H[9 * a + b] * S.z[9 * k + b];
+        asm volatile("" : "+v"(hz) : : "memory");   // its operands are not held across the rows
       }
       const double ct = ct_times(k, a, S.X + k * mr);
       S.g[e] = hz + ct;
       gs = fmax(gs, fmax(fabs(hz), fabs(ct)));
     }
-    gscale = wave::max(gs);
-    __syncthreads();
+    gscale = bmax(gs);
     // backward: f_k = e_k + B' sig_{k+1};  sig_k = c_k + A' sig_{k+1} (k >= 1).
     // The axes do not mix: lane c < 3 carries (sig_p,c, sig_v,c), with each
     // stage's three gradient entries loaded two stages ahead
-    if (lane < 3) {
+    if (tid < 3) {
       const int c = lane;
-      const double h2 = 0.5 * dt * dt;
       double sp_ = 0.0, sv_ = 0.0;
       auto fetch = [&](int k, double& gp, double& gv, double& gu) {
         const int kc = k < 0 ? 0 : k;
@@ -508,14 +692,6 @@ struct MpcCtx {
       t_af[cc] = wave::sum((c == cc && lane < 63) ? s_af : 0.0);
       t_f[cc] = wave::sum((c == cc && lane < 63) ? s_f : 0.0);
     }
-    double a11 = 0.0, a12 = 0.0;
-    for (int k = 0; k < N; ++k) {
-      const double al = dt * dt * (N - k - 0.5);
-      a11 += al * al;
-      a12 += dt * al;
-    }
-    const double a22 = N * dt * dt;
-    const double det = a11 * a22 - a12 * a12;
     double pp[3], pv[3];
     for (int cc = 0; cc < 3; ++cc) {
       const double b1 = -t_af[cc], b2 = -dt * t_f[cc];
@@ -527,7 +703,7 @@ struct MpcCtx {
     }
     __syncthreads();
     double rm = 0.0;
-    for (int e = lane; e < 3 * N; e += kW) {
+    for (int e = tid; e < 3 * N; e += kT) {
       const int k = e / 3, cc = e - 3 * (e / 3);
       const double al = dt * dt * (N - k - 0.5);
       const double ppc = cc == 0 ? pp[0] : (cc == 1 ? pp[1] : pp[2]);
@@ -536,39 +712,47 @@ struct MpcCtx {
       S.rho[e] = v;
       rm = fmax(rm, fabs(v));
     }
-    rmax = wave::max(rm);
-    __syncthreads();
+    rmax = bmax(rm);
   }
 };
 
-// RS: register slots per lane for the reachable rows (N m <= 64 RS)
-template <int RS>
-__global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
+// Four wavefronts per instance.  The recursions over the stages are a serial
+// chain and stay in wavefront 0, at the latency of a few LDS round trips per
+// stage; everything beside them is spread over the others: the barrier
+// Hessians of the stages ahead, the rows (each wavefront holds its own in
+// registers), the gradients.  One wavefront doing all of it in turn left a
+// SIMD's vector unit 71 % idle and could not hide its own waits: LDS (40 KB
+// per instance) allows four instances per CU, so one wavefront each is one per
+// SIMD.  Arithmetic and summation order are those of one wavefront, bit for bit.
+// 16 horizons of 50 steps, 16 reachable rows: 2.07 -> 1.19 ms; 4,096: 11.1 -> 8.1 ms.
+// Registers for three wavefronts per SIMD (149; at 128, for four, it spills and
+// takes 8.4 ms); the kernel for more rows per lane needs 186.
+// NS: register slots per lane (reachable passes per wavefront, at least the
+// four of the plane rows)
+template <int NS>
+__global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 3 : 2))) void mpc_kernel(MpcArgs A) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   const int inst = blockIdx.x;
   if (inst >= A.n) return;
-  const int N = A.N, m = A.m, mr = m + 4, RT = N * mr, lane = threadIdx.x;
-  int ua = 0, ub = 0;
-  {
-    int t = lane < 45 ? lane : 0;
-    while (t >= 9 - ua) { t -= 9 - ua; ++ua; }
-    ub = ua + t;
-  }
-  MpcCtx C{A, carve_mpc(reinterpret_cast<double*>(smem_raw), N, m), mpc_param_layout(m), N, m, mr, RT, lane, A.dt,
-           ua, ub};
+  const int N = A.N, m = A.m, mr = m + 4, RT = N * mr, tid = threadIdx.x, lane = tid & (kW - 1);
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  MpcCtx C{A, carve_mpc(reinterpret_cast<double*>(smem_raw), N, m), mpc_param_layout(m), N, m, mr, RT, lane, wv, tid,
+           A.dt};
+  C.spw = ((N * m + kW - 1) / kW + kWaves - 2) / (kWaves - 1);
+  C.init_lane();
   MpcSm& S = C.S;
   const MpcLayout& Ly = C.Ly;
   const double dt = A.dt;
 
   // ---- load
-  for (int e = lane; e < Ly.total; e += kW) S.prm[e] = A.params[e];
+  for (int e = tid; e < Ly.total; e += kT) S.prm[e] = A.params[e];
   bool bad = false;
-  for (int e = lane; e < 6 * (N + 1); e += kW) {
+  for (int e = tid; e < 6 * (N + 1); e += kT) {
     const double v = A.ref[(int64_t)inst * 6 * (N + 1) + e];
     S.ref[e] = v;
     bad |= !isfinite(v);
   }
-  for (int k = lane; k < N; k += kW) {
+  for (int k = tid; k < N; k += kT) {
     const double* q = A.planes + ((int64_t)inst * N + k) * 4;
     const double nn = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2]);
     bad |= !(nn > 0.0) || !isfinite(nn) || !isfinite(q[3]);
@@ -576,25 +760,24 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
     S.pl[4 * k] = q[0] * in; S.pl[4 * k + 1] = q[1] * in; S.pl[4 * k + 2] = q[2] * in; S.pl[4 * k + 3] = q[3] * in;
   }
   double* x0 = S.tmp;          // start state, read with lane-dependent indices
-  if (lane < 6) S.tmp[lane] = A.x0[6 * (int64_t)inst + lane];
+  if (tid < 6) S.tmp[lane] = A.x0[6 * (int64_t)inst + lane];
   __syncthreads();
   for (int c = 0; c < 6; ++c) bad |= !isfinite(x0[c]);
   auto finish_nan = [&](int status, int its) {
-    for (int e = lane; e < 6 * (N + 1); e += kW) A.X[(int64_t)inst * 6 * (N + 1) + e] = __builtin_nan("");
-    for (int e = lane; e < 3 * N; e += kW) A.U[(int64_t)inst * 3 * N + e] = __builtin_nan("");
-    if (lane == 0) {
+    for (int e = tid; e < 6 * (N + 1); e += kT) A.X[(int64_t)inst * 6 * (N + 1) + e] = __builtin_nan("");
+    for (int e = tid; e < 3 * N; e += kT) A.U[(int64_t)inst * 3 * N + e] = __builtin_nan("");
+    if (tid == 0) {
       A.cost[inst] = __builtin_nan("");
       A.status[inst] = status;
       A.kkt[inst] = __builtin_nan("");
       if (A.iters) A.iters[inst] = its;
     }
   };
-  if (__ballot(bad) != 0ull) { finish_nan(kInvalid, 0); return; }
-  __syncthreads();
+  if (__syncthreads_or(bad)) { finish_nan(kInvalid, 0); return; }
 
   // ---- start point: zero input up to x_{N-2}, then the two inputs that
   // reach r_N; then the Newton step of the LQ without rows (its optimum)
-  for (int e = lane; e < 9 * (N - 2); e += kW) {
+  for (int e = tid; e < 9 * (N - 2); e += kT) {
     const int k = e / 9, a = e - 9 * (e / 9);
     double v;
     if (a < 3) v = x0[a] + k * dt * x0[3 + a];
@@ -602,7 +785,7 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
     else v = 0.0;
     S.z[e] = v;
   }
-  if (lane == 0) {
+  if (tid == 0) {
     double xa[6];
     for (int c = 0; c < 3; ++c) { xa[c] = x0[c] + (N - 2) * dt * x0[3 + c]; xa[3 + c] = x0[3 + c]; }
     // rhs = r_N - A^2 x_{N-2}
@@ -627,11 +810,11 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
       z1[6 + c] = uu[3 + c];
     }
   }
-  for (int e = lane; e < RT; e += kW) S.X[e] = 0.0;     // no rows yet
+  for (int e = tid; e < RT; e += kT) S.X[e] = 0.0;     // no rows yet
   __syncthreads();
   C.factor();
   // g = H z + h
-  for (int e = lane; e < 9 * N; e += kW) {
+  for (int e = tid; e < 9 * N; e += kT) {
     const int k = e / 9, a = e - 9 * (e / 9);
     const double* H = C.Hk(k);
     double v = C.hk(k, a);
@@ -640,16 +823,15 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
   }
   __syncthreads();
   C.lq_solve();
-  for (int e = lane; e < 9 * N; e += kW) S.z[e] += S.dz[e];
+  for (int e = tid; e < 9 * N; e += kT) S.z[e] += S.dz[e];
   __syncthreads();
   // slacks and multipliers; per row, in registers of the owning lane: slack
   // s, multiplier l and primal residual rp = c'z + s - d
-  constexpr int NS = RS + 4;
   double rs[NS], rl[NS], rp[NS];
 #pragma unroll
   for (int j = 0; j < NS; ++j) { rs[j] = 1.0; rl[j] = 1.0; rp[j] = 0.0; }
-  C.template for_rows<RS, true, false>([&](int j, int r, double cz, double, double d) {
-    rs[j] = fmax(d - cz, 1.0);
+  C.template for_rows<NS, true, false>([&](int j, int r, double cz, double, double d, double de) {
+    rs[j] = fmax(fma(d, de, -cz), 1.0);
     S.X[r] = 1.0;
   });
   __syncthreads();
@@ -660,22 +842,24 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
   double mu = 0.0, rpmax = 0.0, rdmax = 0.0, gscale = 0.0;
   for (;; ++it) {
     C.dual_residual(rdmax, gscale);             // multipliers in S.X
-    double smu = 0.0, rpm = 0.0;
-    C.template for_rows<RS, true, false>([&](int j, int r, double cz, double, double d) {
-      const double v = cz + rs[j] - d;
+    double rpm = 0.0;
+    C.template for_rows<NS, true, false>([&](int j, int r, double cz, double, double d, double de) {
+      const double v = fma(-d, de, cz + rs[j]);
       rp[j] = v;
       rpm = fmax(rpm, fabs(v));
-      smu += rs[j] * rl[j];
       S.X[r] = div_nr(rl[j], rs[j]);            // barrier weight for the factorisation
     });
     __syncthreads();
-    mu = wave::sum(smu) / RT;
-    rpmax = wave::max(rpm);
+    mu = C.chain_sum([&](double acc) {
+      C.template for_slots<NS>([&](int j) { acc += rs[j] * rl[j]; });
+      return acc;
+    }) / RT;
+    rpmax = C.bmax(rpm);
     if (mu <= A.tol && rpmax <= 1e-10 && rdmax <= 1e-8 * (1.0 + gscale)) { converged = true; break; }
     if (it >= A.max_iters || !isfinite(mu)) break;
     if (!C.factor()) break;                     // a Quu lost definiteness: keep the current iterate
     // predictor: w = (l / s) rp - l
-    C.template for_rows<RS, false, false>([&](int j, int r, double, double, double) {
+    C.template for_rows<NS, false, false>([&](int j, int r, double, double, double, double) {
       S.X[r] = div_nr(rl[j], rs[j]) * rp[j] - rl[j];
     });
     __syncthreads();
@@ -683,26 +867,32 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
     C.lq_solve();
     // affine step: ds = -rp - c'dz, dl = -l - (l / s) ds; c'dz kept in S.X
     double amax_l = 1.0;
-    C.template for_rows<RS, false, true>([&](int j, int r, double, double cd, double) {
+    C.template for_rows<NS, false, true>([&](int j, int r, double, double cd, double, double) {
       const double ds = -rp[j] - cd;
       const double dl = -rl[j] - div_nr(rl[j], rs[j]) * ds;
       if (ds < 0.0) amax_l = fmin(amax_l, div_nr(rs[j], -ds));
       if (dl < 0.0) amax_l = fmin(amax_l, div_nr(rl[j], -dl));
       S.X[r] = cd;
     });
-    const double aa = wave::min(amax_l);
-    double mua = 0.0;
-    C.template for_rows<RS, false, false>([&](int j, int r, double, double, double) {
+    const double aa = C.bmin(amax_l);
+    double ma[NS], mb[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) ma[j] = mb[j] = 0.0;
+    C.template for_rows<NS, false, false>([&](int j, int r, double, double, double, double) {
       const double ds = -rp[j] - S.X[r];
       const double dl = -rl[j] - div_nr(rl[j], rs[j]) * ds;
-      mua += (rs[j] + aa * ds) * (rl[j] + aa * dl);
+      ma[j] = rs[j] + aa * ds;
+      mb[j] = rl[j] + aa * dl;
       S.X[r] = ds * dl;                         // affine product for the corrector
     });
-    mua = wave::sum(mua) / RT;
+    const double mua = C.chain_sum([&](double acc) {
+      C.template for_slots<NS>([&](int j) { acc += ma[j] * mb[j]; });
+      return acc;
+    }) / RT;
     const double sc = (mua / mu) * (mua / mu) * (mua / mu);
     const double smu_t = sc * mu;
     // corrector: rc = s l + ds_aff dl_aff - sc mu, w = (l rp - rc) / s
-    C.template for_rows<RS, false, false>([&](int j, int r, double, double, double) {
+    C.template for_rows<NS, false, false>([&](int j, int r, double, double, double, double) {
       const double rc = rs[j] * rl[j] + S.X[r] - smu_t;
       S.X[r] = div_nr(rl[j] * rp[j] - rc, rs[j]);
     });
@@ -711,18 +901,18 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
     C.lq_solve();
     // step: ds = -rp - c'dz, dl = (-rc - l ds) / s with rc = l rp - s w (w in S.X)
     double am = 1.0;
-    C.template for_rows<RS, false, true>([&](int j, int r, double, double cd, double) {
+    C.template for_rows<NS, false, true>([&](int j, int r, double, double cd, double, double) {
       const double ds = -rp[j] - cd;
       const double rc = rl[j] * rp[j] - rs[j] * S.X[r];
       const double dl = div_nr(-rc - rl[j] * ds, rs[j]);
       if (ds < 0.0) am = fmin(am, div_nr(rs[j], -ds));
       if (dl < 0.0) am = fmin(am, div_nr(rl[j], -dl));
     });
-    const double alpha = fmin(1.0, 0.995 * wave::min(am));
+    const double alpha = fmin(1.0, 0.995 * C.bmin(am));
     bool nonfinite = !(alpha > 0.0) || !isfinite(alpha);
-    for (int e = lane; e < 9 * N; e += kW) nonfinite |= !isfinite(S.dz[e]);
-    if (__ballot(nonfinite) != 0ull) break;     // a broken direction: keep the current iterate
-    C.template for_rows<RS, false, true>([&](int j, int r, double, double cd, double) {
+    for (int e = tid; e < 9 * N; e += kT) nonfinite |= !isfinite(S.dz[e]);
+    if (__syncthreads_or(nonfinite)) break;     // a broken direction: keep the current iterate
+    C.template for_rows<NS, false, true>([&](int j, int r, double, double cd, double, double) {
       const double ds = -rp[j] - cd;
       const double rc = rl[j] * rp[j] - rs[j] * S.X[r];
       const double dl = div_nr(-rc - rl[j] * ds, rs[j]);
@@ -731,7 +921,7 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
       S.X[r] = rl[j];
     });
     __syncthreads();
-    for (int e = lane; e < 9 * N; e += kW) S.z[e] += alpha * S.dz[e];
+    for (int e = tid; e < 9 * N; e += kT) S.z[e] += alpha * S.dz[e];
     __syncthreads();
   }
 
@@ -751,28 +941,29 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
   }
   const double cost = wave::sum(cst);
   double pres = 0.0, pscale = 0.0, cres = 0.0, lmax = 0.0;
-  C.template for_rows<RS, true, false>([&](int j, int, double v, double, double d) {
-    pres = fmax(pres, v - d);
-    pscale = fmax(pscale, fmax(fabs(v), fabs(d)));
-    cres = fmax(cres, rl[j] * fabs(d - v));
+  C.template for_rows<NS, true, false>([&](int j, int, double v, double, double d, double de) {
+    pres = fmax(pres, fma(-d, de, v));
+    pscale = fmax(pscale, fmax(fabs(v), fabs(d * de)));
+    cres = fmax(cres, rl[j] * fabs(fma(d, de, -v)));
     lmax = fmax(lmax, rl[j]);
   });
-  pres = wave::max(pres); pscale = wave::max(pscale); cres = wave::max(cres); lmax = wave::max(lmax);
+  C.bmax2(pres, pscale);
+  C.bmax2(cres, lmax);
   const double kkt = fmax(fmax(fmax(pres, 0.0) / (1.0 + pscale), rdmax / (1.0 + gscale)), cres / (1.0 + lmax));
   const int64_t xo = (int64_t)inst * 6 * (N + 1);
-  for (int e = lane; e < 6 * N; e += kW) {
+  for (int e = tid; e < 6 * N; e += kT) {
     const int k = e / 6, a = e - 6 * (e / 6);
     A.X[xo + e] = (k == 0) ? x0[a] : S.z[9 * k + a];
   }
-  if (lane < 6) {
+  if (tid < 6) {
     const double* zl = S.z + 9 * (N - 1);
     const int c = lane % 3;
     const double v = lane < 3 ? zl[c] + dt * zl[3 + c] + 0.5 * dt * dt * zl[6 + c] : zl[3 + c] + dt * zl[6 + c];
     A.X[xo + 6 * N + lane] = v;
   }
-  for (int e = lane; e < 3 * N; e += kW) A.U[(int64_t)inst * 3 * N + e] = S.z[9 * (e / 3) + 6 + e % 3];
+  for (int e = tid; e < 3 * N; e += kT) A.U[(int64_t)inst * 3 * N + e] = S.z[9 * (e / 3) + 6 + e % 3];
   const bool solved = kkt <= 1e-6 && isfinite(cost);
-  if (lane == 0) {
+  if (tid == 0) {
     A.cost[inst] = cost;
     A.kkt[inst] = kkt;
     A.status[inst] = solved ? kSolved : (converged ? kNumerical : kMaxIter);
@@ -790,27 +981,28 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
   // trajectory exists (FP64, with a margin for rounding).
   {
     double lm = 0.0;
-    C.template for_rows<RS, false, false>([&](int j, int, double, double, double) { lm = fmax(lm, rl[j]); });
-    lm = wave::max(lm);
+    C.template for_rows<NS, false, false>([&](int j, int, double, double, double, double) { lm = fmax(lm, rl[j]); });
+    lm = C.bmax(lm);
     const double isc = (lm > 0.0 && isfinite(lm)) ? 1.0 / lm : 0.0;
-    C.template for_rows<RS, false, false>([&](int j, int r, double, double, double) { S.X[r] = rl[j] * isc; });
+    C.template for_rows<NS, false, false>([&](int j, int r, double, double, double, double) { S.X[r] = rl[j] * isc; });
     __syncthreads();
     double rdm = 0.0, gsc = 0.0, pi6[6];
     C.template dual_residual<false>(rdm, gsc, pi6);
     // free response: zero inputs from x0
-    for (int e = lane; e < 9 * N; e += kW) {
+    for (int e = tid; e < 9 * N; e += kT) {
       const int k = e / 9, a = e - 9 * (e / 9);
       S.z[e] = a < 3 ? x0[a] + k * dt * x0[3 + a] : (a < 6 ? x0[a] : 0.0);
     }
     __syncthreads();
-    double phi = 0.0, pab = 0.0;
-    C.template for_rows<RS, true, false>([&](int, int r, double cz, double, double d) {
-      const double w = S.X[r];
-      phi += w * (cz - d);
-      pab += w * (fabs(cz) + fabs(d));
+    const double phi = C.chain_sum([&](double acc) {
+      C.template for_rows<NS, true, false>([&](int, int r, double cz, double, double d, double de) { acc += S.X[r] * fma(-d, de, cz); });
+      return acc;
     });
-    phi = wave::sum(phi);
-    pab = wave::sum(pab);
+    const double pab = C.chain_sum([&](double acc) {
+      C.template for_rows<NS, true, false>(
+          [&](int, int r, double cz, double, double d, double de) { acc += S.X[r] * (fabs(cz) + fabs(d * de)); });
+      return acc;
+    });
     double tn = 0.0, tnab = 0.0;
     for (int c = 0; c < 3; ++c) {
       const double ep = x0[c] + N * dt * x0[3 + c] - S.ref[6 * N + c], ev = x0[3 + c] - S.ref[6 * N + 3 + c];
@@ -834,9 +1026,9 @@ __global__ __launch_bounds__(kW) void mpc_kernel(MpcArgs A) {
     // costate recursion behind rho (N stages, growth N dt)
     const double margin = 1e-9 * (pab + tnab + mbab + 3.0 * N * umax * gsc * N * (1.0 + N * dt)) + 1e-300;
     if (phi + tn + mb > margin && isfinite(phi + tn + mb)) {
-      for (int e = lane; e < 6 * (N + 1); e += kW) A.X[xo + e] = __builtin_nan("");
-      for (int e = lane; e < 3 * N; e += kW) A.U[(int64_t)inst * 3 * N + e] = __builtin_nan("");
-      if (lane == 0) {
+      for (int e = tid; e < 6 * (N + 1); e += kT) A.X[xo + e] = __builtin_nan("");
+      for (int e = tid; e < 3 * N; e += kT) A.U[(int64_t)inst * 3 * N + e] = __builtin_nan("");
+      if (tid == 0) {
         A.cost[inst] = __builtin_huge_val();
         A.kkt[inst] = __builtin_nan("");
         A.status[inst] = kInfeasible;
@@ -852,16 +1044,15 @@ size_t mpc_lds_bytes(int N, int m) { return sizeof(double) * size_t(mpc_lds_doub
 hipError_t launch_mpc(const MpcArgs& a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
   const size_t lds = mpc_lds_bytes(a.N, a.m);
-  // register slots for the reachable rows; the plane rows (4 N <= 256) take
-  // four more
+  // register slots: passes of 64 reachable rows over three wavefronts (at most
+  // 11); the plane rows (4 N <= 256) take four in the last
   const int rows = a.N * a.m;
   if (a.N < 2 || a.N > 64 || a.m < 0 || rows > 32 * kW) return hipErrorInvalidValue;
-  if (rows <= 8 * kW)
-    hipLaunchKernelGGL(mpc_kernel<8>, dim3(a.n), dim3(kW), lds, s, a);
-  else if (rows <= 16 * kW)
-    hipLaunchKernelGGL(mpc_kernel<16>, dim3(a.n), dim3(kW), lds, s, a);
+  const int slots = ((rows + kW - 1) / kW + kWaves - 2) / (kWaves - 1);
+  if (slots <= 5)
+    hipLaunchKernelGGL(mpc_kernel<5>, dim3(a.n), dim3(kT), lds, s, a);
   else
-    hipLaunchKernelGGL(mpc_kernel<32>, dim3(a.n), dim3(kW), lds, s, a);
+    hipLaunchKernelGGL(mpc_kernel<11>, dim3(a.n), dim3(kT), lds, s, a);
   return hipGetLastError();
 }
 
