@@ -26,6 +26,8 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <type_traits>
+#include <vector>
 
 #include "rbp_internal.hpp"
 #include "rbp_wave.hpp"
@@ -33,6 +35,23 @@
 namespace rbp {
 
 __constant__ DegConst c_chain_deg[kMaxDeg + 1];
+
+// The Hessian of a path on its free global points depends on the number of
+// segments S alone (times T^-3), G = L L^T.  Per S the inverse of L, NF x NF
+// (NF = 5 S + 1 free points), laid out so that lane i reads entry i of a
+// contiguous row: by columns, and by rows for its transpose.  Formed on the host
+// in extended precision when a device's first batch is built.  G^-1 itself is of
+// no use: a row's normal is a difference of neighbouring points, and products
+// of G^-1 with it lose about five digits more than L^-1 and L^-T in turn.
+constexpr int kChainDeg = 7, kChainMaxSeg = 12;
+constexpr int chain_free(int S) { return (kChainDeg - 1) + (S - 1) * (kChainDeg - 2); }
+constexpr int chain_tab(int S) {   // offset of S segments' tables
+  int o = 0;
+  for (int t = 1; t < S; ++t) o += chain_free(t) * chain_free(t);
+  return o;
+}
+constexpr int kChainTab = chain_tab(kChainMaxSeg + 1);
+static __device__ double t_Lc[kChainTab], t_Lr[kChainTab];
 
 namespace {
 
@@ -45,6 +64,13 @@ constexpr int kRetry = 6;
 constexpr float kBigF = 1e30f;
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+// 1 / sqrt(x), x > 0, from the hardware approximation refined to full precision
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  const double hx = 0.5 * x;
+  r = r * fma(-hx * r, r, 1.5);
+  return r * fma(-hx * r, r, 1.5);
+}
 __device__ __forceinline__ double sel3(int c, double a, double b, double d) {
   return c == 0 ? a : (c == 1 ? b : d);
 }
@@ -52,9 +78,10 @@ __device__ __forceinline__ double sel3(int c, double a, double b, double d) {
 template <int P>
 struct CLds {
   static constexpr int NP = P + 1, NC = 3 * (P + 1), BW = 3 * (P + 1) - 1;
+  static constexpr int NB = NC | 1;   // row stride of the cached normals (read one row per lane)
   int *nf, *nr, *f0, *rowoff;
   int64_t *r0, *hb;
-  double *Af, *bfs, *rb, *Pseg, *gfull, *G1b, *L1b, *L1r, *qv, *xu, *x, *scal;
+  double *Af, *bfs, *rb, *Pseg, *gfull, *G1b, *qv, *xu, *x, *scal;
   float *fan, *rn;
   int* cand;
   unsigned* actbits;
@@ -83,8 +110,6 @@ __device__ CLds<P> ccarve(char* s, const ChainDims& D) {
   L.Pseg = (double*)(s + D.o_Pseg);
   L.gfull = (double*)(s + D.o_gfull);
   L.G1b = (double*)(s + D.o_G1b);
-  L.L1b = (double*)(s + D.o_L1b);
-  L.L1r = (double*)(s + D.o_L1r);
   L.qv = (double*)(s + D.o_qv);
   L.xu = L.qv + 3 * D.nf_pts_cap;
   L.x = (double*)(s + D.o_x);
@@ -126,7 +151,8 @@ __device__ __forceinline__ double mcoef(int s, int k, int j) {
 template <int P>
 __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch, char* smem) {
   using L_t = CLds<P>;
-  constexpr int NP = L_t::NP, NC = L_t::NC, BW = L_t::BW;
+  constexpr int NP = L_t::NP, NC = L_t::NC, BW = L_t::BW, NB = L_t::NB;
+  static_assert(P == kChainDeg, "the tables of L^-1 are for this degree");
   const int lane = threadIdx.x;
   const DegConst& K = c_chain_deg[P];
   const ChainDims& D = A.dims;
@@ -344,105 +370,50 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     L.G1b[e] = v;
   }
   __syncthreads();
-  // band Cholesky of the free block (global points 1..NG-2 -> i = g-1), right-looking
-  for (int e = lane; e < NF * (P + 1); e += kWave) {
-    const int i = e / (P + 1), d = e - (P + 1) * (e / (P + 1));
-    L.L1b[e] = (i - d >= 0) ? L.G1b[(i + 1) * (P + 1) + d] : 0.0;
-  }
-  __syncthreads();
-  for (int i = 0; i < NF; ++i) {
-    const double piv = L.L1b[i * (P + 1)];
-    const double dd = sqrt(fmax(piv, 1e-300));
-    __syncthreads();
-    if (lane == 0) L.L1b[i * (P + 1)] = dd;
-    if (lane >= 1 && lane <= P && i + lane < NF) L.L1b[(i + lane) * (P + 1) + lane] /= dd;
-    __syncthreads();
-    // trailing update of the band: (k, j) with i < j <= k <= i + P
-    if (lane < P * (P + 1) / 2) {
-      int a = 0, rem = lane;
-      while (rem > a) { rem -= a + 1; ++a; }
-      const int kk = i + 1 + a, jj = i + 1 + rem;   // jj <= kk
-      if (kk < NF) {
-        const double lk = L.L1b[kk * (P + 1) + (kk - i)], lj = L.L1b[jj * (P + 1) + (jj - i)];
-        L.L1b[kk * (P + 1) + (kk - jj)] -= lk * lj;
+  // Products with L^-1 and L^-T (x) I3 from the tables, one lane per free
+  // point, three coordinates per lane.  The banded substitution these replace
+  // walks the points one after the other, four sweeps of up to 61 points per
+  // polish step; a product reads 30 KB from L2 at most but nothing in it waits
+  // for anything else.  L^-1 is applied on its own, as the substitution was, so
+  // that |L^-1 d|^2 stays a sum of squares.
+  const int toff = ((S - 1) * (36 + 6 * 5 * (S - 2)) + 25 * ((S - 2) * (S - 1) * (2 * S - 3) / 6));
+  const int li = lane < NF ? lane : NF - 1;
+  constexpr int kU = 16;                      // rows of a table in flight
+  auto tri = [&](const double* tab, bool lower, double b0, double b1, double b2, double& y0, double& y1, double& y2) {
+    // y_i = sum over j <= i (lower) or j >= i of tab[j NF + i] b_j
+    y0 = 0.0; y1 = 0.0; y2 = 0.0;
+    double t[kU];
+    auto fetch = [&](int j0) {
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int j = j0 + u;
+        t[u] = (j < NF && lane < NF && (lower ? j <= lane : j >= lane)) ? tab[j * NF + li] : 0.0;
+      }
+    };
+    fetch(0);
+    for (int j0 = 0; j0 < NF; j0 += kU) {
+      double c[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) c[u] = t[u];
+      fetch(j0 + kU);
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int j = j0 + u < kWave ? j0 + u : 0;
+        y0 += c[u] * wave::bcast(b0, j);
+        y1 += c[u] * wave::bcast(b1, j);
+        y2 += c[u] * wave::bcast(b2, j);
       }
     }
-    __syncthreads();
-  }
-  // banded solves with G1 (x) I3: lane = free point, 3 coordinates per lane
-  // G = L L^T on the points (the same banded factor for each coordinate):
-  // forward half-solve leaves y = L^-1 rhs in registers (lane = point),
-  // backward half-solve writes L^-T y; reciprocal diagonal in L1r
-  for (int i = lane; i < NF; i += kWave) L.L1r[i] = 1.0 / L.L1b[i * (P + 1)];
-  __syncthreads();
-  // Banded forward / backward solves, one lane per free point.  The band
-  // coefficient a lane needs at a point and that point's reciprocal pivot do
-  // not depend on the solution: they are loaded two points ahead (the loop
-  // handles two points per pass), from addresses clamped into the factor, and
-  // lanes outside the band multiply theirs by zero (the clamped entries are
-  // finite), so no load waits behind a branch.
+    y0 *= T15; y1 *= T15; y2 *= T15;
+  };
   auto gfwd = [&](const double* rhs, double& y0, double& y1, double& y2) {
-    y0 = 0; y1 = 0; y2 = 0;
-    if (lane < NF) { y0 = rhs[3 * lane]; y1 = rhs[3 * lane + 1]; y2 = rhs[3 * lane + 2]; }
-    const int jj = lane < NF ? lane : NF - 1;
-    auto fetch = [&](int i, double& dinv, double& l) {      // L[lane][i] below the diagonal, else 0
-      const int ic = i < NF ? i : NF - 1;
-      const int d = lane - i, dc = d < 0 ? 0 : (d > P ? P : d);
-      dinv = L.L1r[ic];
-      l = L.L1b[jj * (P + 1) + dc] * ((d > 0 && d <= P && lane < NF) ? 1.0 : 0.0);
-    };
-    auto step = [&](int i, double dinv, double l) {
-      const double a0 = wave::bcast(y0, i) * dinv, a1 = wave::bcast(y1, i) * dinv, a2 = wave::bcast(y2, i) * dinv;
-      const bool piv = lane == i;
-      y0 = piv ? a0 : y0 - l * a0;
-      y1 = piv ? a1 : y1 - l * a1;
-      y2 = piv ? a2 : y2 - l * a2;
-    };
-    if (NF <= 0) return;
-    double dA, lA, dB, lB;
-    fetch(0, dA, lA);
-    fetch(1, dB, lB);
-    int i = 0;
-    for (; i + 1 < NF; i += 2) {
-      double dC, lC, dD, lD;
-      fetch(i + 2, dC, lC);
-      fetch(i + 3, dD, lD);
-      step(i, dA, lA);
-      step(i + 1, dB, lB);
-      dA = dC; lA = lC; dB = dD; lB = lD;
-    }
-    if (i < NF) step(i, dA, lA);
+    const bool on = lane < NF;
+    tri(t_Lc + toff, true, on ? rhs[3 * li] : 0.0, on ? rhs[3 * li + 1] : 0.0, on ? rhs[3 * li + 2] : 0.0, y0, y1, y2);
   };
   auto gbwd = [&](double y0, double y1, double y2, double* out) {
-    auto fetch = [&](int i, double& dinv, double& l) {      // L[i][lane] above i in the band, else 0
-      const int ic = i < 0 ? 0 : i;
-      const int d = i - lane, dc = d < 0 ? 0 : (d > P ? P : d);
-      dinv = L.L1r[ic];
-      l = L.L1b[ic * (P + 1) + dc] * ((d > 0 && d <= P && i >= 0) ? 1.0 : 0.0);
-    };
-    auto step = [&](int i, double dinv, double l) {
-      const double a0 = wave::bcast(y0, i) * dinv, a1 = wave::bcast(y1, i) * dinv, a2 = wave::bcast(y2, i) * dinv;
-      const bool piv = lane == i;
-      y0 = piv ? a0 : y0 - l * a0;
-      y1 = piv ? a1 : y1 - l * a1;
-      y2 = piv ? a2 : y2 - l * a2;
-    };
-    if (NF > 0) {
-      double dA, lA, dB, lB;
-      fetch(NF - 1, dA, lA);
-      fetch(NF - 2, dB, lB);
-      int i = NF - 1;
-      for (; i - 1 >= 0; i -= 2) {
-        double dC, lC, dD, lD;
-        fetch(i - 2, dC, lC);
-        fetch(i - 3, dD, lD);
-        step(i, dA, lA);
-        step(i - 1, dB, lB);
-        dA = dC; lA = lC; dB = dD; lB = lD;
-      }
-      if (i >= 0) step(i, dA, lA);
-    }
-    if (lane < NF) { out[3 * lane] = y0; out[3 * lane + 1] = y1; out[3 * lane + 2] = y2; }
+    double z0, z1, z2;
+    tri(t_Lr + toff, false, y0, y1, y2, z0, z1, z2);
+    if (lane < NF) { out[3 * lane] = z0; out[3 * lane + 1] = z1; out[3 * lane + 2] = z2; }
     __syncthreads();
   };
   auto gsolve = [&](const double* rhs, double* out) {
@@ -827,39 +798,72 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
 
   // entering normal of (id, side): beta cache slot ``slot``; also writes the
   // global normal into L.np
+  // (entries on the pinned points are 0)
   auto load_normal = [&](int id, int side, int slot) {
     const int s = seg_of(id);
     const int loc = id - L.rowoff[s];
+    const int ws = (P - 2) * s;
+    const int j = lane / 3, c = lane - 3 * (lane / 3);
+    double al = 0.0;
     if (lane < NC) {
-      // window coefficients beta = M_s^T alpha (per coordinate)
-      const int j = lane / 3, c = lane - 3 * (lane / 3);
-      double v = 0.0;
-      for (int k = 0; k < NP; ++k) {
-        const double mk = mcoef(s, k, j);
-        if (mk != 0.0) v += mk * alpha_at(s, loc, 3 * k + c);
-      }
-      L.beta[slot * NC + lane] = double(side) * v;
+      al = alpha_at(s, loc, lane);
+      if (lane < 9) L.scal[lane] = al;
     }
     if (lane == 0) L.actseg[slot] = s;
     __syncthreads();
-    for (int e = lane; e < n; e += kWave) L.np[e] = 0.0;
-    __syncthreads();
-    const int ws = (P - 2) * s;
     if (lane < NC) {
-      const int g = ws + lane / 3;
-      if (g >= 1 && g <= NG - 2) L.np[3 * (g - 1) + (lane - 3 * (lane / 3))] = L.beta[slot * NC + lane];
+      // window coefficients beta = M_s^T alpha (per coordinate; M_s is the
+      // identity but for the first three points of a segment past the first)
+      double v = 0.0;
+      if (s > 0 && j < 3) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const double mk = mcoef(s, k, j);
+          if (mk != 0.0) v += mk * L.scal[3 * k + c];
+        }
+      } else {
+        v = al;
+      }
+      const int g = ws + j;
+      L.beta[slot * NB + lane] = (g >= 1 && g <= NG - 2) ? double(side) * v : 0.0;
+    }
+    __syncthreads();
+    for (int e = lane; e < n; e += kWave) {
+      const int w = e - 3 * (ws - 1);
+      L.np[e] = (w >= 0 && w < NC) ? L.beta[slot * NB + w] : 0.0;
     }
     __syncthreads();
   };
-  // dot of the window normal in slot k with a global vector
+  // dot of the window normal in slot k with a global vector (whose entries at
+  // the pinned points do not exist: any entry stands in, times 0)
   auto ndot = [&](int k, const double* v) -> double {
-    const int ws = (P - 2) * L.actseg[k];
+    const int sgk = L.actseg[k], o = 3 * ((P - 2) * sgk - 1);
+    const double* b = L.beta + k * NB;
     double acc = 0.0;
+#pragma unroll
     for (int e = 0; e < NC; ++e) {
-      const int g = ws + e / 3;
-      if (g >= 1 && g <= NG - 2) acc += L.beta[k * NC + e] * v[3 * (g - 1) + (e - 3 * (e / 3))];
+      const int i = e < 3 ? (sgk > 0 ? o + e : 0) : (e >= NC - 3 ? (sgk < S - 1 ? o + e : 0) : o + e);
+      acc += b[e] * v[i];
     }
     return acc;
+  };
+  // u = G^-1 n for the window normal n in slot k (segment sgk): L^-1 n takes
+  // eight rows of the table
+  auto gsolve_window = [&](int k, int sgk, double* out) {
+    const int i0 = (P - 2) * sgk - 1;          // free index of the window's first point
+    double t[NP], y0 = 0.0, y1 = 0.0, y2 = 0.0;
+#pragma unroll
+    for (int w = 0; w < NP; ++w) {
+      const int j = i0 + w;                    // beta is 0 where j is no free point
+      t[w] = lane < NF ? t_Lc[toff + (j < 0 ? 0 : (j < NF ? j : NF - 1)) * NF + li] : 0.0;
+    }
+#pragma unroll
+    for (int w = 0; w < NP; ++w) {
+      y0 += t[w] * L.beta[k * NB + 3 * w];
+      y1 += t[w] * L.beta[k * NB + 3 * w + 1];
+      y2 += t[w] * L.beta[k * NB + 3 * w + 2];
+    }
+    gbwd(T15 * y0, T15 * y1, T15 * y2, out);
   };
   // c = N^T u for the working set, u in L.u
   auto nt_u = [&](double& c0, double& c1) {
@@ -871,76 +875,79 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
   // the solution: they are loaded two steps ahead, from addresses clamped to
   // entries the factor holds (finite), and lanes that do not take part
   // multiply theirs by zero, so no load waits behind a branch.
-  auto ls_forward = [&](double& v0, double& v1, int qq) {
-    if (qq <= 0) return;
+  // Up to 64 rows each lane has one entry and the second slot's work is left out.
+  auto ls_sweep = [&](auto fwd, auto two, double& v0, double& v1, int qq) {
+    constexpr bool kFwd = decltype(fwd)::value, kTwo = decltype(two)::value;
     const int a0 = e0 < qq ? e0 : qq - 1, a1 = e1 < qq ? e1 : qq - 1;
-    auto fetch = [&](int k, double& d, double& l0, double& l1) {   // L_S[e][k] below the diagonal
-      const int kc = k < qq ? k : qq - 1;
-      d = L.LSd[kc];
-      l0 = L.LS[lso(a0) + (kc < a0 ? kc : a0)] * ((e0 > k && e0 < qq) ? 1.0 : 0.0);
-      l1 = L.LS[lso(a1) + (kc < a1 ? kc : a1)] * ((e1 > k && e1 < qq) ? 1.0 : 0.0);
+    const int o0 = lso(a0), o1 = lso(a1);
+    auto fetch = [&](int t, double& d, double& l0, double& l1) {
+      const int tc = t < qq ? t : qq - 1, k = kFwd ? tc : qq - 1 - tc;
+      d = L.LSd[k];
+      if (kFwd) {   // L_S[e][k] below the diagonal
+        l0 = L.LS[o0 + (k < a0 ? k : a0)] * ((e0 > k && e0 < qq) ? 1.0 : 0.0);
+        if (kTwo) l1 = L.LS[o1 + (k < a1 ? k : a1)] * ((e1 > k && e1 < qq) ? 1.0 : 0.0);
+      } else {      // L_S[k][e] left of the diagonal
+        l0 = L.LS[lso(k) + (e0 < k ? e0 : k)] * (e0 < k ? 1.0 : 0.0);
+        if (kTwo) l1 = L.LS[lso(k) + (e1 < k ? e1 : k)] * (e1 < k ? 1.0 : 0.0);
+      }
     };
-    auto step = [&](int k, double d, double l0, double l1) {
-      const double vk = pick(v0, v1, k) * d;
+    auto step = [&](int t, double d, double l0, double l1) {
+      const int k = kFwd ? t : qq - 1 - t;
+      const double vk = (kTwo ? pick(v0, v1, k) : wave::bcast(v0, k)) * d;
       v0 = e0 == k ? vk : v0 - l0 * vk;
-      v1 = e1 == k ? vk : v1 - l1 * vk;
+      if (kTwo) v1 = e1 == k ? vk : v1 - l1 * vk;
     };
-    double dA, xA, yA, dB, xB, yB;
+    double dA, xA, yA = 0.0, dB, xB, yB = 0.0;
     fetch(0, dA, xA, yA);
     fetch(1, dB, xB, yB);
-    int k = 0;
-    for (; k + 1 < qq; k += 2) {
-      double dC, xC, yC, dD, xD, yD;
-      fetch(k + 2, dC, xC, yC);
-      fetch(k + 3, dD, xD, yD);
-      step(k, dA, xA, yA);
-      step(k + 1, dB, xB, yB);
+    int t = 0;
+    for (; t + 1 < qq; t += 2) {
+      double dC, xC, yC = 0.0, dD, xD, yD = 0.0;
+      fetch(t + 2, dC, xC, yC);
+      fetch(t + 3, dD, xD, yD);
+      step(t, dA, xA, yA);
+      step(t + 1, dB, xB, yB);
       dA = dC; xA = xC; yA = yC; dB = dD; xB = xD; yB = yD;
     }
-    if (k < qq) step(k, dA, xA, yA);
+    if (t < qq) step(t, dA, xA, yA);
+  };
+  auto ls_forward = [&](double& v0, double& v1, int qq) {
+    if (qq <= 0) return;
+    if (qq <= kWave) ls_sweep(std::true_type{}, std::false_type{}, v0, v1, qq);
+    else ls_sweep(std::true_type{}, std::true_type{}, v0, v1, qq);
   };
   auto ls_backward = [&](double& v0, double& v1, int qq) {
     if (qq <= 0) return;
-    auto fetch = [&](int k, double& d, double& l0, double& l1) {   // L_S[k][e] left of the diagonal
-      const int kc = k < 0 ? 0 : k;
-      d = L.LSd[kc];
-      l0 = L.LS[lso(kc) + (e0 < kc ? e0 : kc)] * (e0 < k ? 1.0 : 0.0);
-      l1 = L.LS[lso(kc) + (e1 < kc ? e1 : kc)] * (e1 < k ? 1.0 : 0.0);
-    };
-    auto step = [&](int k, double d, double l0, double l1) {
-      const double vk = pick(v0, v1, k) * d;
-      v0 = e0 == k ? vk : v0 - l0 * vk;
-      v1 = e1 == k ? vk : v1 - l1 * vk;
-    };
-    double dA, xA, yA, dB, xB, yB;
-    fetch(qq - 1, dA, xA, yA);
-    fetch(qq - 2, dB, xB, yB);
-    int k = qq - 1;
-    for (; k - 1 >= 0; k -= 2) {
-      double dC, xC, yC, dD, xD, yD;
-      fetch(k - 2, dC, xC, yC);
-      fetch(k - 3, dD, xD, yD);
-      step(k, dA, xA, yA);
-      step(k - 1, dB, xB, yB);
-      dA = dC; xA = xC; yA = yC; dB = dD; xB = xD; yB = yD;
-    }
-    if (k >= 0) step(k, dA, xA, yA);
+    if (qq <= kWave) ls_sweep(std::false_type{}, std::false_type{}, v0, v1, qq);
+    else ls_sweep(std::false_type{}, std::true_type{}, v0, v1, qq);
   };
-  // w = N r (global), r given by entries (r0, r1)
+  // w = N r (global), r given by entries (r0, r1): each lane sums its own
+  // entries of w over the rows whose window holds them
   auto n_times = [&](double r0, double r1, double* out) {
-    for (int e = lane; e < n; e += kWave) out[e] = 0.0;
-    __syncthreads();
-    if (e0 < q) L.cvec[e0] = r0;
-    if (e1 < q) L.cvec[e1] = r1;
-    __syncthreads();
-    for (int k = 0; k < q; ++k) {
-      const int ws = (P - 2) * L.actseg[k];
-      if (lane < NC) {
-        const int g = ws + lane / 3;
-        if (g >= 1 && g <= NG - 2) out[3 * (g - 1) + (lane - 3 * (lane / 3))] += L.cvec[k] * L.beta[k * NC + lane];
+    const int g0 = e0 < q ? L.actseg[e0] : 0, g1 = e1 < q ? L.actseg[e1] : 0;
+    double acc[3] = {0.0, 0.0, 0.0};
+    for (int k0 = 0; k0 < q; k0 += 4) {
+      double b[4][3], rk[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u < q ? k0 + u : q - 1;
+        const int sgk = __builtin_amdgcn_readlane(k < kWave ? g0 : g1, k & (kWave - 1));
+        rk[u] = k0 + u < q ? pick(r0, r1, k) : 0.0;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          const int w = lane + kWave * t - 3 * ((P - 2) * sgk - 1);
+          b[u][t] = (w >= 0 && w < NC) ? L.beta[k * NB + w] : 0.0;
+        }
       }
-      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) acc[t] += rk[u] * b[u][t];
     }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (lane + kWave * t < n) out[lane + kWave * t] = acc[t];
+    __syncthreads();
   };
   auto set_bit = [&](int id, bool on) {
     if (lane == 0) {
@@ -963,11 +970,9 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     row_bounds(s, id - L.rowoff[s], lo, hi);
     return side > 0 ? hi : -lo;
   };
-  // append constraint (id, side) whose normal sits in beta slot q and np;
-  // u = G^-1 np must be in L.u, c = N^T u in (c0, c1); zz = np^T u - |l|^2
-  auto append_factor = [&](int id, int side, double c0, double c1, double zz) {
-    double l0 = c0, l1 = c1;
-    ls_forward(l0, l1, q);
+  // append constraint (id, side), free right-hand side e_free, whose normal sits in beta slot q and np;
+  // l = L_S^-1 N^T G^-1 np in (l0, l1); zz = np^T G^-1 np - |l|^2
+  auto append_factor = [&](int id, int side, double e_free, double l0, double l1, double zz) {
     const int ro = lso(q);
     if (e0 < q) L.LS[ro + e0] = l0;
     if (e1 < q) L.LS[ro + e1] = l1;
@@ -976,33 +981,49 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       L.LS[ro + q] = dq;
       L.LSd[q] = 1.0 / dq;
       L.actid[q] = id; L.actside[q] = side;
-      L.acte[q] = row_e(id, side) - double(side) * row_const(id);
+      L.acte[q] = e_free;
     }
     set_bit(id, true);
     ++q;
     __syncthreads();
   };
-  // Cholesky delete of index kd (Givens on columns of the rows below)
+  // Cholesky delete of index kd: the rows below move up one place, then Givens
+  // rotations of the columns (kd, kd+1), (kd+1, kd+2), .. restore the triangle.
+  // A lane moves its own columns and rotates its own rows, so nothing in either
+  // loop waits for another lane's store: a lane carries its row's entry of the
+  // column in work, and rotation j takes its pair from lane j.
   auto drop = [&](int kd) {
     set_bit(L.actid[kd], false);
+    // ids, sides, right-hand sides: entries e0 and e1 take their successors'
+    const int s0i = e0 >= kd && e0 < q - 1 ? e0 + 1 : -1, s1i = e1 >= kd && e1 < q - 1 ? e1 + 1 : -1;
+    int id0 = 0, sd0 = 0, sg0 = 0, id1 = 0, sd1 = 0, sg1 = 0;
+    double ev0 = 0.0, ev1 = 0.0;
     __syncthreads();
-    // shift rows kd+1.. up by one (packed L_S, beta slots, ids): row k + 1
-    // (columns 0..k+1) becomes row k, whose spare slot takes column k + 1
-    for (int k = kd; k < q - 1; ++k) {
-      const int rs = lso(k + 1), rd = lso(k);
-      double a0 = 0.0, a1 = 0.0, bv = 0.0;
-      if (e0 <= k + 1) a0 = L.LS[rs + e0];
-      if (e1 <= k + 1) a1 = L.LS[rs + e1];
-      if (lane < NC) bv = L.beta[(k + 1) * NC + lane];
-      int id = 0, sd = 0, sg = 0;
-      double ev = 0.0;
-      if (lane == 0) { id = L.actid[k + 1]; sd = L.actside[k + 1]; sg = L.actseg[k + 1]; ev = L.acte[k + 1]; }
-      __syncthreads();
-      if (e0 <= k + 1) L.LS[rd + e0] = a0;
-      if (e1 <= k + 1) L.LS[rd + e1] = a1;
-      if (lane < NC) L.beta[k * NC + lane] = bv;
-      if (lane == 0) { L.actid[k] = id; L.actside[k] = sd; L.actseg[k] = sg; L.acte[k] = ev; }
-      __syncthreads();
+    if (s0i >= 0) { id0 = L.actid[s0i]; sd0 = L.actside[s0i]; sg0 = L.actseg[s0i]; ev0 = L.acte[s0i]; }
+    if (s1i >= 0) { id1 = L.actid[s1i]; sd1 = L.actside[s1i]; sg1 = L.actseg[s1i]; ev1 = L.acte[s1i]; }
+    __syncthreads();
+    if (s0i >= 0) { L.actid[e0] = id0; L.actside[e0] = sd0; L.actseg[e0] = sg0; L.acte[e0] = ev0; }
+    if (s1i >= 0) { L.actid[e1] = id1; L.actside[e1] = sd1; L.actseg[e1] = sg1; L.acte[e1] = ev1; }
+    // row k + 1 (columns 0..k+1) becomes row k, whose spare slot takes column
+    // k + 1; four rows in flight
+    for (int k0 = kd; k0 < q - 1; k0 += 4) {
+      double a0[4], a1[4], bv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u;
+        const bool on = k < q - 1;
+        a0[u] = (on && e0 <= k + 1) ? L.LS[lso(k + 1) + e0] : 0.0;
+        a1[u] = (on && e1 <= k + 1) ? L.LS[lso(k + 1) + e1] : 0.0;
+        bv[u] = (on && lane < NC) ? L.beta[(k + 1) * NB + lane] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u;
+        const bool on = k < q - 1;
+        if (on && e0 <= k + 1) L.LS[lso(k) + e0] = a0[u];
+        if (on && e1 <= k + 1) L.LS[lso(k) + e1] = a1[u];
+        if (on && lane < NC) L.beta[k * NB + lane] = bv[u];
+      }
     }
     {
       // entry j takes entry j + 1 (entry 64 comes from lane 0's second slot)
@@ -1013,32 +1034,33 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       if (e0 >= kd && e0 < q - 1) lam0 = n0;
       if (e1 >= kd && e1 < q - 1) lam1 = up1;
     }
-    // rows kd..q-2 now have an entry one past the diagonal: rotate columns (j, j+1)
+    __syncthreads();
+    // rows kd..q-2 have an entry one past the diagonal
+    const bool in0 = e0 >= kd && e0 < q - 1, in1 = e1 >= kd && e1 < q - 1;
+    const int r0w = lso(in0 ? e0 : kd), r1w = lso(in1 ? e1 : kd);
+    double c0 = L.LS[r0w + kd], c1 = L.LS[r1w + kd];          // entries of column kd
+    // column j + 1 of a row that reaches it (row e holds columns 0..e+1)
+    auto col0 = [&](int j) { return (in0 && j <= e0 + 1) ? L.LS[r0w + j] : 0.0; };
+    auto col1 = [&](int j) { return (in1 && j <= e1 + 1) ? L.LS[r1w + j] : 0.0; };
+    double x0n = col0(kd + 1), x1n = col1(kd + 1);
     for (int j = kd; j < q - 1; ++j) {
-      const int rj = lso(j);
-      const double a = L.LS[rj + j], b = L.LS[rj + j + 1];
-      const double rr = hypot(a, b);
-      const double cg = rr > 0.0 ? a / rr : 1.0, sg = rr > 0.0 ? b / rr : 0.0;
-      const bool w0 = e0 >= j && e0 < q - 1, w1 = e1 >= j && e1 < q - 1;
-      double x10 = 0, x20 = 0, x11 = 0, x21 = 0;
-      if (w0) { x10 = L.LS[lso(e0) + j]; x20 = L.LS[lso(e0) + j + 1]; }
-      if (w1) { x11 = L.LS[lso(e1) + j]; x21 = L.LS[lso(e1) + j + 1]; }
-      __syncthreads();
-      if (w0) {
-        L.LS[lso(e0) + j] = cg * x10 + sg * x20;
-        L.LS[lso(e0) + j + 1] = -sg * x10 + cg * x20;
-      }
-      if (w1) {
-        L.LS[lso(e1) + j] = cg * x11 + sg * x21;
-        L.LS[lso(e1) + j + 1] = -sg * x11 + cg * x21;
-      }
-      __syncthreads();
+      const double x0c = x0n, x1c = x1n;
+      x0n = col0(j + 2);
+      x1n = col1(j + 2);
+      const double a = pick(c0, c1, j), b = pick(x0c, x1c, j);
+      const double r2 = a * a + b * b;
+      const bool ok = r2 > 0.0;
+      const double ir = ok ? rsqrt_nr(r2) : 1.0;
+      const double cg = ok ? a * ir : 1.0, sg = ok ? b * ir : 0.0;
+      if (in0 && e0 >= j) L.LS[r0w + j] = cg * c0 + sg * x0c;
+      if (in1 && e1 >= j) L.LS[r1w + j] = cg * c1 + sg * x1c;
+      if (lane == 0) L.LSd[j] = ir;
+      c0 = cg * x0c - sg * c0;
+      c1 = cg * x1c - sg * c1;
     }
     --q;
     if (e0 >= q) lam0 = 0.0;
     if (e1 >= q) lam1 = 0.0;
-    if (e0 < q) L.LSd[e0] = 1.0 / L.LS[lso(e0) + e0];
-    if (e1 < q) L.LSd[e1] = 1.0 / L.LS[lso(e1) + e1];
     __syncthreads();
   };
   // smallest of the entries < q, lowest index on ties
@@ -1065,7 +1087,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     const int id = key >> 1, side = (key & 1) ? 1 : -1;
     if ((L.actbits[id >> 5] >> (id & 31)) & 1u) continue;
     load_normal(id, side, q);
-    gsolve(L.np, L.u);
+    gsolve_window(q, L.actseg[q], L.u);
     double c0, c1;
     nt_u(c0, c1);
     const double nu = nplus_dot(q, L.u);
@@ -1073,7 +1095,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     ls_forward(l0, l1, q);
     const double ll = wave::sum((e0 < q ? l0 * l0 : 0.0) + (e1 < q ? l1 * l1 : 0.0));
     const double zz = nu - ll;
-    if (zz > 1e-10 * nu) append_factor(id, side, c0, c1, zz);
+    if (zz > 1e-10 * nu) append_factor(id, side, row_e(id, side) - double(side) * row_const(id), l0, l1, zz);
   }
   // dual feasibility of the working set: S lam = N^T x_u - e
   for (int guard = 0; guard <= QC; ++guard) {
@@ -1138,35 +1160,119 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     build_points(L.x);
     double best = -1.0;
     int key = 0x7fffffff;
-    auto consider = [&](int s, int loc, int id) {
-      if ((L.actbits[id >> 5] >> (id & 31)) & 1u) return;
-      double lo, hi;
-      row_bounds(s, loc, lo, hi);
-      const double v = row_value(s, loc, L.Pseg + s * NC);
-      const double d = row_scale(s, loc);
+    double viol = 0.0;
+    // row ``id`` with value v, bounds lo and hi, scaling d: a candidate if it
+    // is not in the working set (looked up only for a row that would win)
+    auto consider = [&](int id, double v, double lo, double hi, double d) {
       const double vu = v - hi, vl = lo - v;
-      if (vu > ftol * (1.0 + fabs(hi)) && vu * d > best) { best = vu * d; key = 2 * id + 1; }
-      if (isfinite(lo) && vl > ftol * (1.0 + fabs(lo)) && vl * d > best) { best = vl * d; key = 2 * id; }
+      const bool up = vu > ftol * (1.0 + fabs(hi)) && vu * d > best;
+      const bool dn = lo > -1e300 && vl > ftol * (1.0 + fabs(lo)) && vl * d > (up ? vu * d : best);
+      if (!up && !dn) return;
+      if ((L.actbits[id >> 5] >> (id & 31)) & 1u) return;
+      best = dn ? vl * d : vu * d;
+      viol = dn ? vl : vu;
+      key = 2 * id + (dn ? 0 : 1);
     };
-    // the rows held in LDS (faces, velocity, acceleration) segment by
-    // segment, then the reachable rows, whose coefficients come from global
-    // memory, two segments per pass: the two kinds never share a pass, and
-    // two segments' reachable rows (<= 64 together) cost one global round trip
-    for (int s = 0; s < S; ++s) {
-      const int nl = NP * L.nf[s] + 6 * P - 3;
-      for (int loc = lane; loc < nl; loc += kWave) consider(s, loc, L.rowoff[s] + loc);
-    }
-    for (int s = 0; s < S; s += 2) {
-      const int nl0 = NP * L.nf[s] + 6 * P - 3, r0n = L.rowoff[s + 1] - L.rowoff[s] - nl0;
-      int nl1 = 0, r1n = 0;
-      if (s + 1 < S) { nl1 = NP * L.nf[s + 1] + 6 * P - 3; r1n = L.rowoff[s + 2] - L.rowoff[s + 1] - nl1; }
-      for (int u = lane; u < r0n + r1n; u += kWave) {
-        const int sp = u < r0n ? s : s + 1;
-        const int loc = u < r0n ? nl0 + u : nl1 + (u - r0n);
-        consider(sp, loc, L.rowoff[sp] + loc);
+    const double minf = -__builtin_huge_val();
+    // faces: one lane per face, its normal in registers while the eight points
+    // pass; two segments at a time, one per half of the wavefront, where no
+    // polytope has more than 32 faces
+    {
+      const int halves = NFC <= 32 ? 2 : 1, lanes = kWave / halves;
+      const int h = halves == 2 ? lane >> 5 : 0, j = lane & (lanes - 1);
+      for (int s1 = 0; s1 < S; s1 += halves) {
+        const int s = s1 + h;
+        if (s < S && j < L.nf[s]) {
+          const int nfs = L.nf[s];
+          const double* a = L.Af + (s * NFC + j) * 3;
+          const double a0 = a[0], a1 = a[1], a2 = a[2], hi = L.bfs[s * NFC + j], d = L.fan[s * NFC + j];
+          const double* Pp = L.Pseg + s * NC;
+          const int id0 = L.rowoff[s] + j;
+#pragma unroll
+          for (int k = 0; k < NP; ++k)
+            consider(id0 + k * nfs, a0 * Pp[3 * k] + a1 * Pp[3 * k + 1] + a2 * Pp[3 * k + 2], minf, hi, d);
+        }
       }
     }
-    wave::argmax(best, key);
+    // velocity and acceleration rows: one lane per row of a segment
+    if (lane < 6 * P - 3) {
+      const bool vel = lane < 3 * P;
+      const int e = vel ? lane : lane - 3 * P;              // 3 k + c
+      const double b = vel ? A.vmax : A.amax;
+      const double d = vel ? 1.0 / (sv * 1.4142135623730951) : 1.0 / (sa * 2.449489742783178);
+      for (int s = 0; s < S; ++s) {
+        const double* Pp = L.Pseg + s * NC + e;
+        const double p0 = Pp[0], p1 = Pp[3], p2 = Pp[vel ? 3 : 6];
+        const double v = vel ? sv * (p1 - p0) : sa * (p2 - 2.0 * p1 + p0);
+        consider(L.rowoff[s] + NP * L.nf[s] + lane, v, -b, b, d);
+      }
+    }
+    // reachable rows, whose coefficients come from global memory: two segments
+    // per pass (<= 64 rows together where each has at most 32), the next pass's
+    // rows loaded while this one's are worked on
+    {
+      struct Row { double h[NC], g[6]; };
+      auto rows_of = [&](int s, int& n0, int& n1) {
+        n0 = s < S ? L.rowoff[s + 1] - L.rowoff[s] - (NP * L.nf[s] + 6 * P - 3) : 0;
+        n1 = s + 1 < S ? L.rowoff[s + 2] - L.rowoff[s + 1] - (NP * L.nf[s + 1] + 6 * P - 3) : 0;
+      };
+      auto fetch = [&](int s, int u, Row& w) {
+        int n0, n1;
+        rows_of(s, n0, n1);
+        const bool on = u < n0 + n1;
+        const int sp = !on ? 0 : (u < n0 ? s : s + 1), l = !on ? 0 : (u < n0 ? u : u - n0);
+        const double* H = A.H + L.hb[sp] + (int64_t)l * NC;
+        const double* G = A.G + 6 * (L.r0[sp] + l);
+#pragma unroll
+        for (int e = 0; e < NC; ++e) w.h[e] = on ? H[e] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 6; ++e) w.g[e] = (on && sp > 0) ? G[e] : 0.0;
+      };
+      auto use = [&](int s, int u, const Row& w) {
+        int n0, n1;
+        rows_of(s, n0, n1);
+        if (u >= n0 + n1) return;
+        const int sp = u < n0 ? s : s + 1, l = u < n0 ? u : u - n0;
+        const double* Pp = L.Pseg + sp * NC;
+        double v = 0.0;
+#pragma unroll
+        for (int e = 0; e < NC; ++e) v += w.h[e] * Pp[e];
+        if (sp > 0) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) v += (-w.g[c] + sv * w.g[3 + c]) * Pp[c] - sv * w.g[3 + c] * Pp[3 + c];
+        }
+        consider(L.rowoff[sp] + NP * L.nf[sp] + 6 * P - 3 + l, v, minf, L.rb[sp * RC + l], L.rn[sp * RC + l]);
+      };
+      Row ra, rb_;
+      fetch(0, lane, ra);
+      for (int s = 0; s < S; s += 4) {
+        fetch(s + 2, lane, rb_);
+        use(s, lane, ra);
+        fetch(s + 4, lane, ra);
+        use(s + 2, lane, rb_);
+      }
+      // segments with more than 32 rows: what a pass of 64 lanes left
+      if (RC > 32) {
+        for (int s = 0; s < S; s += 2) {
+          int n0, n1;
+          rows_of(s, n0, n1);
+          for (int u = lane + kWave; u < n0 + n1; u += kWave) {
+            fetch(s, u, ra);
+            use(s, u, ra);
+          }
+        }
+      }
+    }
+    // the largest score; among equal ones the lowest row
+    {
+      double bm = best;
+      int km = key;
+      wave::argmax(bm, km);
+      const unsigned long long own = __ballot(best == bm && key == km);
+      best = bm;
+      key = km;
+      viol = wave::bcast(viol, own ? __builtin_ctzll(own) : 0);
+    }
     if (!(best > 0.0)) { status = kSolved; break; }
     if (q >= QC - 1 && QC < A.q_full) {
       for (int k = lane; k < q; k += kWave)
@@ -1177,21 +1283,20 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     }
     if (steps >= max_steps || key < 0 || (key >> 1) >= m || q >= QC - 1) { status = kPolishFailed; break; }
     const int id = key >> 1, side = (key & 1) ? 1 : -1;
-    const int sp = seg_of(id);
-    const double val = row_value(sp, id - L.rowoff[sp], L.Pseg + sp * NC);
     const double e_full = row_e(id, side);
-    double splus = double(side) * val - e_full;
+    double splus = viol;                    // side * value - e_full, from the lane that owns the row
     const double e_free = e_full - double(side) * row_const(id);
     load_normal(id, side, q);       // slot q holds the entering normal
     double lamp = 0.0;
     bool added = false;
     while (!added) {
       ++steps;
-      gsolve(L.np, L.u);                      // u = G^-1 n+
+      gsolve_window(q, L.actseg[q], L.u);     // u = G^-1 n+
       double c0, c1;
       nt_u(c0, c1);                           // c = N^T u
       double r0 = c0, r1 = c1;                // r = S^-1 c
       ls_forward(r0, r1, q);
+      const double l0 = r0, l1 = r1;          // L_S^-1 c, the row that appending adds
       ls_backward(r0, r1, q);
       if (e0 >= q) r0 = 0.0;
       if (e1 >= q) r1 = 0.0;
@@ -1262,7 +1367,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
         }
       }
       if (t2 <= t1) {
-        append_factor(id, side, c0, c1, zz);
+        append_factor(id, side, e_free, l0, l1, zz);
         if (e0 == q - 1) lam0 = lamp;
         if (e1 == q - 1) lam1 = lamp;
         added = true;
@@ -1378,8 +1483,6 @@ ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bo
   d.o_Pseg = take(d.s_cap * NC * 8);
   d.o_gfull = take(3 * d.ng_cap * 8);
   d.o_G1b = take(d.ng_cap * NP * 8);
-  d.o_L1b = take(d.nf_pts_cap * NP * 8);
-  d.o_L1r = take(d.nf_pts_cap * 8);
   d.o_qv = take(2 * 3 * d.nf_pts_cap * 8);
   d.o_x = take(d.n_cap * 8);
   d.o_scal = take(16 * 8);
@@ -1402,7 +1505,7 @@ ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bo
   auto take_b = [&](int bytes) { const int at = b; b += (bytes + 15) & ~15; return at; };
   d.o_LS = take_b(((d.q_cap * (d.q_cap + 3)) >> 1) * 8);   // packed rows, k + 2 slots each
   d.o_LSd = take_b(d.q_cap * 8);
-  d.o_beta = take_b(d.q_cap * NC * 8);
+  d.o_beta = take_b(d.q_cap * (NC | 1) * 8);
   d.o_acte = take_b(d.q_cap * 8);
   d.o_u = take_b(4 * d.n_cap * 8);
   d.o_cvec = take_b(d.q_cap * 8);
@@ -1413,12 +1516,69 @@ ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bo
   return d;
 }
 
+// L^-1 of every segment count (T = 1), in extended precision from the
+// degree's Hessian: G sums the window Hessians 2 Q1 (first segment) and
+// 2 M^T Q1 M, M the window map (mcoef).
+static bool build_chain_tables(const DegConst& K, std::vector<double>& Lc, std::vector<double>& Lr) {
+  typedef long double R;
+  constexpr int P = kChainDeg, NP = P + 1;
+  Lc.assign(kChainTab, 0.0);
+  Lr.assign(kChainTab, 0.0);
+  R M[NP][NP] = {}, W[2][NP][NP] = {};
+  for (int k = 0; k < NP; ++k) M[k][k] = 1;
+  M[0][0] = 0; M[0][2] = 1;
+  M[1][1] = -1; M[1][2] = 2;
+  M[2][0] = 1; M[2][1] = -4; M[2][2] = 4;
+  for (int a = 0; a < NP; ++a)
+    for (int b = 0; b < NP; ++b) {
+      W[0][a][b] = R(2) * R(K.Q1[a][b]);
+      for (int k = 0; k < NP; ++k)
+        for (int l = 0; l < NP; ++l) W[1][a][b] += M[k][a] * R(2) * R(K.Q1[k][l]) * M[l][b];
+    }
+  for (int S = 1; S <= kChainMaxSeg; ++S) {
+    const int NF = chain_free(S), o = chain_tab(S);
+    std::vector<R> G(size_t(NF) * NF, R(0)), Li(size_t(NF) * NF, R(0));
+    for (int s = 0; s < S; ++s)
+      for (int a = 0; a < NP; ++a)
+        for (int b = 0; b < NP; ++b) {
+          const int i = (P - 2) * s + a - 1, j = (P - 2) * s + b - 1;
+          if (i >= 0 && j >= 0 && i < NF && j < NF) G[size_t(i) * NF + j] += W[s > 0 ? 1 : 0][a][b];
+        }
+    for (int j = 0; j < NF; ++j) {              // Cholesky, lower triangle
+      for (int k = 0; k < j; ++k)
+        for (int i = j; i < NF; ++i) G[size_t(i) * NF + j] -= G[size_t(i) * NF + k] * G[size_t(j) * NF + k];
+      const R d = G[size_t(j) * NF + j];
+      if (!(d > 0)) return false;
+      const R r = std::sqrt(d);
+      for (int i = j; i < NF; ++i) G[size_t(i) * NF + j] /= r;
+    }
+    for (int c = 0; c < NF; ++c)                // its inverse, column by column
+      for (int i = c; i < NF; ++i) {
+        R v = i == c ? R(1) : R(0);
+        for (int k = c; k < i; ++k) v -= G[size_t(i) * NF + k] * Li[size_t(k) * NF + c];
+        Li[size_t(i) * NF + c] = v / G[size_t(i) * NF + i];
+      }
+    for (int i = 0; i < NF; ++i)
+      for (int j = 0; j < NF; ++j) {
+        Lc[size_t(o) + size_t(j) * NF + i] = double(Li[size_t(i) * NF + j]);
+        Lr[size_t(o) + size_t(i) * NF + j] = double(Li[size_t(i) * NF + j]);
+      }
+  }
+  return true;
+}
+
 hipError_t upload_chain_constants(int device) {
   (void)device;
   DegConst host[kMaxDeg + 1];
   std::memset(host, 0, sizeof(host));
   for (int p = kMinDeg; p <= kMaxDeg; ++p)
     if (!build_degree(p, host[p])) return hipErrorInvalidValue;
+  std::vector<double> Lc, Lr;
+  if (!build_chain_tables(host[kChainDeg], Lc, Lr)) return hipErrorInvalidValue;
+  hipError_t e;
+  if ((e = hipMemcpyToSymbol(HIP_SYMBOL(t_Lc), Lc.data(), kChainTab * sizeof(double), 0, hipMemcpyHostToDevice)) ||
+      (e = hipMemcpyToSymbol(HIP_SYMBOL(t_Lr), Lr.data(), kChainTab * sizeof(double), 0, hipMemcpyHostToDevice)))
+    return e;
   return hipMemcpyToSymbol(HIP_SYMBOL(c_chain_deg), host, sizeof(host), 0, hipMemcpyHostToDevice);
 }
 

@@ -131,7 +131,7 @@ struct BackArgs {
 // ---- multi-segment paths (rbp_chain.hip)
 struct ChainDims {
   int s_cap, nf_cap, r_cap, q_cap, nf_pts_cap, ng_cap, n_cap, m_cap;
-  int o_segi, o_seg64, o_Af, o_bfs, o_fan, o_rb, o_rn, o_Pseg, o_gfull, o_G1b, o_L1b, o_L1r, o_qv, o_x, o_scal,
+  int o_segi, o_seg64, o_Af, o_bfs, o_fan, o_rb, o_rn, o_Pseg, o_gfull, o_G1b, o_qv, o_x, o_scal,
       o_cand, o_bits;
   int o_Kb, o_zr, o_yr, o_accp, o_Pf, o_xt, o_Cs, o_Wm;          // ADMM part of the region
   int o_LS, o_LSd, o_beta, o_acte, o_u, o_cvec, o_actid;          // polish part of the region
