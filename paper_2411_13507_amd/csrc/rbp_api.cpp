@@ -746,11 +746,14 @@ int rbp_solve_chains(rbp_chains* c, const double* x0, const double* goal, const 
     a.N = g.start + g.count;
     a.q_full = q_full;
     a.retry_only = 0;
-    a.dims = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_first, admm);
+    a.dims = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_first, admm, false);
     e = rbp::launch_chains(a, gs);
     if (e == hipSuccess && q_first < q_full) {
       a.retry_only = 1;
-      a.dims = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_full, admm);
+      a.dims = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_full, admm, true);
+      // the four-wavefront kernel's mailbox takes 6 KB more LDS
+      if (size_t(a.dims.bytes) > kLdsBytes)
+        a.dims = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_full, admm, false);
       e = rbp::launch_chains(a, gs);
     }
   }

@@ -62,6 +62,9 @@ constexpr int kSolved = 0, kInfeasible = 1, kPolishFailed = 3, kNumerical = 4, k
 // overwrites every output
 constexpr int kRetry = 6;
 constexpr float kBigF = 1e30f;
+// wavefronts per path of the team kernel, and what the first asks of the others
+constexpr int kTeamWaves = 4;
+constexpr int kJobExit = 0, kJobScan = 1, kJobLower = 2, kJobUpper = 3;
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // 1 / sqrt(x), x > 0, from the hardware approximation refined to full precision
@@ -148,12 +151,26 @@ __device__ __forceinline__ double mcoef(int s, int k, int j) {
   return j == 2 ? 4.0 : (j == 1 ? -4.0 : (j == 0 ? 1.0 : 0.0));   // k == 2
 }
 
-template <int P>
+// kTeam = false: one wavefront per path.  kTeam = true: a workgroup of four; the
+// first runs the method, the others take their share of the two jobs that are
+// wide, the violation scan and the products with L^-1, and wait in between.
+template <int P, bool kTeam>
 __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch, char* smem) {
   using L_t = CLds<P>;
   constexpr int NP = L_t::NP, NC = L_t::NC, BW = L_t::BW, NB = L_t::NB;
   static_assert(P == kChainDeg, "the tables of L^-1 are for this degree");
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wv = kTeam ? __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)) : 0;
+  // orders LDS accesses between the lanes of this wavefront
+  auto sync = [&]() {
+    if constexpr (kTeam) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    } else {
+      __syncthreads();
+    }
+  };
   const DegConst& K = c_chain_deg[P];
   const ChainDims& D = A.dims;
   L_t L = ccarve<P>(smem, D);
@@ -170,7 +187,6 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
   for (int e = 0; e < 6; ++e) { x0[e] = A.x0[6 * (int64_t)ch + e]; bad |= !isfinite(x0[e]); }
   for (int c = 0; c < 3; ++c) { dg[c] = A.goal[3 * (int64_t)ch + c] - x0[c]; bad |= !isfinite(dg[c]); }
   const int64_t pbase = (int64_t)NC * s0;   // output offset (doubles)
-  (void)T15;
 
   auto finish = [&](int status) {
     for (int e = lane; e < S * NC; e += kWave) A.P_out[pbase + e] = __builtin_nan("");
@@ -178,6 +194,231 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       A.cost_out[ch] = status == kInfeasible ? __builtin_huge_val() : __builtin_nan("");
       A.status_out[ch] = status;
       A.kkt_out[ch] = __builtin_nan("");
+    }
+  };
+
+  // ---- the two wide jobs, in parts (part of parts; one wavefront each)
+  const int NFC = D.nf_cap, RC = D.r_cap;
+  const int toff = ((S - 1) * (36 + 6 * 5 * (S - 2)) + 25 * ((S - 2) * (S - 1) * (2 * S - 3) / 6));
+  const int li = lane < NF ? lane : NF - 1;
+  constexpr int kU = 16;                      // rows of a table in flight
+  // Products with L^-1 and L^-T (x) I3 from the tables, one lane per free
+  // point, three coordinates per lane: y_i = T^1.5 times the sum over j <= i
+  // (lower, L^-1) or j >= i of tab[j NF + i] b_j, whose other entries are 0 in
+  // the table: every lane loads every row, without a branch.  b must be 0 in
+  // lanes past the last free point.  The banded substitution these
+  // replace walks the points one after the other, four sweeps of up to 61 points
+  // per polish step; a product reads 30 KB from L2 at most but nothing in it
+  // waits for anything else.  L^-1 is applied on its own, as the substitution
+  // was, so that |L^-1 d|^2 stays a sum of squares.
+  auto tri_part = [&](int part, int parts, bool lower, double b0, double b1, double b2, double& y0, double& y1,
+                      double& y2) {
+    const double* tab = (lower ? t_Lc : t_Lr) + toff;
+    y0 = 0.0; y1 = 0.0; y2 = 0.0;
+    double t[kU];
+    auto fetch = [&](int j0) {
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int j = j0 + u;
+        t[u] = tab[(j < NF ? j : NF - 1) * NF + li];
+      }
+    };
+    fetch(part * kU);
+    for (int j0 = part * kU; j0 < NF; j0 += parts * kU) {
+      double c[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) c[u] = t[u];
+      fetch(j0 + parts * kU);
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int j = j0 + u;                   // < 64; b is 0 past NF
+        y0 += c[u] * wave::bcast(b0, j);
+        y1 += c[u] * wave::bcast(b1, j);
+        y2 += c[u] * wave::bcast(b2, j);
+      }
+    }
+    const double f = lane < NF ? T15 : 0.0;
+    y0 *= f; y1 *= f; y2 *= f;
+  };
+  // The most violated row outside the working set at the points in Pseg: its
+  // score, key and violation, the same in every lane.  Rows' scaling is 1 /
+  // |alpha|.
+  auto scan_part = [&](int part, int parts, double& best, int& key, double& viol) {
+    best = -1.0;
+    key = 0x7fffffff;
+    viol = 0.0;
+    // row ``id`` with value v, bounds lo and hi, scaling d: a candidate if it
+    // is not in the working set (looked up only for a row that would win)
+    auto consider = [&](int id, double v, double lo, double hi, double d) {
+      const double vu = v - hi, vl = lo - v;
+      const bool up = vu > A.feas_tol * (1.0 + fabs(hi)) && vu * d > best;
+      const bool dn = lo > -1e300 && vl > A.feas_tol * (1.0 + fabs(lo)) && vl * d > (up ? vu * d : best);
+      if (!up && !dn) return;
+      if ((L.actbits[id >> 5] >> (id & 31)) & 1u) return;
+      best = dn ? vl * d : vu * d;
+      viol = dn ? vl : vu;
+      key = 2 * id + (dn ? 0 : 1);
+    };
+    const double minf = -__builtin_huge_val();
+    // faces: one lane per face, its normal in registers while the eight points
+    // pass; two segments at a time, one per half of the wavefront, where no
+    // polytope has more than 32 faces
+    {
+      const int halves = NFC <= 32 ? 2 : 1, lanes = kWave / halves;
+      const int h = halves == 2 ? lane >> 5 : 0, j = lane & (lanes - 1);
+      for (int s1 = part * halves; s1 < S; s1 += parts * halves) {
+        const int s = s1 + h;
+        if (s < S && j < L.nf[s]) {
+          const int nfs = L.nf[s];
+          const double* a = L.Af + (s * NFC + j) * 3;
+          const double a0 = a[0], a1 = a[1], a2 = a[2], hi = L.bfs[s * NFC + j], d = L.fan[s * NFC + j];
+          const double* Pp = L.Pseg + s * NC;
+          const int id0 = L.rowoff[s] + j;
+#pragma unroll
+          for (int k = 0; k < NP; ++k)
+            consider(id0 + k * nfs, a0 * Pp[3 * k] + a1 * Pp[3 * k + 1] + a2 * Pp[3 * k + 2], minf, hi, d);
+        }
+      }
+    }
+    // velocity and acceleration rows: one lane per row of a segment
+    if (lane < 6 * P - 3) {
+      const bool vel = lane < 3 * P;
+      const int e = vel ? lane : lane - 3 * P;              // 3 k + c
+      const double b = vel ? A.vmax : A.amax;
+      const double d = vel ? 1.0 / (sv * 1.4142135623730951) : 1.0 / (sa * 2.449489742783178);
+      for (int s = part; s < S; s += parts) {
+        const double* Pp = L.Pseg + s * NC + e;
+        const double p0 = Pp[0], p1 = Pp[3], p2 = Pp[vel ? 3 : 6];
+        const double v = vel ? sv * (p1 - p0) : sa * (p2 - 2.0 * p1 + p0);
+        consider(L.rowoff[s] + NP * L.nf[s] + lane, v, -b, b, d);
+      }
+    }
+    // reachable rows, whose coefficients come from global memory: two segments
+    // per pass (<= 64 rows together where each has at most 32), the next pass's
+    // rows loaded while this one's are worked on
+    {
+      struct Row { double h[NC], g[6]; };
+      auto rows_of = [&](int s, int& n0, int& n1) {
+        n0 = s < S ? L.rowoff[s + 1] - L.rowoff[s] - (NP * L.nf[s] + 6 * P - 3) : 0;
+        n1 = s + 1 < S ? L.rowoff[s + 2] - L.rowoff[s + 1] - (NP * L.nf[s + 1] + 6 * P - 3) : 0;
+      };
+      auto fetch = [&](int s, int u, Row& w) {
+        int n0, n1;
+        rows_of(s, n0, n1);
+        const bool on = u < n0 + n1;
+        const int sp = !on ? 0 : (u < n0 ? s : s + 1), l = !on ? 0 : (u < n0 ? u : u - n0);
+        const double* H = A.H + L.hb[sp] + (int64_t)l * NC;
+        const double* G = A.G + 6 * (L.r0[sp] + l);
+#pragma unroll
+        for (int e = 0; e < NC; ++e) w.h[e] = on ? H[e] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 6; ++e) w.g[e] = (on && sp > 0) ? G[e] : 0.0;
+      };
+      auto use = [&](int s, int u, const Row& w) {
+        int n0, n1;
+        rows_of(s, n0, n1);
+        if (u >= n0 + n1) return;
+        const int sp = u < n0 ? s : s + 1, l = u < n0 ? u : u - n0;
+        const double* Pp = L.Pseg + sp * NC;
+        double v = 0.0;
+#pragma unroll
+        for (int e = 0; e < NC; ++e) v += w.h[e] * Pp[e];
+        if (sp > 0) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) v += (-w.g[c] + sv * w.g[3 + c]) * Pp[c] - sv * w.g[3 + c] * Pp[3 + c];
+        }
+        consider(L.rowoff[sp] + NP * L.nf[sp] + 6 * P - 3 + l, v, minf, L.rb[sp * RC + l], L.rn[sp * RC + l]);
+      };
+      Row ra, rb_;
+      const int st = 2 * parts;
+      fetch(2 * part, lane, ra);
+      for (int s = 2 * part; s < S; s += 2 * st) {
+        fetch(s + st, lane, rb_);
+        use(s, lane, ra);
+        fetch(s + 2 * st, lane, ra);
+        use(s + st, lane, rb_);
+      }
+      // segments with more than 32 rows: what a pass of 64 lanes left
+      if (RC > 32) {
+        for (int s = 2 * part; s < S; s += st) {
+          int n0, n1;
+          rows_of(s, n0, n1);
+          for (int u = lane + kWave; u < n0 + n1; u += kWave) {
+            fetch(s, u, ra);
+            use(s, u, ra);
+          }
+        }
+      }
+    }
+    // the largest score; among equal ones the lowest row
+    {
+      double bm = best;
+      int km = key;
+      wave::argmax(bm, km);
+      const unsigned long long own = __ballot(best == bm && key == km);
+      best = bm;
+      key = km;
+      viol = wave::bcast(viol, own ? __builtin_ctzll(own) : 0);
+    }
+  };
+  // workgroup's mailbox: job, its results, the right-hand side and partial
+  // products
+  double* const team = reinterpret_cast<double*>(smem + D.o_team);
+  int* const job = reinterpret_cast<int*>(team);
+  double* const found = team + 2;                       // 3 per wavefront
+  double* const rhs_t = team + 2 + 3 * kTeamWaves;      // 3 x 64
+  double* const part_t = rhs_t + 3 * kWave;             // 3 x 64 per helper
+  if constexpr (kTeam) {
+    if (wv > 0) {
+      for (;;) {
+        __syncthreads();                                // a job is posted
+        const int what = *job;
+        if (what == kJobExit) return;
+        if (what == kJobScan) {
+          double b, vi;
+          int k;
+          scan_part(wv, kTeamWaves, b, k, vi);
+          if (lane == 0) { found[3 * wv] = b; found[3 * wv + 1] = double(k); found[3 * wv + 2] = vi; }
+        } else {
+          double y0, y1, y2;
+          tri_part(wv, kTeamWaves, what == kJobLower, rhs_t[lane], rhs_t[kWave + lane], rhs_t[2 * kWave + lane], y0, y1, y2);
+          double* o = part_t + 3 * kWave * (wv - 1);
+          o[lane] = y0; o[kWave + lane] = y1; o[2 * kWave + lane] = y2;
+        }
+        __syncthreads();                                // done
+      }
+    }
+  }
+  auto tri = [&](bool lower, double b0, double b1, double b2, double& y0, double& y1, double& y2) {
+    if constexpr (kTeam) {
+      rhs_t[lane] = b0; rhs_t[kWave + lane] = b1; rhs_t[2 * kWave + lane] = b2;
+      if (lane == 0) *job = lower ? kJobLower : kJobUpper;
+      __syncthreads();
+      tri_part(0, kTeamWaves, lower, b0, b1, b2, y0, y1, y2);
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kTeamWaves - 1; ++w) {
+        const double* o = part_t + 3 * kWave * w;
+        y0 += o[lane]; y1 += o[kWave + lane]; y2 += o[2 * kWave + lane];
+      }
+    } else {
+      tri_part(0, 1, lower, b0, b1, b2, y0, y1, y2);
+    }
+  };
+  auto scan = [&](double& best, int& key, double& viol) {
+    if constexpr (kTeam) {
+      if (lane == 0) *job = kJobScan;
+      __syncthreads();
+      scan_part(0, kTeamWaves, best, key, viol);
+      __syncthreads();
+#pragma unroll
+      for (int w = 1; w < kTeamWaves; ++w) {
+        const double b = found[3 * w], vi = found[3 * w + 2];
+        const int k = int(found[3 * w + 1]);
+        if (b > best || (b == best && k < key)) { best = b; key = k; viol = vi; }
+      }
+    } else {
+      scan_part(0, 1, best, key, viol);
     }
   };
 
@@ -191,15 +432,14 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     L.nr[lane] = int(A.reach_off[sg + 1] - A.reach_off[sg]);
     L.hb[lane] = A.H_off[sg];
   }
-  __syncthreads();
+  sync();
   if (lane == 0) {
     int acc = 0;
     for (int s = 0; s < S; ++s) { L.rowoff[s] = acc; acc += NP * L.nf[s] + 6 * P - 3 + L.nr[s]; }
     L.rowoff[S] = acc;
   }
-  __syncthreads();
+  sync();
   const int m = L.rowoff[S];
-  const int NFC = D.nf_cap, RC = D.r_cap;
   // faces (shifted bound) and reachable rows (shifted bound, 1/|alpha|)
   for (int s = 0; s < S; ++s) {
     const int nf = L.nf[s], nr = L.nr[s];
@@ -334,7 +574,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       else v = xv[3 * (g - 1) + c];
       L.gfull[e] = v;
     }
-    __syncthreads();
+    sync();
     for (int e = lane; e < S * NC; e += kWave) {
       const int s = e / NC, r = e - NC * (e / NC), k = r / 3, c = r - 3 * (r / 3);
       const int ws = (P - 2) * s;
@@ -343,7 +583,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       if (k >= 3) v = L.gfull[3 * (ws + k) + c];
       L.Pseg[e] = v;
     }
-    __syncthreads();
+    sync();
   };
 
   // ---- Hessian G1 (banded, bandwidth P) and its Cholesky factor on the free points
@@ -356,7 +596,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       for (int k2 = 0; k2 < NP; ++k2) v += mcoef(1, k, a) * 2.0 * iT3 * K.Q1[k][k2] * mcoef(1, k2, b);
     L.Wm[NP * NP + e] = v;
   }
-  __syncthreads();
+  sync();
   for (int e = lane; e < NG * (P + 1); e += kWave) {
     const int g = e / (P + 1), d = e - (P + 1) * (e / (P + 1));
     const int h = g - d;
@@ -369,52 +609,17 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     }
     L.G1b[e] = v;
   }
-  __syncthreads();
-  // Products with L^-1 and L^-T (x) I3 from the tables, one lane per free
-  // point, three coordinates per lane.  The banded substitution these replace
-  // walks the points one after the other, four sweeps of up to 61 points per
-  // polish step; a product reads 30 KB from L2 at most but nothing in it waits
-  // for anything else.  L^-1 is applied on its own, as the substitution was, so
-  // that |L^-1 d|^2 stays a sum of squares.
-  const int toff = ((S - 1) * (36 + 6 * 5 * (S - 2)) + 25 * ((S - 2) * (S - 1) * (2 * S - 3) / 6));
-  const int li = lane < NF ? lane : NF - 1;
-  constexpr int kU = 16;                      // rows of a table in flight
-  auto tri = [&](const double* tab, bool lower, double b0, double b1, double b2, double& y0, double& y1, double& y2) {
-    // y_i = sum over j <= i (lower) or j >= i of tab[j NF + i] b_j
-    y0 = 0.0; y1 = 0.0; y2 = 0.0;
-    double t[kU];
-    auto fetch = [&](int j0) {
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int j = j0 + u;
-        t[u] = (j < NF && lane < NF && (lower ? j <= lane : j >= lane)) ? tab[j * NF + li] : 0.0;
-      }
-    };
-    fetch(0);
-    for (int j0 = 0; j0 < NF; j0 += kU) {
-      double c[kU];
-#pragma unroll
-      for (int u = 0; u < kU; ++u) c[u] = t[u];
-      fetch(j0 + kU);
-#pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int j = j0 + u < kWave ? j0 + u : 0;
-        y0 += c[u] * wave::bcast(b0, j);
-        y1 += c[u] * wave::bcast(b1, j);
-        y2 += c[u] * wave::bcast(b2, j);
-      }
-    }
-    y0 *= T15; y1 *= T15; y2 *= T15;
-  };
+  sync();
+  // Products with L^-1 and L^-T (x) I3: tri (above), one lane per free point
   auto gfwd = [&](const double* rhs, double& y0, double& y1, double& y2) {
     const bool on = lane < NF;
-    tri(t_Lc + toff, true, on ? rhs[3 * li] : 0.0, on ? rhs[3 * li + 1] : 0.0, on ? rhs[3 * li + 2] : 0.0, y0, y1, y2);
+    tri(true, on ? rhs[3 * li] : 0.0, on ? rhs[3 * li + 1] : 0.0, on ? rhs[3 * li + 2] : 0.0, y0, y1, y2);
   };
   auto gbwd = [&](double y0, double y1, double y2, double* out) {
     double z0, z1, z2;
-    tri(t_Lr + toff, false, y0, y1, y2, z0, z1, z2);
+    tri(false, y0, y1, y2, z0, z1, z2);
     if (lane < NF) { out[3 * lane] = z0; out[3 * lane + 1] = z1; out[3 * lane + 2] = z2; }
-    __syncthreads();
+    sync();
   };
   auto gsolve = [&](const double* rhs, double* out) {
     double y0, y1, y2;
@@ -427,10 +632,10 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     const int g = i + 1, d = (NG - 1) - g;
     L.qv[e] = (d <= P) ? L.G1b[(NG - 1) * (P + 1) + d] * sel3(c, dg[0], dg[1], dg[2]) : 0.0;
   }
-  __syncthreads();
+  sync();
   gsolve(L.qv, L.xu);
   for (int e = lane; e < n; e += kWave) L.xu[e] = -L.xu[e];
-  __syncthreads();
+  sync();
 
   // ======================================================================
   // FP32 ADMM warm start (banded K in LDS)
@@ -450,7 +655,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       }
       L.Kb[e] = v;
     }
-    __syncthreads();
+    sync();
     for (int s = 0; s < S; ++s) {
       // C_s in control-point space: faces, difference rows, reachable rows (matrix cores)
       const int nf = L.nf[s], nr = L.nr[s];
@@ -484,13 +689,13 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, a, acc, 0, 0, 0);
       }
       for (int e = lane; e < NC * NC; e += kWave) L.Cs[e] = 0.0f;
-      __syncthreads();
+      sync();
 #pragma unroll
       for (int g = 0; g < 16; ++g) {
         const int i = 8 * (g >> 2) + 4 * half + (g & 3);
         if (i < NC && col < NC) L.Cs[i * NC + col] = acc[g];
       }
-      __syncthreads();
+      sync();
       for (int e = lane; e < NC * NC; e += kWave) {
         const int i = e / NC, j = e - NC * (e / NC);
         const int ki = i / 3, ci = i - 3 * ki, kj = j / 3, cj = j - 3 * kj;
@@ -517,7 +722,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
         }
         L.Cs[e] = v;
       }
-      __syncthreads();
+      sync();
       // window transform M^T C M and accumulation into the band (free points only)
       constexpr int EPL = (NC * NC + kWave - 1) / kWave;
       float tv[EPL];
@@ -540,7 +745,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
         }
         tv[ti] = float(v) * rho;
       }
-      __syncthreads();
+      sync();
       const int ws = (P - 2) * s;
 #pragma unroll
       for (int ti = 0; ti < EPL; ++ti) {
@@ -553,25 +758,25 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
           if (vj <= vi) L.Kb[vi * (BW + 1) + (vi - vj)] += tv[ti];
         }
       }
-      __syncthreads();
+      sync();
     }
     // band Cholesky of K (FP32), right-looking
     for (int i = 0; i < n; ++i) {
       const float dd = sqrtf(fmaxf(L.Kb[i * (BW + 1)], 1e-30f));
-      __syncthreads();
+      sync();
       if (lane == 0) L.Kb[i * (BW + 1)] = dd;
       if (lane >= 1 && lane <= BW && i + lane < n) L.Kb[(i + lane) * (BW + 1) + lane] /= dd;
-      __syncthreads();
+      sync();
       for (int t = lane; t < BW * (BW + 1) / 2; t += kWave) {
         int a = 0, rem = t;
         while (rem > a) { rem -= a + 1; ++a; }
         const int kk = i + 1 + a, jj = i + 1 + rem;
         if (kk < n) L.Kb[kk * (BW + 1) + (kk - jj)] -= L.Kb[kk * (BW + 1) + (kk - i)] * L.Kb[jj * (BW + 1) + (jj - i)];
       }
-      __syncthreads();
+      sync();
     }
     for (int e = lane; e < m; e += kWave) { L.zr[e] = 0.0f; L.yr[e] = 0.0f; }
-    __syncthreads();
+    sync();
     for (int it = 0; it < K_admm; ++it) {
       // control-point accumulations sum_rows alpha * d (rho (z - d c) - y)
       for (int e = lane; e < S * NC; e += kWave) {
@@ -604,7 +809,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
         }
         L.accp[e] = t;
       }
-      __syncthreads();
+      sync();
       // right-hand side on the free global points (both windows touching a point)
       for (int e = lane; e < n; e += kWave) {
         const int g = e / 3 + 1, c = e - 3 * (e / 3);
@@ -620,7 +825,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
         }
         L.xt[e] = t;
       }
-      __syncthreads();
+      sync();
       // x~ = K^-1 rhs with the band factor (lane i%64 holds entries i, i+64, i+128, ...)
       {
         constexpr int MAXV = 4;                 // n <= 256
@@ -656,14 +861,14 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
 #pragma unroll
         for (int v = 0; v < MAXV; ++v) { const int i = lane + kWave * v; if (i < n) L.xt[i] = b[v]; }
       }
-      __syncthreads();
+      sync();
       // control points of x~ (FP32) and row update
       for (int e = lane; e < 3 * NG; e += kWave) {
         const int g = e / 3, c = e - 3 * (e / 3);
         double v = g == 0 ? 0.0 : (g == NG - 1 ? sel3(c, dg[0], dg[1], dg[2]) : double(L.xt[3 * (g - 1) + c]));
         L.gfull[e] = v;
       }
-      __syncthreads();
+      sync();
       for (int e = lane; e < S * NC; e += kWave) {
         const int s = e / NC, r = e - NC * (e / NC), k = r / 3, c = r - 3 * (r / 3);
         const int ws = (P - 2) * s;
@@ -672,7 +877,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
         if (k >= 3) v = L.gfull[3 * (ws + k) + c];
         L.Pseg[e] = v;
       }
-      __syncthreads();
+      sync();
       for (int s = 0; s < S; ++s) {
         const int ms = L.rowoff[s + 1] - L.rowoff[s], ro = L.rowoff[s];
         for (int loc = lane; loc < ms; loc += kWave) {
@@ -690,7 +895,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
           L.yr[ro + loc] = y;
         }
       }
-      __syncthreads();
+      sync();
     }
     // proposals: most active first (|y|), at most q_cap of them
     for (int t = 0; t < D.q_cap; ++t) {
@@ -715,10 +920,10 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       if (!(best > 0.0) || key < 0 || (key >> 1) >= m) break;
       if (lane == 0) { L.cand[t] = key; L.yr[key >> 1] = 0.0f; }
       ++ncand;
-      __syncthreads();
+      sync();
     }
   }
-  __syncthreads();
+  sync();
 
   // ======================================================================
   // FP64 dual active-set polish
@@ -767,7 +972,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       L.zv[e] = 0.5 * (lo + hi) - L.xu[e];
       L.w[e] = fmax(0.5 * (hi - lo), 0.0);
     }
-    __syncthreads();
+    sync();
     double cc = 0.0, ww = 0.0;
     for (int e = lane; e < n; e += kWave) {
       cc += L.zv[e] * gmul_at(L.zv, e, false);
@@ -777,10 +982,10 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     ww = wave::sum(ww);
     const double rt = sqrt(fmax(cc, 0.0)) + sqrt(fmax(ww, 0.0));
     Ub = fmin(0.5 * rt * rt, 3.0 * S * A.amax * A.amax * T * (1.0 + 1e-12));
-    __syncthreads();
+    sync();
   }
   for (int e = lane; e < n; e += kWave) L.x[e] = L.xu[e];
-  __syncthreads();
+  sync();
   int q = 0, steps = 0, status = kPolishFailed;
   // Working set of up to QC - 1 <= 127 rows: lane l holds entries l and l + 64
   // of every working-set vector (multipliers, right-hand sides of the Schur
@@ -810,7 +1015,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       if (lane < 9) L.scal[lane] = al;
     }
     if (lane == 0) L.actseg[slot] = s;
-    __syncthreads();
+    sync();
     if (lane < NC) {
       // window coefficients beta = M_s^T alpha (per coordinate; M_s is the
       // identity but for the first three points of a segment past the first)
@@ -827,12 +1032,12 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       const int g = ws + j;
       L.beta[slot * NB + lane] = (g >= 1 && g <= NG - 2) ? double(side) * v : 0.0;
     }
-    __syncthreads();
+    sync();
     for (int e = lane; e < n; e += kWave) {
       const int w = e - 3 * (ws - 1);
       L.np[e] = (w >= 0 && w < NC) ? L.beta[slot * NB + w] : 0.0;
     }
-    __syncthreads();
+    sync();
   };
   // dot of the window normal in slot k with a global vector (whose entries at
   // the pinned points do not exist: any entry stands in, times 0)
@@ -947,7 +1152,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
 #pragma unroll
     for (int t = 0; t < 3; ++t)
       if (lane + kWave * t < n) out[lane + kWave * t] = acc[t];
-    __syncthreads();
+    sync();
   };
   auto set_bit = [&](int id, bool on) {
     if (lane == 0) {
@@ -985,7 +1190,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     }
     set_bit(id, true);
     ++q;
-    __syncthreads();
+    sync();
   };
   // Cholesky delete of index kd: the rows below move up one place, then Givens
   // rotations of the columns (kd, kd+1), (kd+1, kd+2), .. restore the triangle.
@@ -998,10 +1203,10 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     const int s0i = e0 >= kd && e0 < q - 1 ? e0 + 1 : -1, s1i = e1 >= kd && e1 < q - 1 ? e1 + 1 : -1;
     int id0 = 0, sd0 = 0, sg0 = 0, id1 = 0, sd1 = 0, sg1 = 0;
     double ev0 = 0.0, ev1 = 0.0;
-    __syncthreads();
+    sync();
     if (s0i >= 0) { id0 = L.actid[s0i]; sd0 = L.actside[s0i]; sg0 = L.actseg[s0i]; ev0 = L.acte[s0i]; }
     if (s1i >= 0) { id1 = L.actid[s1i]; sd1 = L.actside[s1i]; sg1 = L.actseg[s1i]; ev1 = L.acte[s1i]; }
-    __syncthreads();
+    sync();
     if (s0i >= 0) { L.actid[e0] = id0; L.actside[e0] = sd0; L.actseg[e0] = sg0; L.acte[e0] = ev0; }
     if (s1i >= 0) { L.actid[e1] = id1; L.actside[e1] = sd1; L.actseg[e1] = sg1; L.acte[e1] = ev1; }
     // row k + 1 (columns 0..k+1) becomes row k, whose spare slot takes column
@@ -1034,7 +1239,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       if (e0 >= kd && e0 < q - 1) lam0 = n0;
       if (e1 >= kd && e1 < q - 1) lam1 = up1;
     }
-    __syncthreads();
+    sync();
     // rows kd..q-2 have an entry one past the diagonal
     const bool in0 = e0 >= kd && e0 < q - 1, in1 = e1 >= kd && e1 < q - 1;
     const int r0w = lso(in0 ? e0 : kd), r1w = lso(in1 ? e1 : kd);
@@ -1061,7 +1266,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     --q;
     if (e0 >= q) lam0 = 0.0;
     if (e1 >= q) lam1 = 0.0;
-    __syncthreads();
+    sync();
   };
   // smallest of the entries < q, lowest index on ties
   auto min_entry = [&](double v0, double v1, double& mn, int& kd) {
@@ -1079,7 +1284,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     ncand = A.ws_meta[2 * ch];
     steps = A.ws_meta[2 * ch + 1];
     for (int t = lane; t < ncand; t += kWave) L.cand[t] = A.ws_keys[(int64_t)ch * A.ws_stride + t];
-    __syncthreads();
+    sync();
   }
   // ---- warm start from the ADMM proposals (or the stored working set)
   for (int t = 0; t < ncand && q < QC - 1; ++t) {
@@ -1124,7 +1329,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     }
     gsolve(L.w, L.zv);
     for (int e = lane; e < n; e += kWave) L.x[e] = L.xu[e] - L.zv[e];
-    __syncthreads();
+    sync();
   }
   // FP64 check of the dual bound for multipliers lp >= 0 on the entering
   // row (normal in np) and max(lam, 0) on the working set: every feasible
@@ -1141,7 +1346,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       mbabs += fabs(t);
     }
     for (int e = lane; e < n; e += kWave) L.zv[e] = lp * L.np[e] + L.w[e];
-    __syncthreads();
+    sync();
     double f0, f1, f2;
     gfwd(L.zv, f0, f1, f2);
     const double rgr = wave::sum(lane < NF ? f0 * f0 + f1 * f1 + f2 * f2 : 0.0);
@@ -1149,7 +1354,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     for (int e = lane; e < n; e += kWave) rxu += L.zv[e] * L.xu[e];
     rxu = wave::sum(rxu);
     const double D = rxu - 0.5 * rgr - mb;
-    __syncthreads();
+    sync();
     return D > Ub + 1e-9 * (fabs(rxu) + 0.5 * rgr + mbabs + Ub) + 1e-12;
   };
   int bound_tries = 0;
@@ -1158,121 +1363,9 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
   bool infeasible = false;
   while (true) {
     build_points(L.x);
-    double best = -1.0;
-    int key = 0x7fffffff;
-    double viol = 0.0;
-    // row ``id`` with value v, bounds lo and hi, scaling d: a candidate if it
-    // is not in the working set (looked up only for a row that would win)
-    auto consider = [&](int id, double v, double lo, double hi, double d) {
-      const double vu = v - hi, vl = lo - v;
-      const bool up = vu > ftol * (1.0 + fabs(hi)) && vu * d > best;
-      const bool dn = lo > -1e300 && vl > ftol * (1.0 + fabs(lo)) && vl * d > (up ? vu * d : best);
-      if (!up && !dn) return;
-      if ((L.actbits[id >> 5] >> (id & 31)) & 1u) return;
-      best = dn ? vl * d : vu * d;
-      viol = dn ? vl : vu;
-      key = 2 * id + (dn ? 0 : 1);
-    };
-    const double minf = -__builtin_huge_val();
-    // faces: one lane per face, its normal in registers while the eight points
-    // pass; two segments at a time, one per half of the wavefront, where no
-    // polytope has more than 32 faces
-    {
-      const int halves = NFC <= 32 ? 2 : 1, lanes = kWave / halves;
-      const int h = halves == 2 ? lane >> 5 : 0, j = lane & (lanes - 1);
-      for (int s1 = 0; s1 < S; s1 += halves) {
-        const int s = s1 + h;
-        if (s < S && j < L.nf[s]) {
-          const int nfs = L.nf[s];
-          const double* a = L.Af + (s * NFC + j) * 3;
-          const double a0 = a[0], a1 = a[1], a2 = a[2], hi = L.bfs[s * NFC + j], d = L.fan[s * NFC + j];
-          const double* Pp = L.Pseg + s * NC;
-          const int id0 = L.rowoff[s] + j;
-#pragma unroll
-          for (int k = 0; k < NP; ++k)
-            consider(id0 + k * nfs, a0 * Pp[3 * k] + a1 * Pp[3 * k + 1] + a2 * Pp[3 * k + 2], minf, hi, d);
-        }
-      }
-    }
-    // velocity and acceleration rows: one lane per row of a segment
-    if (lane < 6 * P - 3) {
-      const bool vel = lane < 3 * P;
-      const int e = vel ? lane : lane - 3 * P;              // 3 k + c
-      const double b = vel ? A.vmax : A.amax;
-      const double d = vel ? 1.0 / (sv * 1.4142135623730951) : 1.0 / (sa * 2.449489742783178);
-      for (int s = 0; s < S; ++s) {
-        const double* Pp = L.Pseg + s * NC + e;
-        const double p0 = Pp[0], p1 = Pp[3], p2 = Pp[vel ? 3 : 6];
-        const double v = vel ? sv * (p1 - p0) : sa * (p2 - 2.0 * p1 + p0);
-        consider(L.rowoff[s] + NP * L.nf[s] + lane, v, -b, b, d);
-      }
-    }
-    // reachable rows, whose coefficients come from global memory: two segments
-    // per pass (<= 64 rows together where each has at most 32), the next pass's
-    // rows loaded while this one's are worked on
-    {
-      struct Row { double h[NC], g[6]; };
-      auto rows_of = [&](int s, int& n0, int& n1) {
-        n0 = s < S ? L.rowoff[s + 1] - L.rowoff[s] - (NP * L.nf[s] + 6 * P - 3) : 0;
-        n1 = s + 1 < S ? L.rowoff[s + 2] - L.rowoff[s + 1] - (NP * L.nf[s + 1] + 6 * P - 3) : 0;
-      };
-      auto fetch = [&](int s, int u, Row& w) {
-        int n0, n1;
-        rows_of(s, n0, n1);
-        const bool on = u < n0 + n1;
-        const int sp = !on ? 0 : (u < n0 ? s : s + 1), l = !on ? 0 : (u < n0 ? u : u - n0);
-        const double* H = A.H + L.hb[sp] + (int64_t)l * NC;
-        const double* G = A.G + 6 * (L.r0[sp] + l);
-#pragma unroll
-        for (int e = 0; e < NC; ++e) w.h[e] = on ? H[e] : 0.0;
-#pragma unroll
-        for (int e = 0; e < 6; ++e) w.g[e] = (on && sp > 0) ? G[e] : 0.0;
-      };
-      auto use = [&](int s, int u, const Row& w) {
-        int n0, n1;
-        rows_of(s, n0, n1);
-        if (u >= n0 + n1) return;
-        const int sp = u < n0 ? s : s + 1, l = u < n0 ? u : u - n0;
-        const double* Pp = L.Pseg + sp * NC;
-        double v = 0.0;
-#pragma unroll
-        for (int e = 0; e < NC; ++e) v += w.h[e] * Pp[e];
-        if (sp > 0) {
-#pragma unroll
-          for (int c = 0; c < 3; ++c) v += (-w.g[c] + sv * w.g[3 + c]) * Pp[c] - sv * w.g[3 + c] * Pp[3 + c];
-        }
-        consider(L.rowoff[sp] + NP * L.nf[sp] + 6 * P - 3 + l, v, minf, L.rb[sp * RC + l], L.rn[sp * RC + l]);
-      };
-      Row ra, rb_;
-      fetch(0, lane, ra);
-      for (int s = 0; s < S; s += 4) {
-        fetch(s + 2, lane, rb_);
-        use(s, lane, ra);
-        fetch(s + 4, lane, ra);
-        use(s + 2, lane, rb_);
-      }
-      // segments with more than 32 rows: what a pass of 64 lanes left
-      if (RC > 32) {
-        for (int s = 0; s < S; s += 2) {
-          int n0, n1;
-          rows_of(s, n0, n1);
-          for (int u = lane + kWave; u < n0 + n1; u += kWave) {
-            fetch(s, u, ra);
-            use(s, u, ra);
-          }
-        }
-      }
-    }
-    // the largest score; among equal ones the lowest row
-    {
-      double bm = best;
-      int km = key;
-      wave::argmax(bm, km);
-      const unsigned long long own = __ballot(best == bm && key == km);
-      best = bm;
-      key = km;
-      viol = wave::bcast(viol, own ? __builtin_ctzll(own) : 0);
-    }
+    double best, viol;
+    int key;
+    scan(best, key, viol);
     if (!(best > 0.0)) { status = kSolved; break; }
     if (q >= QC - 1 && QC < A.q_full) {
       for (int k = lane; k < q; k += kWave)
@@ -1304,7 +1397,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       // d = n+ - N r; z = G^-1 d and zz = d^T G^-1 d = |L^-1 d|^2, a sum of
       // squares that is small exactly when n+ lies in the span of N
       for (int e = lane; e < n; e += kWave) L.zv[e] = L.np[e] - L.w[e];
-      __syncthreads();
+      sync();
       double f0, f1, f2;
       gfwd(L.zv, f0, f1, f2);
       const double zz = wave::sum(lane < NF ? f0 * f0 + f1 * f1 + f2 * f2 : 0.0);
@@ -1356,7 +1449,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       if (e1 < q) lam1 -= t * r1;
       lamp += t;
       if (zfull) splus -= t * zz;
-      __syncthreads();
+      sync();
       // the dual value passed the box bound: try the FP64 certificate
       if (bound_tries < 4 && dual > Ub * (1.0 + 1e-9) + 1e-12) {
         ++bound_tries;
@@ -1455,13 +1548,36 @@ __global__ __launch_bounds__(64) void chain_kernel(ChainArgs A) {
   if (b >= A.N) return;
   const int ch = A.order ? A.order[b] : b;
   if (A.retry_only && A.status_out[ch] != kRetry) return;
-  chain_instance<P>(A, ch, smem);
+  chain_instance<P, false>(A, ch, smem);
+}
+
+// The full-cap pass: LDS (92-132 KB) allows one path per CU, so three of the
+// CU's SIMDs idle with one wavefront per path, and the pass ends with its
+// slowest path.  1,024 paths of 4-12
+// segments: 8.57 ms with one wavefront per path in this pass, 6.83 ms with four.
+template <int P>
+__global__ __launch_bounds__(64 * kTeamWaves) void chain_team_kernel(ChainArgs A) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int b = blockIdx.x + A.inst_base;
+  if (b >= A.N) return;
+  const int ch = A.order ? A.order[b] : b;
+  const bool mine = !A.retry_only || A.status_out[ch] == kRetry;
+  __syncthreads();   // every wavefront has read the status before the first overwrites it
+  if (!mine) return;
+  chain_instance<P, true>(A, ch, smem);
+  // helpers leave chain_instance at this job; the first wavefront posts it
+  // wherever it left the method
+  if (threadIdx.x < kWave) {
+    if (threadIdx.x == 0) *reinterpret_cast<int*>(smem + A.dims.o_team) = kJobExit;
+    __syncthreads();
+  }
 }
 
 }  // namespace
 
-ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bool admm) {
+ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bool admm, bool team) {
   ChainDims d{};
+  d.team = team ? 1 : 0;
   d.s_cap = s_cap < 1 ? 1 : s_cap;
   d.nf_cap = nf_cap < 1 ? 1 : nf_cap;
   d.r_cap = r_cap < 1 ? 1 : r_cap;
@@ -1513,6 +1629,8 @@ ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bo
   // polish only: nothing of the ADMM part but the window Hessians is used
   if (!admm) a = setup_end;
   d.bytes = a > b ? a : b;
+  d.o_team = d.bytes;
+  if (team) d.bytes += (2 + 3 * kTeamWaves + 3 * kWave * kTeamWaves) * 8;
   return d;
 }
 
@@ -1585,7 +1703,10 @@ hipError_t upload_chain_constants(int device) {
 hipError_t launch_chains(const ChainArgs& a, hipStream_t s) {
   if (a.N - a.inst_base <= 0) return hipSuccess;
   if (a.P != 7) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((chain_kernel<7>), dim3(a.N - a.inst_base), dim3(kWave), a.dims.bytes, s, a);
+  if (a.dims.team)
+    hipLaunchKernelGGL((chain_team_kernel<7>), dim3(a.N - a.inst_base), dim3(kWave * kTeamWaves), a.dims.bytes, s, a);
+  else
+    hipLaunchKernelGGL((chain_kernel<7>), dim3(a.N - a.inst_base), dim3(kWave), a.dims.bytes, s, a);
   return hipGetLastError();
 }
 

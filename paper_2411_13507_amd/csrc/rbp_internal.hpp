@@ -131,6 +131,7 @@ struct BackArgs {
 // ---- multi-segment paths (rbp_chain.hip)
 struct ChainDims {
   int s_cap, nf_cap, r_cap, q_cap, nf_pts_cap, ng_cap, n_cap, m_cap;
+  int team, o_team;   // 1: four wavefronts per path; their mailbox
   int o_segi, o_seg64, o_Af, o_bfs, o_fan, o_rb, o_rn, o_Pseg, o_gfull, o_G1b, o_qv, o_x, o_scal,
       o_cand, o_bits;
   int o_Kb, o_zr, o_yr, o_accp, o_Pf, o_xt, o_Cs, o_Wm;          // ADMM part of the region
@@ -282,7 +283,8 @@ hipError_t launch_mpc(const MpcArgs& a, hipStream_t s);
 LdsDims make_dims(int pmax, int r_cap, int nf_cap, int real_bytes, bool admm);
 // LDS of the backward pass alone (its own, smaller carve: more waves resident)
 LdsDims make_back_dims(int pmax, int nf_cap);
-ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bool admm);
+// team: room for the four-wavefront kernel's mailbox, which launch_chains then picks
+ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bool admm, bool team);
 hipError_t upload_chain_constants(int device);
 hipError_t launch_chains(const ChainArgs& a, hipStream_t s);
 hipError_t upload_constants(int device);
