@@ -504,6 +504,7 @@ struct rbp_chains {
   int device = 0;
   rbp_chain_desc desc{};
   int32_t N = 0, s_max = 1, nf_max = 1, r_max = 0;
+  int n_cu = 1;
   int64_t pt_total = 0;
   int32_t* d_order = nullptr;
   int32_t* ws_keys = nullptr;   // working set of each path at its first-pass overflow
@@ -538,8 +539,16 @@ int ensure_chain_constants(int device) {
 // with n free variables never holds more than n; the polish stops when q
 // reaches the capacity minus one, hence n + 2 for short paths.
 // working-set rows of the first path pass: at 12 segments of degree 7 its LDS
-// (about 50 KB) leaves three paths resident per CU, against one at the full cap
+// (46 KB, polish only) leaves three paths resident per CU, against one at the full cap
 constexpr int kChainFirstPassRows = 32;
+// Batches of up to this many paths per CU are solved in one pass by the
+// four-wavefront kernel at the full cap: a CU works through its few paths one
+// after the other, each much faster, and no path waits for the first pass of
+// the others.  With two passes / one pass, polish only: 256 paths 5.3 / 3.2 ms,
+// 512 5.3 / 3.6, 1,024 5.6 / 4.3, 2,048 6.1 / 6.5, 8,192 12.4 / 17.8.  The
+// ADMM warm start runs on one wavefront in either, so with it the line is one
+// path per CU: 256 paths 8.8 / 6.9 ms, 512 8.9 / 10.5, 1,024 13.8 / 17.3.
+constexpr int kChainTeamPathsPerCu = 4;
 
 void free_chains(rbp_chains* c) {
   for (int k = 0; k < rbp_chains::kLanes - 1; ++k) {
@@ -611,6 +620,7 @@ int rbp_build_chains(const rbp_chain_desc* d, hipStream_t stream, rbp_chains** o
   c->device = dev;
   c->desc = *d;
   c->N = N;
+  if (hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || c->n_cu < 1) c->n_cu = 1;
   const int p = d->degree;
   std::vector<int32_t> order(N);
   if (N > 0) {
@@ -735,8 +745,8 @@ int rbp_solve_chains(rbp_chains* c, const double* x0, const double* goal, const 
     const rbp_chains::Group& g = c->groups[k];
     const int l = fork ? c->group_lane[k] : 0;
     const hipStream_t gs = l == 0 ? stream : c->side[l - 1];
-    // a first pass with a small working-set cap keeps LDS per path low (more
-    // paths resident per CU); the few paths whose working set outgrows it are
+    // larger batches: a first pass with a small working-set cap keeps LDS per path
+    // low (more paths resident per CU); the few paths whose working set outgrows it are
     // finished by a full-cap pass, which continues from the working set the
     // first pass held and skips every other path
     const int q_full = chain_q_cap(d.degree, g.s_max);
@@ -746,14 +756,20 @@ int rbp_solve_chains(rbp_chains* c, const double* x0, const double* goal, const 
     a.N = g.start + g.count;
     a.q_full = q_full;
     a.retry_only = 0;
+    // the four-wavefront kernel, unless its mailbox (6 KB) passes the LDS
+    rbp::ChainDims full = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_full, admm, true);
+    const bool team = size_t(full.bytes) <= kLdsBytes;
+    if (!team) full = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_full, admm, false);
+    if (team && c->N <= (admm ? 1 : kChainTeamPathsPerCu) * c->n_cu) {
+      a.dims = full;
+      e = rbp::launch_chains(a, gs);
+      continue;
+    }
     a.dims = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_first, admm, false);
     e = rbp::launch_chains(a, gs);
     if (e == hipSuccess && q_first < q_full) {
       a.retry_only = 1;
-      a.dims = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_full, admm, true);
-      // the four-wavefront kernel's mailbox takes 6 KB more LDS
-      if (size_t(a.dims.bytes) > kLdsBytes)
-        a.dims = rbp::make_chain_dims(d.degree, g.s_max, g.nf_max, g.r_max, q_full, admm, false);
+      a.dims = full;
       e = rbp::launch_chains(a, gs);
     }
   }

@@ -1551,10 +1551,11 @@ __global__ __launch_bounds__(64) void chain_kernel(ChainArgs A) {
   chain_instance<P, false>(A, ch, smem);
 }
 
-// The full-cap pass: LDS (92-132 KB) allows one path per CU, so three of the
-// CU's SIMDs idle with one wavefront per path, and the pass ends with its
-// slowest path.  1,024 paths of 4-12
-// segments: 8.57 ms with one wavefront per path in this pass, 6.83 ms with four.
+// The full-cap pass, and small batches whole: LDS (66-138 KB) and registers
+// allow one path per CU or two, so with one wavefront per path the CU's SIMDs
+// idle, and a launch ends with its slowest path.  1,024 paths of 4-12 segments,
+// polish only: 8.57 ms with one wavefront per path in the full-cap pass, 6.83 ms
+// with four.
 template <int P>
 __global__ __launch_bounds__(64 * kTeamWaves) void chain_team_kernel(ChainArgs A) {
   extern __shared__ __attribute__((aligned(16))) char smem[];

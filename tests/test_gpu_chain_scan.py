@@ -3,7 +3,7 @@
 one, two, three and twelve segments, polytopes with more than 32 faces, no, more
 than 32 and more than 64 reachable rows per segment, another duration, and the
 largest LDS footprint, against the FP64 oracle at the tolerances of the other path
-tests.  Each batch is solved as it is and tiled to more paths than a launch takes
+tests.  Each batch is solved as it is and tiled to more paths than are taken
 with four wavefronts from the start: copies must agree bit for bit."""
 import dataclasses
 
@@ -73,7 +73,7 @@ def test_chain_edges(gpu_available, name, admm):
     print(f"case: {name}, {b.n} paths, admm_iters {admm}", flush=True)
     _, out = gpu_chains(b, _opts(admm))
     compare_chains(b, out, list(range(b.n)), name)
-    copies = 288 // b.n                            # more paths in one group than the chip has CUs
+    copies = 1152 // b.n                           # more than four paths per CU
     _, big = gpu_chains(gen.concat_chains([b] * copies), _opts(admm))
     for k in ("status", "cost"):
         t = big[k].reshape(copies, -1)
