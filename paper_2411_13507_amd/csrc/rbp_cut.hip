@@ -185,120 +185,105 @@ __global__ __launch_bounds__(kCutBlock) void cut_prefilter_kernel(CutArgs A) {
     if (base + i < (unsigned long long)A.list_cap) A.list[base + i] = near[i];
 }
 
-// Closest point to the origin of the face of the simplex {w0..w3} selected
-// by MASK (bits = vertices): the affine projection, accepted when its
-// barycentric weights are all positive.  Every index is a compile-time
-// constant, so the simplex stays in registers.
-template <int MASK>
-__device__ __forceinline__ bool face_point(const V3 (&w)[4], V3& x) {
-  constexpr int S = __builtin_popcount(MASK);
-  constexpr int I0 = (MASK & 1) ? 0 : (MASK & 2) ? 1 : (MASK & 4) ? 2 : 3;
-  const V3 w0 = w[I0];
-  if constexpr (S == 1) {
-    x = w0;
-    return true;
-  } else {
-    // the other vertices of the face, in increasing order
-    V3 d[3];
-    int m = 0;
+// Weights of the projection of the origin onto the line / plane through w0 and
+// w0 + d_a (, w0 + d_b), from their Gram matrix g and r = -d . w0; false where
+// the face is degenerate or a weight is negative.
+__device__ __forceinline__ bool edge_weight(double g, double r, double& t) {
+  if (!(g > 1e-30 * fmax(g, 1e-300))) return false;
+  t = r / g;
+  return (t > -1e-14) & (1.0 - t > -1e-14);
+}
+__device__ __forceinline__ bool tri_weights(double gaa, double gab, double gbb, double ra, double rb, double& ta,
+                                            double& tb) {
+  const double scale = fmax(gaa, gbb), det = gaa * gbb - gab * gab;
+  if (!(fabs(det) > 1e-24 * scale * scale)) return false;
+  const double inv = 1.0 / det;
+  ta = (ra * gbb - gab * rb) * inv;
+  tb = (gaa * rb - ra * gab) * inv;
+  return (ta > -1e-14) & (tb > -1e-14) & (1.0 - ta - tb > -1e-14);
+}
+
+// Closest point to the origin of conv(w[0..k)), k <= 4, where w[0] is the
+// point added last: the nearest accepted projection over the faces that hold
+// w[0].  The closest point of conv(w[1..k)) is known and w[0] lies beyond the
+// plane through it, so no other face can hold the new one: 7 faces instead of
+// 15, all with the same base point, whose differences and Gram matrix are
+// formed once.  On return w[0..k) holds the face found.
+__device__ __forceinline__ void closest_face(V3 (&w)[4], int& k, V3& v) {
+  const V3 w0 = w[0];
+  V3 d[3];
+  double G[3][3], r[3];
 #pragma unroll
-    for (int i = I0 + 1; i < 4; ++i)
-      if (MASK & (1 << i)) d[m++] = sub(w[i], w0);
-    // minimise |w0 + sum_j t_j d_j|^2: Gram system G t = -D^T w0
-    double G[3][3], rhs[3], t[3] = {0.0, 0.0, 0.0};
+  for (int a = 0; a < 3; ++a) { d[a] = sub(w[a + 1], w0); r[a] = -dot(d[a], w0); }
 #pragma unroll
-    for (int a = 0; a < S - 1; ++a) {
-      rhs[a] = -dot(d[a], w0);
+  for (int a = 0; a < 3; ++a)
 #pragma unroll
-      for (int c = 0; c < S - 1; ++c) G[a][c] = dot(d[a], d[c]);
+    for (int b = a; b < 3; ++b) { G[a][b] = dot(d[a], d[b]); G[b][a] = G[a][b]; }
+  double best = dot(w0, w0);
+  int bm = 0;               // bit a: d[a] spans the face
+  v = w0;
+  auto offer = [&](bool ok, int mask, V3 x) {
+    const double xx = dot(x, x);
+    if (ok && xx < best) { best = xx; bm = mask; v = x; }
+  };
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    if (k > a + 1) {
+      double t = 0.0;
+      const bool ok = edge_weight(G[a][a], r[a], t);
+      offer(ok, 1 << a, axpy(t, d[a], w0));
     }
-    double scale = 0.0;
 #pragma unroll
-    for (int a = 0; a < S - 1; ++a) scale = fmax(scale, G[a][a]);
-    if constexpr (S == 2) {
-      if (!(G[0][0] > 1e-30 * fmax(scale, 1e-300))) return false;
-      t[0] = rhs[0] / G[0][0];
-    } else if constexpr (S == 3) {
-      const double det = G[0][0] * G[1][1] - G[0][1] * G[1][0];
-      if (!(fabs(det) > 1e-24 * scale * scale)) return false;
-      t[0] = (rhs[0] * G[1][1] - G[0][1] * rhs[1]) / det;
-      t[1] = (G[0][0] * rhs[1] - rhs[0] * G[1][0]) / det;
-    } else {
-      const double det = G[0][0] * (G[1][1] * G[2][2] - G[1][2] * G[2][1]) -
-                         G[0][1] * (G[1][0] * G[2][2] - G[1][2] * G[2][0]) +
-                         G[0][2] * (G[1][0] * G[2][1] - G[1][1] * G[2][0]);
-      if (!(fabs(det) > 1e-24 * scale * scale * scale)) return false;
-      // Cramer's rule, column c of G replaced by rhs
+  for (int b = 1; b < 3; ++b)
+    if (k > b + 1) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        double M[3][3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-          for (int b = 0; b < 3; ++b) M[a][b] = (b == c) ? rhs[a] : G[a][b];
-        t[c] = (M[0][0] * (M[1][1] * M[2][2] - M[1][2] * M[2][1]) - M[0][1] * (M[1][0] * M[2][2] - M[1][2] * M[2][0]) +
-                M[0][2] * (M[1][0] * M[2][1] - M[1][1] * M[2][0])) / det;
+      for (int a = 0; a < b; ++a) {
+        double ta = 0.0, tb = 0.0;
+        const bool ok = tri_weights(G[a][a], G[a][b], G[b][b], r[a], r[b], ta, tb);
+        offer(ok, (1 << a) | (1 << b), axpy(tb, d[b], axpy(ta, d[a], w0)));
       }
     }
-    double t0 = 1.0;
-    bool ok = true;
-#pragma unroll
-    for (int j = 0; j < S - 1; ++j) {
-      t0 -= t[j];
-      ok &= t[j] > -1e-14;
+  if (k > 3) {
+    const double c00 = G[1][1] * G[2][2] - G[1][2] * G[1][2], c01 = G[0][2] * G[1][2] - G[0][1] * G[2][2],
+                 c02 = G[0][1] * G[1][2] - G[0][2] * G[1][1], c11 = G[0][0] * G[2][2] - G[0][2] * G[0][2],
+                 c12 = G[0][1] * G[0][2] - G[0][0] * G[1][2], c22 = G[0][0] * G[1][1] - G[0][1] * G[0][1];
+    const double det = G[0][0] * c00 + G[0][1] * c01 + G[0][2] * c02;
+    const double scale = fmax(G[0][0], fmax(G[1][1], G[2][2]));
+    if (fabs(det) > 1e-24 * scale * scale * scale) {
+      const double inv = 1.0 / det;
+      const double t0 = (c00 * r[0] + c01 * r[1] + c02 * r[2]) * inv, t1 = (c01 * r[0] + c11 * r[1] + c12 * r[2]) * inv,
+                   t2 = (c02 * r[0] + c12 * r[1] + c22 * r[2]) * inv;
+      const bool ok = (t0 > -1e-14) & (t1 > -1e-14) & (t2 > -1e-14) & (1.0 - t0 - t1 - t2 > -1e-14);
+      offer(ok, 7, axpy(t2, d[2], axpy(t1, d[1], axpy(t0, d[0], w0))));
     }
-    if (!(ok && t0 > -1e-14)) return false;
-    x = w0;
-#pragma unroll
-    for (int j = 0; j < S - 1; ++j) x = axpy(t[j], d[j], x);
-    return true;
   }
+  // keep the face's points, in order
+  const V3 w1 = w[1], w2 = w[2], w3 = w[3];
+  w[1] = (bm & 1) ? w1 : (bm & 2) ? w2 : w3;
+  w[2] = (bm & 3) == 3 ? w2 : w3;
+  k = 1 + __builtin_popcount(bm);
 }
 
-template <int MASK>
-__device__ __forceinline__ void try_face(const V3 (&w)[4], int k, double& best, int& best_mask, V3& best_v) {
-  if (MASK >= (1 << k)) return;
-  V3 x;
-  if (!face_point<MASK>(w, x)) return;
-  const double xx = dot(x, x);
-  if (xx < best) { best = xx; best_mask = MASK; best_v = x; }
-}
-
-// keep the vertices of face MASK, in order, as the new simplex
-template <int MASK>
-__device__ __forceinline__ void keep_face(V3 (&w)[4], int& k) {
-  V3 nw[4] = {w[0], w[0], w[0], w[0]};
-  int s = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (MASK & (1 << i)) nw[s++] = w[i];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) w[i] = nw[i];
-  k = __builtin_popcount(MASK);
-}
-
-// Closest point to the origin of conv(w[0..k)), k <= 4: the nearest accepted
-// face projection over every face.  On return w[0..k) holds that face.
-// Returns false when no face qualified (degenerate input).
-__device__ bool closest_face(V3 (&w)[4], int& k, V3& v) {
-  double best = __builtin_huge_val();
-  int bm = 0;
+// The first of the points v0..v1-1 of pv that maximises u . p, and the maximum;
+// four points in flight (a lane's loads hit L2, one after the other they are
+// most of a support call).
+__device__ __forceinline__ V3 farthest(const double* pv, int v0, int v1, V3 u, double& best) {
   V3 bv{0.0, 0.0, 0.0};
-  try_face<1>(w, k, best, bm, bv);  try_face<2>(w, k, best, bm, bv);  try_face<3>(w, k, best, bm, bv);
-  try_face<4>(w, k, best, bm, bv);  try_face<5>(w, k, best, bm, bv);  try_face<6>(w, k, best, bm, bv);
-  try_face<7>(w, k, best, bm, bv);  try_face<8>(w, k, best, bm, bv);  try_face<9>(w, k, best, bm, bv);
-  try_face<10>(w, k, best, bm, bv); try_face<11>(w, k, best, bm, bv); try_face<12>(w, k, best, bm, bv);
-  try_face<13>(w, k, best, bm, bv); try_face<14>(w, k, best, bm, bv); try_face<15>(w, k, best, bm, bv);
-  switch (bm) {
-    case 1: keep_face<1>(w, k); break;   case 2: keep_face<2>(w, k); break;   case 3: keep_face<3>(w, k); break;
-    case 4: keep_face<4>(w, k); break;   case 5: keep_face<5>(w, k); break;   case 6: keep_face<6>(w, k); break;
-    case 7: keep_face<7>(w, k); break;   case 8: keep_face<8>(w, k); break;   case 9: keep_face<9>(w, k); break;
-    case 10: keep_face<10>(w, k); break; case 11: keep_face<11>(w, k); break; case 12: keep_face<12>(w, k); break;
-    case 13: keep_face<13>(w, k); break; case 14: keep_face<14>(w, k); break; case 15: keep_face<15>(w, k); break;
-    default: return false;
+  best = 0.0;
+  for (int q = v0; q < v1; q += 4) {
+    V3 p[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int64_t qi = 3 * (int64_t)(q + i < v1 ? q + i : v1 - 1);
+      p[i] = {pv[qi], pv[qi + 1], pv[qi + 2]};
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const double d = dot(u, p[i]);
+      if ((q == v0 && i == 0) || d > best) { best = d; bv = p[i]; }
+    }
   }
-  v = bv;
-  return true;
+  return bv;
 }
 
 // Squared distance from the origin to a convex set given by its support
@@ -320,13 +305,13 @@ __device__ double gjk_dist2(Support support, V3 w0, double zero2, V3& v) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) dup |= (i < k) & (w[i].x == wn.x) & (w[i].y == wn.y) & (w[i].z == wn.z);
     if (dup) break;
-    // append at slot k (fixed slots keep the simplex in registers)
-    if (k == 1) w[1] = wn;
-    else if (k == 2) w[2] = wn;
-    else w[3] = wn;
+    w[3] = w[2];
+    w[2] = w[1];
+    w[1] = w[0];
+    w[0] = wn;
     ++k;
     V3 nv;
-    if (!closest_face(w, k, nv)) break;
+    closest_face(w, k, nv);
     const double nvv = dot(nv, nv);
     if (!(nvv < vv)) break;   // no progress: v is optimal to rounding
     v = nv;
@@ -650,11 +635,19 @@ __global__ __launch_bounds__(kWave) void cut_qp_kernel(CutArgs A) {
       // violates some row)
       const int r0 = A.pob_off[j], r1 = A.pob_off[j + 1];
       unsigned outside = 0u;
-      for (int r = r0; r < r1; ++r) {
-        const V3 a{A.pob_A[3 * r], A.pob_A[3 * r + 1], A.pob_A[3 * r + 2]};
-        const double bb = A.pob_b[r];
+      for (int r = r0; r < r1; r += 4) {
+        V3 a[4];
+        double bb[4];
 #pragma unroll
-        for (int k = 0; k < NP; ++k) outside |= (dot(a, pts[k]) > bb ? 1u : 0u) << k;
+        for (int i = 0; i < 4; ++i) {          // the last row again past the end
+          const int ri = r + i < r1 ? r + i : r1 - 1;
+          a[i] = {A.pob_A[3 * ri], A.pob_A[3 * ri + 1], A.pob_A[3 * ri + 2]};
+          bb[i] = A.pob_b[ri];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int k = 0; k < NP; ++k) outside |= (dot(a[i], pts[k]) > bb[i] ? 1u : 0u) << k;
       }
       inside = outside != (1u << NP) - 1u;
       if (!inside) {
@@ -663,14 +656,7 @@ __global__ __launch_bounds__(kWave) void cut_qp_kernel(CutArgs A) {
         // normal m = c - that point; offset = max over the vertices of m . v
         const int v0 = A.pv_off[j], v1 = A.pv_off[j + 1];
         auto vmax = [&](V3 u, double& best) -> V3 {
-          V3 bv{A.pv[3 * v0], A.pv[3 * v0 + 1], A.pv[3 * v0 + 2]};
-          best = dot(u, bv);
-          for (int q = v0 + 1; q < v1; ++q) {
-            const V3 vq{A.pv[3 * q], A.pv[3 * q + 1], A.pv[3 * q + 2]};
-            const double d = dot(u, vq);
-            if (d > best) { best = d; bv = vq; }
-          }
-          return bv;
+          return farthest(A.pv, v0, v1, u, best);
         };
         auto support = [&](V3 u) -> V3 { double bd; return sub(c, vmax(u, bd)); };
         V3 m;
@@ -729,14 +715,8 @@ __global__ __launch_bounds__(kWave) void cut_qp_kernel(CutArgs A) {
           const double d = dot(u, pts[k]);
           if (d < bd) { bd = d; bp = pts[k]; }
         }
-        V3 bv{A.pv[3 * v0], A.pv[3 * v0 + 1], A.pv[3 * v0 + 2]};
-        double best = dot(u, bv);
-        for (int q2 = v0 + 1; q2 < v1; ++q2) {
-          const V3 vq{A.pv[3 * q2], A.pv[3 * q2 + 1], A.pv[3 * q2 + 2]};
-          const double d = dot(u, vq);
-          if (d > best) { best = d; bv = vq; }
-        }
-        return sub(bp, bv);
+        double best;
+        return sub(bp, farthest(A.pv, v0, v1, u, best));
       };
       V3 v;
       d2 = gjk_dist2(support, sub(pts[0], V3{A.pv[3 * v0], A.pv[3 * v0 + 1], A.pv[3 * v0 + 2]}), zero2, v);
