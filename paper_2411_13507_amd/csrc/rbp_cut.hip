@@ -185,22 +185,11 @@ __global__ __launch_bounds__(kCutBlock) void cut_prefilter_kernel(CutArgs A) {
     if (base + i < (unsigned long long)A.list_cap) A.list[base + i] = near[i];
 }
 
-// Weights of the projection of the origin onto the line / plane through w0 and
-// w0 + d_a (, w0 + d_b), from their Gram matrix g and r = -d . w0; false where
-// the face is degenerate or a weight is negative.
-__device__ __forceinline__ bool edge_weight(double g, double r, double& t) {
-  if (!(g > 1e-30 * fmax(g, 1e-300))) return false;
-  t = r / g;
-  return (t > -1e-14) & (1.0 - t > -1e-14);
-}
-__device__ __forceinline__ bool tri_weights(double gaa, double gab, double gbb, double ra, double rb, double& ta,
-                                            double& tb) {
-  const double scale = fmax(gaa, gbb), det = gaa * gbb - gab * gab;
-  if (!(fabs(det) > 1e-24 * scale * scale)) return false;
-  const double inv = 1.0 / det;
-  ta = (ra * gbb - gab * rb) * inv;
-  tb = (gaa * rb - ra * gab) * inv;
-  return (ta > -1e-14) & (tb > -1e-14) & (1.0 - ta - tb > -1e-14);
+// 1 / x to an ulp or two: the hardware's estimate, corrected twice.
+__device__ __forceinline__ double rcp_nr(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
 }
 
 // Closest point to the origin of conv(w[0..k)), k <= 4, where w[0] is the
@@ -224,38 +213,45 @@ __device__ __forceinline__ void closest_face(V3 (&w)[4], int& k, V3& v) {
   v = w0;
   auto offer = [&](bool ok, int mask, V3 x) {
     const double xx = dot(x, x);
-    if (ok && xx < best) { best = xx; bm = mask; v = x; }
+    const bool take = ok & (xx < best);
+    best = take ? xx : best;
+    bm = take ? mask : bm;
+    v.x = take ? x.x : v.x;
+    v.y = take ? x.y : v.y;
+    v.z = take ? x.z : v.z;
   };
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-    if (k > a + 1) {
-      double t = 0.0;
-      const bool ok = edge_weight(G[a][a], r[a], t);
-      offer(ok, 1 << a, axpy(t, d[a], w0));
-    }
-#pragma unroll
-  for (int b = 1; b < 3; ++b)
-    if (k > b + 1) {
-#pragma unroll
-      for (int a = 0; a < b; ++a) {
-        double ta = 0.0, tb = 0.0;
-        const bool ok = tri_weights(G[a][a], G[a][b], G[b][b], r[a], r[b], ta, tb);
-        offer(ok, (1 << a) | (1 << b), axpy(tb, d[b], axpy(ta, d[a], w0)));
-      }
-    }
-  if (k > 3) {
+  // weights of the other points positive (to rounding), those of w0 too, and
+  // the face not degenerate; without branches, so that the faces' chains of
+  // dependent operations overlap
+  auto edge = [&](int a, bool on) {
+    const double g = G[a][a], t = r[a] * rcp_nr(g);
+    offer(on & (g > 1e-30 * fmax(g, 1e-300)) & (t > -1e-14) & (1.0 - t > -1e-14), 1 << a, axpy(t, d[a], w0));
+  };
+  auto tri = [&](int a, int b, bool on) {
+    const double gaa = G[a][a], gab = G[a][b], gbb = G[b][b];
+    const double scale = fmax(gaa, gbb), det = gaa * gbb - gab * gab, inv = rcp_nr(det);
+    const double ta = (r[a] * gbb - gab * r[b]) * inv, tb = (gaa * r[b] - r[a] * gab) * inv;
+    offer(on & (fabs(det) > 1e-24 * scale * scale) & (ta > -1e-14) & (tb > -1e-14) & (1.0 - ta - tb > -1e-14),
+          (1 << a) | (1 << b), axpy(tb, d[b], axpy(ta, d[a], w0)));
+  };
+  edge(0, true);
+  if (k > 2) {
+    const bool four = k > 3;
+    edge(1, true);
+    edge(2, four);
+    tri(0, 1, true);
+    tri(0, 2, four);
+    tri(1, 2, four);
     const double c00 = G[1][1] * G[2][2] - G[1][2] * G[1][2], c01 = G[0][2] * G[1][2] - G[0][1] * G[2][2],
                  c02 = G[0][1] * G[1][2] - G[0][2] * G[1][1], c11 = G[0][0] * G[2][2] - G[0][2] * G[0][2],
                  c12 = G[0][1] * G[0][2] - G[0][0] * G[1][2], c22 = G[0][0] * G[1][1] - G[0][1] * G[0][1];
-    const double det = G[0][0] * c00 + G[0][1] * c01 + G[0][2] * c02;
+    const double det = G[0][0] * c00 + G[0][1] * c01 + G[0][2] * c02, inv = rcp_nr(det);
     const double scale = fmax(G[0][0], fmax(G[1][1], G[2][2]));
-    if (fabs(det) > 1e-24 * scale * scale * scale) {
-      const double inv = 1.0 / det;
-      const double t0 = (c00 * r[0] + c01 * r[1] + c02 * r[2]) * inv, t1 = (c01 * r[0] + c11 * r[1] + c12 * r[2]) * inv,
-                   t2 = (c02 * r[0] + c12 * r[1] + c22 * r[2]) * inv;
-      const bool ok = (t0 > -1e-14) & (t1 > -1e-14) & (t2 > -1e-14) & (1.0 - t0 - t1 - t2 > -1e-14);
-      offer(ok, 7, axpy(t2, d[2], axpy(t1, d[1], axpy(t0, d[0], w0))));
-    }
+    const double t0 = (c00 * r[0] + c01 * r[1] + c02 * r[2]) * inv, t1 = (c01 * r[0] + c11 * r[1] + c12 * r[2]) * inv,
+                 t2 = (c02 * r[0] + c12 * r[1] + c22 * r[2]) * inv;
+    offer(four & (fabs(det) > 1e-24 * scale * scale * scale) & (t0 > -1e-14) & (t1 > -1e-14) & (t2 > -1e-14) &
+              (1.0 - t0 - t1 - t2 > -1e-14),
+          7, axpy(t2, d[2], axpy(t1, d[1], axpy(t0, d[0], w0))));
   }
   // keep the face's points, in order
   const V3 w1 = w[1], w2 = w[2], w3 = w[3];
