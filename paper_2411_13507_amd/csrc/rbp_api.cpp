@@ -801,9 +801,11 @@ void rbp_destroy_batch(rbp_batch* b) {
 struct rbp_cut {
   int device = 0;
   rbp_cut_desc desc{};
-  unsigned long long* counter = nullptr;
-  int64_t* list = nullptr;
-  int64_t cap = 0;
+  int64_t* list = nullptr;      // workspace of a run, as the next three
+  int* n_near = nullptr;
+  int* most = nullptr;
+  unsigned* n_third = nullptr;
+  rbp::CutArgs plan{};          // the sizes of a run (cut_plan)
   int n_cu = 1;
   rbp::CutCtr* ctr = nullptr;   // per edge: centroid and reach (workspace of a run)
   int32_t* pv_off = nullptr;    // vertex table of the polytope obstacles
@@ -814,7 +816,8 @@ struct rbp_cut {
 
 namespace {
 void free_cut(rbp_cut* c) {
-  for (void* p : {static_cast<void*>(c->counter), static_cast<void*>(c->list), static_cast<void*>(c->pv_off),
+  for (void* p : {static_cast<void*>(c->n_near), static_cast<void*>(c->most),
+                  static_cast<void*>(c->n_third), static_cast<void*>(c->list), static_cast<void*>(c->pv_off),
                   static_cast<void*>(c->pv), static_cast<void*>(c->ctr), static_cast<void*>(c->pbox)})
     if (p) (void)hipFree(p);
   delete c;
@@ -958,15 +961,21 @@ int rbp_build_cut(const rbp_cut_desc* d, hipStream_t stream, rbp_cut** out) {
   if (!c) return RBP_E_ALLOC;
   c->device = dev;
   c->desc = *d;
-  c->cap = std::max<int64_t>(pairs, 1);
-  if ((rc = dalloc(&c->counter, 2)) || (rc = dalloc(&c->list, size_t(c->cap))) ||
+  int n_cu = 0;
+  if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1) n_cu = 1;
+  c->n_cu = n_cu;   // sizes the grid-stride launches over the listed pairs
+  c->plan.n_edges = d->n_edges;
+  c->plan.n_obst = d->n_obstacles + d->n_polytopes;
+  rbp::cut_plan(c->plan, n_cu);
+  if ((rc = dalloc(&c->n_near, size_t(std::max(c->plan.n_region, 1)))) || (rc = dalloc(&c->most, 1)) ||
+      (rc = dalloc(&c->n_third, size_t(c->plan.n_blocks))) || (rc = dalloc(&c->list, size_t(std::max<int64_t>(pairs, 1)))) ||
       (rc = dalloc(&c->ctr, size_t(std::max(d->n_edges, 1)))) || (rc = dalloc(&c->pbox, std::max<size_t>(pbox.size(), 6))) ||
       (rc = dalloc(&c->pv_off, vo.size())) || (rc = dalloc(&c->pv, std::max<size_t>(verts.size(), 3)))) {
     free_cut(c);
     return rc;
   }
-  // the count reads 0 until the first run (which zeroes it with a kernel)
-  if (hipMemsetAsync(c->counter, 0, 2 * sizeof(unsigned long long), stream) != hipSuccess ||
+  // the count reads 0 until the first run, whose kernels write all they read
+  if (hipMemsetAsync(c->n_third, 0, size_t(c->plan.n_blocks) * sizeof(unsigned), stream) != hipSuccess ||
       hipMemcpyAsync(c->pv_off, vo.data(), vo.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) ||
       (!verts.empty() &&
        hipMemcpyAsync(c->pv, verts.data(), verts.size() * sizeof(double), hipMemcpyHostToDevice, stream)) ||
@@ -976,9 +985,6 @@ int rbp_build_cut(const rbp_cut_desc* d, hipStream_t stream, rbp_cut** out) {
     free_cut(c);
     return RBP_E_DEVICE;
   }
-  int n_cu = 0;
-  if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1) n_cu = 1;
-  c->n_cu = n_cu;   // sizes the grid-stride launches over the listed pairs
   c->last_stream = stream;
   *out = c;
   return RBP_OK;
@@ -991,13 +997,13 @@ int rbp_cut_run(rbp_cut* c, const double* P, uint8_t* code, uint8_t* step, doubl
   if (d.n_edges == 0) return RBP_OK;
   const int n_obst = d.n_obstacles + d.n_polytopes;
   if (!P || !n_collide || (n_obst > 0 && !code)) return RBP_E_INVALID;
-  rbp::CutArgs a{};
+  rbp::CutArgs a = c->plan;
   a.n_edges = d.n_edges; a.n_obst = n_obst; a.n_box = d.n_obstacles; a.degree = d.degree;
   a.P = P; a.box_lo = d.box_lo; a.box_hi = d.box_hi;
   a.pob_off = d.pob_off; a.pob_A = d.pob_A; a.pob_b = d.pob_b; a.pv_off = c->pv_off; a.pv = c->pv;
   a.code = code; a.step = step; a.qp_dist2 = qp_dist2; a.n_collide = n_collide;
   a.ctr = c->ctr; a.pbox = c->pbox;
-  a.counter = c->counter; a.list = c->list; a.list_cap = c->cap;
+  a.list = c->list; a.n_near = c->n_near; a.most = c->most; a.n_third = c->n_third;
   if (rbp::launch_cut(a, stream, c->n_cu) != hipSuccess) return RBP_E_DEVICE;
   c->last_stream = stream;
   return RBP_OK;
@@ -1005,11 +1011,15 @@ int rbp_cut_run(rbp_cut* c, const double* P, uint8_t* code, uint8_t* step, doubl
 
 int rbp_cut_qp_count(rbp_cut* c, int64_t* n_qp) {
   if (!c || !n_qp) return RBP_E_INVALID;
-  unsigned long long v = 0;
-  if (hipStreamSynchronize(c->last_stream) != hipSuccess ||
-      hipMemcpy(&v, c->counter, sizeof(v), hipMemcpyDeviceToHost) != hipSuccess)
-    return RBP_E_DEVICE;
-  *n_qp = int64_t(v);
+  if (hipStreamSynchronize(c->last_stream) != hipSuccess) return RBP_E_DEVICE;
+  unsigned part[2048];
+  int64_t sum = 0;
+  for (int k = 0; k < c->plan.n_blocks; k += 2048) {
+    const int n = std::min(c->plan.n_blocks - k, 2048);
+    if (hipMemcpy(part, c->n_third + k, n * sizeof(unsigned), hipMemcpyDeviceToHost) != hipSuccess) return RBP_E_DEVICE;
+    for (int i = 0; i < n; ++i) sum += part[i];
+  }
+  *n_qp = sum;
   return RBP_OK;
 }
 

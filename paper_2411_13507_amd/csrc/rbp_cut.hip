@@ -50,10 +50,19 @@ constexpr int kCutBlock = 256;
 constexpr int kWave = 64;
 constexpr int kObsChunk = 8;    // obstacles per block of the filter
 constexpr int kEdges = 4;       // edges per thread of the filter
-constexpr int kNearCap = 1024;  // listed pairs a block holds before they go out one by one
+constexpr int kTile = kCutBlock * kEdges;   // edges per block of the filter
 // list entries are (obstacle << 32 | edge); this bit marks the polytope pairs
 // whose Cut-QP value is still to be computed
 constexpr int64_t kWantsValue = int64_t(1) << 62;
+
+// The pairs a filter block can list have a region of the list of their own,
+// as many entries as the block has pairs; region r belongs to edge tile r % n_tile
+// and obstacle chunk r / n_tile.
+__device__ __forceinline__ int64_t region_base(const CutArgs& A, int r) {
+  const int oc = r / A.n_tile, x = r - oc * A.n_tile, o0 = oc * kObsChunk;
+  const int rows = A.n_obst - o0 < kObsChunk ? A.n_obst - o0 : kObsChunk;
+  return (int64_t)o0 * A.n_edges + (int64_t)x * kTile * rows;
+}
 
 struct V3 {
   double x, y, z;
@@ -71,7 +80,7 @@ template <int P>
 __global__ __launch_bounds__(kCutBlock) void cut_edge_kernel(CutArgs A) {
   constexpr int NP = P + 1;
   const int e = blockIdx.x * kCutBlock + threadIdx.x;
-  if (e == 0) { A.counter[0] = 0ull; A.counter[1] = 0ull; }
+  if (e == 0) *A.most = 0;
   if (e >= A.n_edges) return;
   A.n_collide[e] = 0;
   double p[3 * NP];
@@ -97,16 +106,15 @@ __global__ __launch_bounds__(kCutBlock) void cut_edge_kernel(CutArgs A) {
 // bytes.  kVec: the thread's edges are consecutive, so that a row's codes go
 // out as one 4-byte word (and the NaNs as two 16-byte ones) where every row of
 // the outputs starts aligned; otherwise they lie a wavefront apart, so that a
-// store still covers consecutive bytes.  Pairs that are not far are collected
-// in LDS and appended to the list with one atomic per block: with one per
-// wavefront the counter itself bounds the kernel.
-// 50,000 edges x 200 boxes: 70.4 -> 26.5 us against steps 1 and 2 on every pair;
-// 20,000 edges x (200 boxes + 100 polytopes), with steps and values: 315 -> 23 us.
+// store still covers consecutive bytes.  Pairs that are not far go to the block's
+// own region of the list, their number to n_near: with one atomic on a common
+// counter per block, let alone per wavefront, the counter itself bounds the kernel.
+// 50,000 edges x 200 boxes: 70.4 us with steps 1 and 2 on every pair, 26.5 us with
+// the far test and one counter, 19 us with regions; 20,000 edges x (200 boxes + 100
+// polytopes), with steps and values: 315, 23 and 18 us.
 template <bool kVec>
 __global__ __launch_bounds__(kCutBlock) void cut_prefilter_kernel(CutArgs A) {
-  __shared__ int64_t near[kNearCap];
   __shared__ int n_near;
-  __shared__ unsigned long long base;
   const int tid = threadIdx.x;
   if (tid == 0) n_near = 0;
   __syncthreads();
@@ -118,6 +126,8 @@ __global__ __launch_bounds__(kCutBlock) void cut_prefilter_kernel(CutArgs A) {
     const int e = e0 + u * kStep;
     c[u] = A.ctr[e < A.n_edges ? e : A.n_edges - 1];
   }
+  const int region = (A.obst_base / kObsChunk + blockIdx.y) * A.n_tile + blockIdx.x;
+  int64_t* const near = A.list + region_base(A, region);
   const int o0 = A.obst_base + blockIdx.y * kObsChunk, o1 = o0 + kObsChunk < A.n_obst ? o0 + kObsChunk : A.n_obst;
   for (int o = o0; o < o1; ++o) {
     // the box of the obstacle: its own corners, or those of its vertices
@@ -164,25 +174,16 @@ __global__ __launch_bounds__(kCutBlock) void cut_prefilter_kernel(CutArgs A) {
       for (int u = 0; u < kEdges; ++u) {
         const int e = e0 + u * kStep;
         if (((codes >> (8 * u)) & 1u) == 0u && e < A.n_edges) {
-          const int64_t ent = ((int64_t)o << 32) | (int64_t)e;
-          const int pos = atomicAdd(&n_near, 1);
-          if (pos < kNearCap) {
-            near[pos] = ent;
-          } else {   // more than the block's buffer holds: straight to the list
-            const unsigned long long g = atomicAdd(A.counter + 1, 1ull);
-            if (g < (unsigned long long)A.list_cap) A.list[g] = ent;
-          }
+          near[atomicAdd(&n_near, 1)] = ((int64_t)o << 32) | (int64_t)e;
         }
       }
     }
   }
   __syncthreads();
-  const int n = n_near < kNearCap ? n_near : kNearCap;
-  if (n == 0) return;
-  if (tid == 0) base = atomicAdd(A.counter + 1, (unsigned long long)n);
-  __syncthreads();
-  for (int i = tid; i < n; i += kCutBlock)
-    if (base + i < (unsigned long long)A.list_cap) A.list[base + i] = near[i];
+  if (tid == 0) {
+    A.n_near[region] = n_near;
+    if (n_near > kWave) atomicMax(A.most, n_near);   // readers take 64 for less
+  }
 }
 
 // 1 / x to an ulp or two: the hardware's estimate, corrected twice.
@@ -487,16 +488,17 @@ __device__ V3 min_norm_point(const V3 (&pts)[NP], const double (&H)[6], V3 g, do
 
 template <int NP>
 __global__ __launch_bounds__(kCutBlock) void cut_value_kernel(CutArgs A) {
-  const unsigned long long cnt = A.counter[1];
-  const int64_t n = (int64_t)(cnt < (unsigned long long)A.list_cap ? cnt : (unsigned long long)A.list_cap);
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kCutBlock / kWave) + threadIdx.x / kWave));
   const int64_t nw = (int64_t)gridDim.x * (kCutBlock / kWave);
-  // a wavefront looks at 64 entries at once, nw apart (neighbouring entries
-  // are alike, so the marked ones spread over the wavefronts)
+  const int64_t R = A.n_region, n = R * (*A.most > kWave ? *A.most : kWave);
+  // a wavefront looks at 64 entries at once, nw apart in the order first entry
+  // of every region, second entry, .. (a region's entries are alike, so the
+  // marked ones spread over the wavefronts)
   for (int64_t t0 = wv; t0 < n; t0 += nw * kWave) {
-   const int64_t tl = t0 + nw * lane;
-   const int64_t el = tl < n ? A.list[tl] : 0;
+   const int64_t tl = t0 + nw * lane, slot = tl / R;
+   const int r = (int)(tl - slot * R);
+   const int64_t el = tl < n && slot < A.n_near[r] ? A.list[region_base(A, r) + slot] : 0;
    for (unsigned long long todo = __ballot((el & kWantsValue) != 0); todo; todo &= todo - 1) {
     const int src = __builtin_ctzll(todo);
     const int o = __builtin_amdgcn_readlane((int)((el & ~kWantsValue) >> 32), src);
@@ -592,12 +594,37 @@ __global__ __launch_bounds__(kCutBlock) void cut_value_kernel(CutArgs A) {
 template <int P>
 __global__ __launch_bounds__(kWave) void cut_qp_kernel(CutArgs A) {
   constexpr int NP = P + 1;
-  const unsigned long long cnt = A.counter[1];
-  const int64_t n = (int64_t)(cnt < (unsigned long long)A.list_cap ? cnt : (unsigned long long)A.list_cap);
-  for (int64_t t0 = (int64_t)blockIdx.x * kWave; t0 < n; t0 += (int64_t)gridDim.x * kWave) {
-    const int64_t t = t0 + threadIdx.x;
-    const bool live = t < n;
-    const int64_t ent = live ? A.list[t] : 0;
+  // A wavefront takes 64 entries of a group of consecutive regions (one region
+  // while there are blocks enough), the first 64 of every group before the next.
+  const int lane = threadIdx.x, G = A.group, n_group = (A.n_region + G - 1) / G;
+  const int64_t n_chunk = ((int64_t)(*A.most > kWave ? *A.most : kWave) * G + kWave - 1) / kWave;
+  const int64_t step_c = gridDim.x / n_group;
+  const int step_g = gridDim.x % n_group;
+  unsigned n3 = 0;                                            // pairs that reached step 3
+  int gi = blockIdx.x % n_group;
+  for (int64_t ch = blockIdx.x / n_group; ch < n_chunk;) {
+    const int first = gi * G;
+    const int64_t t = ch * kWave + lane;
+    gi += step_g;
+    ch += step_c + (gi >= n_group ? 1 : 0);
+    if (gi >= n_group) gi -= n_group;
+    const int cn = lane < G && first + lane < A.n_region ? A.n_near[first + lane] : 0;
+    int upto = cn, reg = 0;
+    if (G > 1) {
+      for (int d = 1; d < kWave; d <<= 1) {
+        const int up = __shfl_up(upto, d, kWave);
+        if (lane >= d) upto += up;
+      }
+      // the regions that end at or before entry t
+      for (int d = kWave / 2; d; d >>= 1)
+        if (__shfl(upto, reg + d - 1, kWave) <= t) reg += d;
+    }
+    const int total = __builtin_amdgcn_readlane(upto, G > 1 ? kWave - 1 : 0);
+    const int before = __shfl(upto - cn, reg, kWave);
+    const bool live = t < total;
+    const int64_t pos = live ? region_base(A, first + reg) + t - before : 0;
+    if (__ballot(live) == 0ull) continue;
+    const int64_t ent = live ? A.list[pos] : 0;
     const int o = (int)(ent >> 32), e = (int)(ent & 0xffffffffll);
     V3 pts[NP];
     V3 c{0.0, 0.0, 0.0};
@@ -666,9 +693,7 @@ __global__ __launch_bounds__(kWave) void cut_qp_kernel(CutArgs A) {
       }
     }
     // pairs that reach step 3, counted for rbp_cut_qp_count
-    const unsigned long long third = __ballot(live && !inside && !beyond);
-    if (third && threadIdx.x == (unsigned)__builtin_ctzll(third))
-      atomicAdd(A.counter, (unsigned long long)__popcll(third));
+    n3 += (unsigned)__popcll(__ballot(live && !inside && !beyond));
     if (!live) continue;
     const int64_t q = (int64_t)o * A.n_edges + e;
     if (inside || beyond) {
@@ -724,10 +749,11 @@ __global__ __launch_bounds__(kWave) void cut_qp_kernel(CutArgs A) {
     A.code[q] = (uint8_t)code;
     if (A.qp_dist2) {
       A.qp_dist2[q] = value;
-      if (code && o >= A.n_box) A.list[t] = ent | kWantsValue;
+      if (code && o >= A.n_box) A.list[pos] = ent | kWantsValue;
     }
     if (!code) atomicAdd(&A.n_collide[e], 1);
   }
+  if (lane == 0) A.n_third[blockIdx.x] = n3;
 }
 
 template <int P>
@@ -737,11 +763,11 @@ hipError_t launch_cut_p(const CutArgs& a, hipStream_t s, int n_cu) {
   // grid.y is limited to 65,535 blocks: more obstacles go in further launches
   constexpr int kMost = 65535 * kObsChunk;
   const int n_poly = a.n_obst - a.n_box;
-  const int gx = (a.n_edges + kCutBlock * kEdges - 1) / (kCutBlock * kEdges);
+  const int gx = a.n_tile;
   // words of four edges: every row o * n_edges of the outputs starts on one
   const bool vec = a.n_edges % kEdges == 0 && (reinterpret_cast<uintptr_t>(a.code) & 3) == 0 &&
                    (reinterpret_cast<uintptr_t>(a.step) & 3) == 0 && (reinterpret_cast<uintptr_t>(a.qp_dist2) & 15) == 0;
-  for (int o = 0; o < a.n_obst; o += kMost) {
+  for (int o = 0; o < a.n_obst; o += kMost) {   // kMost is a multiple of kObsChunk
     CutArgs b = a;
     b.obst_base = o;
     const int n = a.n_obst - o < kMost ? a.n_obst - o : kMost;
@@ -749,13 +775,22 @@ hipError_t launch_cut_p(const CutArgs& a, hipStream_t s, int n_cu) {
     if (vec) hipLaunchKernelGGL(cut_prefilter_kernel<true>, grid, dim3(kCutBlock), 0, s, b);
     else hipLaunchKernelGGL(cut_prefilter_kernel<false>, grid, dim3(kCutBlock), 0, s, b);
   }
-  hipLaunchKernelGGL((cut_qp_kernel<P>), dim3(16 * n_cu), dim3(kWave), 0, s, a);
+  hipLaunchKernelGGL((cut_qp_kernel<P>), dim3(a.n_blocks), dim3(kWave), 0, s, a);
   if (a.qp_dist2 && n_poly > 0)
     hipLaunchKernelGGL((cut_value_kernel<P + 1>), dim3(4 * n_cu), dim3(kCutBlock), 0, s, a);
   return hipGetLastError();
 }
 
 }  // namespace
+
+// list regions of n_edges x n_obst pairs, blocks of the step kernel and the
+// regions that one of its wavefronts looks at together
+void cut_plan(CutArgs& a, int n_cu) {
+  a.n_tile = (a.n_edges + kTile - 1) / kTile;
+  a.n_region = a.n_tile * ((a.n_obst + kObsChunk - 1) / kObsChunk);
+  a.n_blocks = 16 * n_cu;
+  a.group = a.n_region / a.n_blocks + 1 < kWave ? a.n_region / a.n_blocks + 1 : kWave;
+}
 
 hipError_t launch_cut(const CutArgs& a, hipStream_t s, int n_cu) {
   if (a.n_edges <= 0) return hipSuccess;

@@ -199,10 +199,14 @@ struct CutArgs {
   int obst_base;             // first obstacle of a filter launch
   const double* pbox;        // [n_obst - n_box][6] lower and upper corner of each polytope's vertices
   CutCtr* ctr;               // [n_edges] workspace
-  unsigned long long* counter;   // device: [0] pairs that reached step 3, [1] pairs in the list
-  int64_t* list;             // pairs that are not far (o << 32 | e)
-  int64_t list_cap;
+  int64_t* list;             // pairs that are not far (o << 32 | e), [n_obst n_edges] in regions
+  int n_tile, n_region;      // edge tiles; regions of the list, one per filter block
+  int n_blocks, group;       // blocks of the step kernel; regions a wavefront takes together
+  int* n_near;               // [n_region] entries
+  int* most;                 // largest of them, where above 64
+  unsigned* n_third;         // [n_blocks] pairs that reached step 3
 };
+void cut_plan(CutArgs& a, int n_cu);
 hipError_t launch_cut(const CutArgs& a, hipStream_t s, int n_cu);
 
 // ---- building the graph and adjacent hyperplanes (rbp_graph.hip)
