@@ -50,3 +50,28 @@ def test_lattice_distances(gpu_available, p, rank):
             elif o < n_o:
                 assert code[o, e] == 0, (o, e, d2[o, e])
     assert n3 > 0 or rank == 0
+
+
+@pytest.mark.parametrize("n_e,n_o", [(1, 4095), (3, 4100), (1030, 2100), (2, 270_000)])
+def test_many_list_regions(gpu_available, n_e, n_o):
+    """More list regions than the step kernel has wavefronts for (it then takes
+    2 to 64 of them together), empty ones and full ones: deciding steps and counts
+    against Alg. 2 in NumPy."""
+    import torch
+    from paper_2411_13507_amd.api import CutGPU
+    from tests.test_gpu_cut_far import _steps
+    rng = np.random.default_rng(n_o)
+    P = rng.uniform(4, 6, (n_e, 1, 3)) + rng.uniform(-0.3, 0.3, (n_e, 4, 3))
+    lo = rng.uniform(0, 9.5, (n_o, 3))
+    lo[: n_o // 64] = 5 + 0.2 * rng.standard_normal((n_o // 64, 3))     # near every edge
+    hi = lo + rng.uniform(0.05, 0.5, (n_o, 3))
+    print(f"case: {n_e} edges, {n_o} boxes", flush=True)
+    g = CutGPU(types.SimpleNamespace(box_lo=lo, box_hi=hi, degree=3), n_e)
+    for _ in range(2):
+        r = g.run(torch.as_tensor(P, device="cuda"))
+        step, code = r.step.cpu().numpy(), r.code.cpu().numpy()
+        want, sure = _steps(P, lo, hi)
+        assert np.array_equal(step[sure], want[sure])
+        assert g.qp_count() == int((step == 3).sum()) > 0
+        assert np.array_equal(np.isnan(r.qp_dist2.cpu().numpy()), step != 3)
+        assert np.array_equal(r.n_collide.cpu().numpy(), (code == 0).sum(0))
