@@ -430,13 +430,14 @@ __device__ V3 min_norm_point(const V3 (&pts)[NP], const double (&H)[6], V3 g, do
 #pragma unroll
       for (int i = 0; i < 3; ++i) d0[i] = M[i][i];
       bool sing = false;
+      double ip[3];             // 1 / pivot
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         sing |= !(M[k][k] > 1e-12 * d0[k]) | !(d0[k] > 0.0);
-        const double piv = M[k][k] > 0.0 ? M[k][k] : 1.0;
+        ip[k] = rcp_nr(M[k][k] > 0.0 ? M[k][k] : 1.0);
 #pragma unroll
         for (int i = k + 1; i < 3; ++i) {
-          const double l = M[i][k] / piv;
+          const double l = M[i][k] * ip[k];
 #pragma unroll
           for (int j = k + 1; j < 3; ++j) M[i][j] -= l * M[k][j];
           y[i] -= l * y[k];
@@ -447,7 +448,7 @@ __device__ V3 min_norm_point(const V3 (&pts)[NP], const double (&H)[6], V3 g, do
         double acc = y[k];
 #pragma unroll
         for (int j = k + 1; j < 3; ++j) acc -= M[k][j] * y[j];
-        y[k] = acc / (M[k][k] > 0.0 ? M[k][k] : 1.0);
+        y[k] = acc * ip[k];
       }
       if (sing) {                                       // drop the last point, stop
         --nc;
@@ -472,7 +473,7 @@ __device__ V3 min_norm_point(const V3 (&pts)[NP], const double (&H)[6], V3 g, do
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (i < nc && be[i] <= 0.0) {
-          const double ti = al[i] / (al[i] - be[i]);
+          const double ti = al[i] * rcp_nr(al[i] - be[i]);
           if (ti < th) { th = ti; kd = i; }
         }
       }
@@ -486,8 +487,9 @@ __device__ V3 min_norm_point(const V3 (&pts)[NP], const double (&H)[6], V3 g, do
       double sa = 0.0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) { al[i] = i < nc ? fmax(al[i], 0.0) : 0.0; sa += al[i]; }
+      const double is = rcp_nr(sa);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) al[i] /= sa;
+      for (int i = 0; i < 4; ++i) al[i] *= is;
       if (nc == 1) break;
     }
   }
