@@ -545,9 +545,10 @@ constexpr int kChainFirstPassRows = 32;
 // four-wavefront kernel at the full cap: a CU works through its few paths one
 // after the other, each much faster, and no path waits for the first pass of
 // the others.  With two passes / one pass, polish only: 256 paths 5.3 / 3.2 ms,
-// 512 5.3 / 3.6, 1,024 5.6 / 4.3, 2,048 6.1 / 6.5, 8,192 12.4 / 17.8.  The
-// ADMM warm start runs on one wavefront in either, so with it the line is one
-// path per CU: 256 paths 8.8 / 6.9 ms, 512 8.9 / 10.5, 1,024 13.8 / 17.3.
+// 512 5.3 / 3.6, 1,024 5.6 / 4.3, 2,048 6.1 / 6.5, 8,192 12.4 / 17.8 (since the
+// inverse Schur factor: 256 paths 3.0, 1,024 4.2, 2,048 in two passes 6.0, 8,192
+// 12.1).  The ADMM warm start runs on one wavefront in either, so with it the line
+// is one path per CU: 256 paths 8.8 / 6.9 ms, 512 8.9 / 10.5, 1,024 13.8 / 17.3.
 constexpr int kChainTeamPathsPerCu = 4;
 
 void free_chains(rbp_chains* c) {

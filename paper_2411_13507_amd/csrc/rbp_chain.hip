@@ -1,5 +1,5 @@
 // Multi-segment paths: S degree-p segments joined with continuous position,
-// velocity and acceleration, one 64-lane wavefront per path.
+// velocity and acceleration, one 64-lane wavefront per path, or four.
 //
 // Each segment keeps its control points in its own free-space polytope
 // (Property 1 of the paper), respects the velocity and acceleration bounds
@@ -18,8 +18,8 @@
 //
 // Forward pass: FP32 ADMM warm start with the banded K = P + rho A^T D^2 A
 // factored in LDS; FP64 dual active-set polish (Goldfarb-Idnani in the
-// Hessian's metric) using banded Cholesky solves with G1 (one lane per global
-// point) and a dense Cholesky factor of the small Schur complement
+// Hessian's metric) using products with L^-1 and L^-T, G1 = L L^T (one lane per
+// global point), and a dense Cholesky factor of the small Schur complement
 // N^T G^-1 N of the working set; Farkas vectors verified in FP64.
 #include <hip/hip_runtime.h>
 
@@ -92,7 +92,7 @@ struct CLds {
   float *Kb, *zr, *yr, *accp, *Pf, *xt, *Cs;
   double* Wm;
   // polish region
-  double *LS, *LSd, *beta, *acte, *u, *w, *zv, *np, *cvec;
+  double *W, *beta, *acte, *u, *w, *zv, *np, *cvec;
   int *actid, *actside, *actseg;
 };
 
@@ -127,8 +127,7 @@ __device__ CLds<P> ccarve(char* s, const ChainDims& D) {
   L.xt = (float*)(s + D.o_xt);
   L.Cs = (float*)(s + D.o_Cs);
   L.Wm = (double*)(s + D.o_Wm);
-  L.LS = (double*)(s + D.o_LS);
-  L.LSd = (double*)(s + D.o_LSd);
+  L.W = (double*)(s + D.o_W);
   L.beta = (double*)(s + D.o_beta);
   L.acte = (double*)(s + D.o_acte);
   L.u = (double*)(s + D.o_u);
@@ -989,12 +988,11 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
   int q = 0, steps = 0, status = kPolishFailed;
   // Working set of up to QC - 1 <= 127 rows: lane l holds entries l and l + 64
   // of every working-set vector (multipliers, right-hand sides of the Schur
-  // solves).  L_S is stored packed by rows, row k in k + 2 slots (the spare
-  // slot past the diagonal takes the Givens downdate), with its reciprocal
-  // diagonal in LSd.
+  // solves).  Of the factor L_S of N^T G^-1 N the inverse W is kept, packed by
+  // rows, row k in k + 1 slots.
   double lam0 = 0.0, lam1 = 0.0;   // multipliers of entries lane and lane + 64
   const int e0 = lane, e1 = lane + kWave;
-  auto lso = [](int k) -> int { return (k * (k + 3)) >> 1; };
+  auto row_at = [](int k) -> int { return (k * (k + 1)) >> 1; };
   auto pick = [&](double v0, double v1, int k) -> double {
     return wave::bcast(k < kWave ? v0 : v1, k & (kWave - 1));
   };
@@ -1075,56 +1073,51 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     c0 = e0 < q ? ndot(e0, L.u) : 0.0;
     c1 = e1 < q ? ndot(e1, L.u) : 0.0;
   };
-  // forward / backward solves with L_S on the first qq entries.  The factor
-  // entries a lane needs at step k and the reciprocal pivot do not depend on
-  // the solution: they are loaded two steps ahead, from addresses clamped to
-  // entries the factor holds (finite), and lanes that do not take part
-  // multiply theirs by zero, so no load waits behind a branch.
-  // Up to 64 rows each lane has one entry and the second slot's work is left out.
-  auto ls_sweep = [&](auto fwd, auto two, double& v0, double& v1, int qq) {
+  // L_S^-1 v (kFwd) or L_S^-T v on the first qq entries: products with W or its
+  // transpose, four rows in flight, where substitution with L_S waits for each
+  // entry before the next (1,024 paths: 4.70 -> 4.46 ms; eight rows in flight: 4.50,
+  // and slower on short working sets).  Entries from qq on
+  // come out 0.  Up to 64 rows each lane has one entry and the second slot's
+  // work is left out.
+  auto w_times = [&](auto fwd, auto two, double& v0, double& v1, int qq) {
     constexpr bool kFwd = decltype(fwd)::value, kTwo = decltype(two)::value;
-    const int a0 = e0 < qq ? e0 : qq - 1, a1 = e1 < qq ? e1 : qq - 1;
-    const int o0 = lso(a0), o1 = lso(a1);
-    auto fetch = [&](int t, double& d, double& l0, double& l1) {
-      const int tc = t < qq ? t : qq - 1, k = kFwd ? tc : qq - 1 - tc;
-      d = L.LSd[k];
-      if (kFwd) {   // L_S[e][k] below the diagonal
-        l0 = L.LS[o0 + (k < a0 ? k : a0)] * ((e0 > k && e0 < qq) ? 1.0 : 0.0);
-        if (kTwo) l1 = L.LS[o1 + (k < a1 ? k : a1)] * ((e1 > k && e1 < qq) ? 1.0 : 0.0);
-      } else {      // L_S[k][e] left of the diagonal
-        l0 = L.LS[lso(k) + (e0 < k ? e0 : k)] * (e0 < k ? 1.0 : 0.0);
-        if (kTwo) l1 = L.LS[lso(k) + (e1 < k ? e1 : k)] * (e1 < k ? 1.0 : 0.0);
+    constexpr int kV = 4;
+    const int o0 = row_at(e0 < qq ? e0 : 0), o1 = row_at(e1 < qq ? e1 : 0);
+    double y0 = 0.0, y1 = 0.0;
+    for (int k0 = 0; k0 < qq; k0 += kV) {
+      double x0[kV], x1[kV];
+#pragma unroll
+      for (int u = 0; u < kV; ++u) {
+        const int k = k0 + u, kr = k < qq ? row_at(k) : 0;
+        const bool on0 = kFwd ? k <= e0 && e0 < qq : e0 <= k && k < qq;
+        const bool on1 = kFwd ? k <= e1 && e1 < qq : e1 <= k && k < qq;
+        x0[u] = L.W[on0 ? (kFwd ? o0 + k : kr + e0) : 0];
+        x0[u] = on0 ? x0[u] : 0.0;
+        if (kTwo) {
+          x1[u] = L.W[on1 ? (kFwd ? o1 + k : kr + e1) : 0];
+          x1[u] = on1 ? x1[u] : 0.0;
+        }
       }
-    };
-    auto step = [&](int t, double d, double l0, double l1) {
-      const int k = kFwd ? t : qq - 1 - t;
-      const double vk = (kTwo ? pick(v0, v1, k) : wave::bcast(v0, k)) * d;
-      v0 = e0 == k ? vk : v0 - l0 * vk;
-      if (kTwo) v1 = e1 == k ? vk : v1 - l1 * vk;
-    };
-    double dA, xA, yA = 0.0, dB, xB, yB = 0.0;
-    fetch(0, dA, xA, yA);
-    fetch(1, dB, xB, yB);
-    int t = 0;
-    for (; t + 1 < qq; t += 2) {
-      double dC, xC, yC = 0.0, dD, xD, yD = 0.0;
-      fetch(t + 2, dC, xC, yC);
-      fetch(t + 3, dD, xD, yD);
-      step(t, dA, xA, yA);
-      step(t + 1, dB, xB, yB);
-      dA = dC; xA = xC; yA = yC; dB = dD; xB = xD; yB = yD;
+#pragma unroll
+      for (int u = 0; u < kV; ++u) {
+        const int k = k0 + u;
+        const double vk = k >= qq ? 0.0 : kTwo ? pick(v0, v1, k) : wave::bcast(v0, k & (kWave - 1));
+        y0 += x0[u] * vk;
+        if (kTwo) y1 += x1[u] * vk;
+      }
     }
-    if (t < qq) step(t, dA, xA, yA);
+    v0 = y0;
+    v1 = y1;
   };
   auto ls_forward = [&](double& v0, double& v1, int qq) {
     if (qq <= 0) return;
-    if (qq <= kWave) ls_sweep(std::true_type{}, std::false_type{}, v0, v1, qq);
-    else ls_sweep(std::true_type{}, std::true_type{}, v0, v1, qq);
+    if (qq <= kWave) w_times(std::true_type{}, std::false_type{}, v0, v1, qq);
+    else w_times(std::true_type{}, std::true_type{}, v0, v1, qq);
   };
   auto ls_backward = [&](double& v0, double& v1, int qq) {
     if (qq <= 0) return;
-    if (qq <= kWave) ls_sweep(std::false_type{}, std::false_type{}, v0, v1, qq);
-    else ls_sweep(std::false_type{}, std::true_type{}, v0, v1, qq);
+    if (qq <= kWave) w_times(std::false_type{}, std::false_type{}, v0, v1, qq);
+    else w_times(std::false_type{}, std::true_type{}, v0, v1, qq);
   };
   // w = N r (global), r given by entries (r0, r1): each lane sums its own
   // entries of w over the rows whose window holds them
@@ -1177,14 +1170,13 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
   };
   // append constraint (id, side), free right-hand side e_free, whose normal sits in beta slot q and np;
   // l = L_S^-1 N^T G^-1 np in (l0, l1); zz = np^T G^-1 np - |l|^2
-  auto append_factor = [&](int id, int side, double e_free, double l0, double l1, double zz) {
-    const int ro = lso(q);
-    if (e0 < q) L.LS[ro + e0] = l0;
-    if (e1 < q) L.LS[ro + e1] = l1;
+  auto append_factor = [&](int id, int side, double e_free, double r0, double r1, double zz) {
+    const int ro = row_at(q);
+    const double id_q = 1.0 / sqrt(zz);
+    if (e0 < q) L.W[ro + e0] = -r0 * id_q;
+    if (e1 < q) L.W[ro + e1] = -r1 * id_q;
     if (lane == 0) {
-      const double dq = sqrt(zz);
-      L.LS[ro + q] = dq;
-      L.LSd[q] = 1.0 / dq;
+      L.W[ro + q] = id_q;
       L.actid[q] = id; L.actside[q] = side;
       L.acte[q] = e_free;
     }
@@ -1192,11 +1184,12 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     ++q;
     sync();
   };
-  // Cholesky delete of index kd: the rows below move up one place, then Givens
-  // rotations of the columns (kd, kd+1), (kd+1, kd+2), .. restore the triangle.
-  // A lane moves its own columns and rotates its own rows, so nothing in either
-  // loop waits for another lane's store: a lane carries its row's entry of the
-  // column in work, and rotation j takes its pair from lane j.
+  // Remove working-set row kd.  W S W^T = 1, so an orthogonal combination of
+  // the rows of W that leaves column kd to one row alone, which goes, is the new
+  // factor once column kd is dropped: rotations of (what is carried, row j + 1)
+  // for j = kd, kd + 1, ..  keep it triangular.  A lane rotates its own columns
+  // and writes row j where row j was read before, so nothing waits for another
+  // lane's store.
   auto drop = [&](int kd) {
     set_bit(L.actid[kd], false);
     // ids, sides, right-hand sides: entries e0 and e1 take their successors'
@@ -1209,26 +1202,14 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     sync();
     if (s0i >= 0) { L.actid[e0] = id0; L.actside[e0] = sd0; L.actseg[e0] = sg0; L.acte[e0] = ev0; }
     if (s1i >= 0) { L.actid[e1] = id1; L.actside[e1] = sd1; L.actseg[e1] = sg1; L.acte[e1] = ev1; }
-    // row k + 1 (columns 0..k+1) becomes row k, whose spare slot takes column
-    // k + 1; four rows in flight
+    // the cached normals, four rows in flight
     for (int k0 = kd; k0 < q - 1; k0 += 4) {
-      double a0[4], a1[4], bv[4];
+      double bv[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = k0 + u;
-        const bool on = k < q - 1;
-        a0[u] = (on && e0 <= k + 1) ? L.LS[lso(k + 1) + e0] : 0.0;
-        a1[u] = (on && e1 <= k + 1) ? L.LS[lso(k + 1) + e1] : 0.0;
-        bv[u] = (on && lane < NC) ? L.beta[(k + 1) * NB + lane] : 0.0;
-      }
+      for (int u = 0; u < 4; ++u) bv[u] = (k0 + u < q - 1 && lane < NC) ? L.beta[(k0 + u + 1) * NB + lane] : 0.0;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int k = k0 + u;
-        const bool on = k < q - 1;
-        if (on && e0 <= k + 1) L.LS[lso(k) + e0] = a0[u];
-        if (on && e1 <= k + 1) L.LS[lso(k) + e1] = a1[u];
-        if (on && lane < NC) L.beta[k * NB + lane] = bv[u];
-      }
+      for (int u = 0; u < 4; ++u)
+        if (k0 + u < q - 1 && lane < NC) L.beta[(k0 + u) * NB + lane] = bv[u];
     }
     {
       // entry j takes entry j + 1 (entry 64 comes from lane 0's second slot)
@@ -1240,28 +1221,23 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       if (e1 >= kd && e1 < q - 1) lam1 = up1;
     }
     sync();
-    // rows kd..q-2 have an entry one past the diagonal
-    const bool in0 = e0 >= kd && e0 < q - 1, in1 = e1 >= kd && e1 < q - 1;
-    const int r0w = lso(in0 ? e0 : kd), r1w = lso(in1 ? e1 : kd);
-    double c0 = L.LS[r0w + kd], c1 = L.LS[r1w + kd];          // entries of column kd
-    // column j + 1 of a row that reaches it (row e holds columns 0..e+1)
-    auto col0 = [&](int j) { return (in0 && j <= e0 + 1) ? L.LS[r0w + j] : 0.0; };
-    auto col1 = [&](int j) { return (in1 && j <= e1 + 1) ? L.LS[r1w + j] : 0.0; };
-    double x0n = col0(kd + 1), x1n = col1(kd + 1);
+    auto at0 = [&](int j) { return (e0 <= j && j < q) ? L.W[row_at(j) + e0] : 0.0; };
+    auto at1 = [&](int j) { return (e1 <= j && j < q) ? L.W[row_at(j) + e1] : 0.0; };
+    double c0 = at0(kd), c1 = at1(kd), x0n = at0(kd + 1), x1n = at1(kd + 1);
+    double a = pick(c0, c1, kd);
+    const int w0 = e0 > kd ? e0 - 1 : e0, w1 = e1 > kd ? e1 - 1 : e1;
     for (int j = kd; j < q - 1; ++j) {
       const double x0c = x0n, x1c = x1n;
-      x0n = col0(j + 2);
-      x1n = col1(j + 2);
-      const double a = pick(c0, c1, j), b = pick(x0c, x1c, j);
-      const double r2 = a * a + b * b;
-      const bool ok = r2 > 0.0;
-      const double ir = ok ? rsqrt_nr(r2) : 1.0;
-      const double cg = ok ? a * ir : 1.0, sg = ok ? b * ir : 0.0;
-      if (in0 && e0 >= j) L.LS[r0w + j] = cg * c0 + sg * x0c;
-      if (in1 && e1 >= j) L.LS[r1w + j] = cg * c1 + sg * x1c;
-      if (lane == 0) L.LSd[j] = ir;
-      c0 = cg * x0c - sg * c0;
-      c1 = cg * x1c - sg * c1;
+      x0n = at0(j + 2);
+      x1n = at1(j + 2);
+      const double b = pick(x0c, x1c, kd);
+      const double r2 = a * a + b * b, ir = rsqrt_nr(r2);
+      const double cg = a * ir, sg = b * ir;
+      if (e0 != kd && e0 <= j + 1) L.W[row_at(j) + w0] = cg * x0c - sg * c0;
+      if (e1 != kd && e1 <= j + 1) L.W[row_at(j) + w1] = cg * x1c - sg * c1;
+      c0 = cg * c0 + sg * x0c;
+      c1 = cg * c1 + sg * x1c;
+      a = r2 * ir;
     }
     --q;
     if (e0 >= q) lam0 = 0.0;
@@ -1300,7 +1276,10 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
     ls_forward(l0, l1, q);
     const double ll = wave::sum((e0 < q ? l0 * l0 : 0.0) + (e1 < q ? l1 * l1 : 0.0));
     const double zz = nu - ll;
-    if (zz > 1e-10 * nu) append_factor(id, side, row_e(id, side) - double(side) * row_const(id), l0, l1, zz);
+    if (zz > 1e-10 * nu) {
+      ls_backward(l0, l1, q);
+      append_factor(id, side, row_e(id, side) - double(side) * row_const(id), l0, l1, zz);
+    }
   }
   // dual feasibility of the working set: S lam = N^T x_u - e
   for (int guard = 0; guard <= QC; ++guard) {
@@ -1389,7 +1368,6 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
       nt_u(c0, c1);                           // c = N^T u
       double r0 = c0, r1 = c1;                // r = S^-1 c
       ls_forward(r0, r1, q);
-      const double l0 = r0, l1 = r1;          // L_S^-1 c, the row that appending adds
       ls_backward(r0, r1, q);
       if (e0 >= q) r0 = 0.0;
       if (e1 >= q) r1 = 0.0;
@@ -1460,7 +1438,7 @@ __device__ __forceinline__ void chain_instance(const ChainArgs& A, const int ch,
         }
       }
       if (t2 <= t1) {
-        append_factor(id, side, e_free, l0, l1, zz);
+        append_factor(id, side, e_free, r0, r1, zz);
         if (e0 == q - 1) lam0 = lamp;
         if (e1 == q - 1) lam1 = lamp;
         added = true;
@@ -1620,8 +1598,7 @@ ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bo
   d.o_Cs = take_a(NC * NC * 4);
   int b = region;
   auto take_b = [&](int bytes) { const int at = b; b += (bytes + 15) & ~15; return at; };
-  d.o_LS = take_b(((d.q_cap * (d.q_cap + 3)) >> 1) * 8);   // packed rows, k + 2 slots each
-  d.o_LSd = take_b(d.q_cap * 8);
+  d.o_W = take_b(((d.q_cap * (d.q_cap + 1)) >> 1) * 8);   // packed rows, k + 1 slots each
   d.o_beta = take_b(d.q_cap * (NC | 1) * 8);
   d.o_acte = take_b(d.q_cap * 8);
   d.o_u = take_b(4 * d.n_cap * 8);
