@@ -136,8 +136,9 @@ typedef struct rbp_solve_opts {
   int32_t plain;              /* 1: FP64 iterations, one kernel launch per
                                  instance (the unbatched baseline)                */
   int32_t launch_shape;       /* grouped schedule: 0 = one instance (wavefront)
-                                 per workgroup, registers sized for two
-                                 wavefronts per SIMD; 1 = one per workgroup,
+                                 per workgroup, registers sized for three
+                                 wavefronts per SIMD up to degree 7, two above
+                                 and with FP64 iterations; 1 = one per workgroup,
                                  registers for one wavefront per SIMD; 2 = two
                                  instances per workgroup, each wavefront on its
                                  own LDS slice.  Ignored with plain, with
@@ -282,12 +283,14 @@ int rbp_chains_get_sizes(const rbp_chains* chains, rbp_batch_sizes* out);
 
 /*
  * Forward pass over all paths: FP32 ADMM warm start (admm_iters > 0) with a
- * banded KKT matrix in LDS, FP64 dual active-set polish with banded Cholesky
- * solves.  Infeasibility is reported only with a certificate checked in FP64:
+ * banded KKT matrix in LDS, FP64 dual active-set polish with products of the
+ * Hessian's inverse factor (one table per segment count, made with the device's
+ * first batch).  Infeasibility is reported only with a certificate checked in FP64:
  * a Farkas vector, or a dual value of the polish's multipliers above every
  * objective value in the box that the chained velocity rows give (weak
- * duality).  Paths are launched in groups by segment count; each group runs
- * twice: every path first with a small working set, then the few whose
+ * duality).  Paths are launched in groups by segment count.  Batches of up to
+ * four paths per compute unit (one with the warm start) run once, four
+ * wavefronts per path; each group of a larger one runs twice: every path first with a small working set, then the few whose
  * working set outgrew it at the full size, continuing from the working set
  * the first launch held (their outputs are rewritten; until then status_out
  * may hold an internal value).  The groups run on `stream` and the device's
@@ -354,13 +357,14 @@ typedef struct rbp_cut_desc {
 
 typedef struct rbp_cut rbp_cut;
 
-/* Upper bound on n_edges * (n_obstacles + n_polytopes) (the undecided-pair
- * list is sized for every pair). */
+/* Upper bound on n_edges * (n_obstacles + n_polytopes) (the list of
+ * pairs that are not far apart is sized for every pair). */
 #define RBP_CUT_MAX_PAIRS (1LL << 28)
 
 /*
  * Keeps the obstacle arrays (device pointers, owned by the caller, which
- * must keep them alive) and allocates the undecided-pair list.  Polytope
+ * must keep them alive) and allocates that list, its counts and 32 bytes per edge, which a run
+ * overwrites (runs of one object must not overlap).  Polytope
  * rows are copied to the host (the call synchronises `stream`) to enumerate
  * each polytope's vertices (intersections of three of its planes that
  * satisfy every row, duplicates merged), which the supporting planes and the
@@ -394,7 +398,7 @@ int rbp_cut_run(rbp_cut* cut, const double* P, uint8_t* code, uint8_t* step, dou
  * stream of that run).  Errors: RBP_E_INVALID, RBP_E_DEVICE. */
 int rbp_cut_qp_count(rbp_cut* cut, int64_t* n_qp);
 
-/* Frees the list (waits for the last run). */
+/* Frees the object and its memory (waits for the last run). */
 void rbp_destroy_cut(rbp_cut* cut);
 
 /* ------------------------------------------------------------------------
@@ -449,7 +453,7 @@ void rbp_destroy_graph(rbp_graph* graph);
  *            read during the call only
  *   V, adj, degree   as in rbp_graph_run (caller-owned device buffers)
  * Workspace: a fixed device array of RBP_GRAPH_NOALLOC_DOUBLES doubles
- * (8 MiB) per GPU, held by the library until the process ends; a call needs
+ * (8 MiB, and 64 KiB of flags) per GPU, held by the library until the process ends; a call needs
  * 2 n m + 2 ceil(n / 64) m of them (n nodes, m rows; 5,000 nodes with 64 rows
  * need 650,112).  Every call on one GPU uses that GPU's array, so calls that
  * overlap on one GPU (different streams, or host threads) race: order them

@@ -26,7 +26,7 @@ from .api import SegmentBatchGPU
 CACHE = os.environ.get("RBP_AUTOTUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "rbp_autotune.json"))
 CANDIDATES: Tuple[Tuple[int, float], ...] = ((0, 0.1), (5, 0.1), (10, 0.1), (20, 0.1), (10, 0.03), (10, 0.3), (10, 1.0))
 # (schedule, launch shape): grouped with one wavefront per workgroup and
-# registers for two per SIMD (the default), the same with registers for one
+# registers for two or three per SIMD (the default), the same with registers for one
 # per SIMD, grouped with two instances per workgroup, one launch for the batch
 LAUNCHES: Tuple[Tuple[int, int], ...] = ((0, 0), (0, 1), (0, 2), (1, 0))
 
