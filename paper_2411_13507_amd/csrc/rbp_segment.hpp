@@ -898,9 +898,20 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   // rotation of (j, j+1) has sine sqrt(P_j / P_{j+1}) and cosine s_{j+1} /
   // sqrt(P_{j+1}): lane j forms its pair from the running sums, and the loop
   // carries one basis entry and one entry of a row of S per lane from column to
-  // column (no rotation waits for another's result in LDS, and S needs no
-  // rebuilding: against rotating R and inverting it again a drop takes a
-  // fraction of the time).  The signs keep the diagonal of S positive.
+  // column (no rotation waits for another's result in LDS; against rotating R and
+  // inverting it again a drop takes a fraction of the time).  The signs keep the
+  // diagonal of S positive.
+  // What leaves a row of S with the last column cancels: the row's rounding errors
+  // stay and grow, against what is left of it, by the ratio of the two, which is
+  // one over the angle for a row nearly parallel to the dropped one.  (The basis
+  // loses nothing: the direction of s is exact to rounding however long s is.)
+  // Where the ratio passes kMaxGrowth for some row, the columns that the drop
+  // changed are formed again from the basis and the rows' normals, as append forms
+  // them.  Below it the errors stay under some 1e-14; ordinary rows hardly ever
+  // reach it.  With pairs of rows 1e-6 apart in a warm start, the largest excess of
+  // a returned point over a bound: 3.5e-8 without this, 6e-13 with it (4e-13 where R
+  // is rotated and inverted again at every drop).  Its price is 0-1 % of a solve.
+  constexpr double kMaxGrowth = 32.0;
   auto drop = [&](int kd) {
     {
       int own, bit;
@@ -937,6 +948,10 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
     double sa = lr <= kd ? L.Ri[kd * (kd + 1) / 2 + lr] : 0.0;
     double qb = L.Q1[(kd + 1 < q ? kd + 1 : kd) * NS + li];
     double sb = kd + 1 < q ? L.Ri[(kd + 1) * (kd + 2) / 2 + (lr <= kd + 1 ? lr : 0)] : 0.0;
+    // squared length of what is left of this lane's row (at least: of the columns
+    // before kd its diagonal entry alone)
+    const double sd = lr < kd ? L.Ri[lr * (lr + 1) / 2 + lr] : 0.0;
+    double left = sd * sd;
     for (int j = kd; j < q - 1; ++j) {
       const int jn = j + 2 < q ? j + 2 : j + 1;          // next column, loaded ahead
       const double qn = L.Q1[jn * NS + li];
@@ -945,14 +960,32 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
       const double sbm = lr <= j + 1 ? sb : 0.0;
       if (vl) L.Q1[j * NS + lane] = w * qb - c * qa;
       qa = w * qa + c * qb;
-      if (lane < q && lane != kd && lw <= j) L.Ri[j * (j + 1) / 2 + lw] = w * sbm - c * sa;
+      const double sv = w * sbm - c * sa;                // 0 below the diagonal
+      left = fma(sv, sv, left);
+      if (lane < q && lane != kd && lw <= j) L.Ri[j * (j + 1) / 2 + lw] = sv;
       sa = w * sa + c * sbm;
       qb = qn;
       sb = sn;
     }
+    const bool redo = wany(lane < q && lane != kd && kd < q - 1 && !(sa * sa <= kMaxGrowth * kMaxGrowth * left));
     --q;
     if (lane >= q) lamr = 0.0;
     bsync<kWS>();
+    if (redo) {
+      for (int k = kd; k < q; ++k) {
+        const int ln = opaque(lane), t = ln / 3, id = __builtin_amdgcn_readfirstlane(L.actid[k]);
+        if (ln < N) L.vB[ln] = double(L.actside[k]) * in.whitened(id, t, ln - 3 * t, ln, L.cL1i, L.Af, L.Hd);
+        bsync<kWS>();
+        const double c = ln <= k ? dot_row<N>(L.Q1 + ln * NS, L.vB) : 0.0;
+        if (ln < k) L.vC[ln] = c;
+        bsync<kWS>();
+        const double r = ln < k ? upper_times_q(L.Ri, L.vC, ln, k) : 0.0;
+        const double ck = wave::bcast(c, k);
+        const double ick = div_nr(1.0, ck);
+        if (ck > 0.0 && ln <= k) L.Ri[k * (k + 1) / 2 + ln] = ln == k ? ick : -r * ick;
+        bsync<kWS>();
+      }
+    }
   };
 
   // multipliers of the current working set at the minimiser on its face:
