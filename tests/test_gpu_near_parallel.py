@@ -90,3 +90,64 @@ def test_segment_rows_hold(p, delta):
               f"largest excess {worst:.1e}", flush=True)
         assert len(ok) >= 0.9 * len(insts)
         assert worst <= 2e-11
+
+
+def _turned_paths(b, P, paths, delta):
+    """Some paths of ``b`` with the rows of every segment doubled as above."""
+    import dataclasses
+    seg_off, A, f, po, H, h0, G, ro, ho = [0], [], [], [0], [], [], [], [0], [0]
+    for c in paths:
+        ch = b.chain(c)
+        for s, seg in enumerate(ch["segments"]):
+            t = _turned(np.random.default_rng([c, s]), dict(seg, x0=ch["x0"]), P[int(b.seg_off[c]) + s], delta)
+            A.append(t["A_face"]); f.append(t["b_face"]); po.append(po[-1] + len(f[-1]))
+            H.append(t["H"].ravel()); h0.append(t["h0"]); G.append(t["G"])
+            ro.append(ro[-1] + len(h0[-1])); ho.append(ho[-1] + H[-1].size)
+        seg_off.append(seg_off[-1] + len(ch["segments"]))
+    return dataclasses.replace(
+        b, seg_off=np.asarray(seg_off, np.int64), poly_off=np.asarray(po, np.int32), A_face=np.concatenate(A),
+        b_face=np.concatenate(f), poly_idx=np.arange(len(A), dtype=np.int32), reach_off=np.asarray(ro, np.int64),
+        H_off=np.asarray(ho, np.int64), H=np.concatenate(H), h0=np.concatenate(h0), G=np.concatenate(G),
+        x0=b.x0[paths], goal=b.goal[paths])
+
+
+def _path_excess(b, c, P):
+    """As _excess, over the segments of path c (control points P [segments, points, 3])."""
+    ch, x0 = b.chain(c), b.x0[c, :3]
+    worst = -np.inf
+    for s, seg in enumerate(ch["segments"]):
+        Q = P[s]
+        sv, sa = b.degree / b.T, b.degree * (b.degree - 1) / b.T ** 2
+        bound = seg["b_face"] - seg["A_face"] @ x0
+        worst = max(worst, (((Q - x0) @ seg["A_face"].T - bound) / (1 + np.abs(bound))).max())
+        worst = max(worst, (np.abs(np.diff(Q, axis=0)).max() * sv - b.vmax) / (1 + b.vmax),
+                    (np.abs(np.diff(Q, 2, axis=0)).max() * sa - b.amax) / (1 + b.amax))
+        H, G = seg["H"], seg["G"]
+        bound = seg["h0"] - H.reshape(len(H), -1, 3).sum(1) @ x0 + G[:, :3] @ x0
+        v = H @ (Q - x0).ravel()
+        if s == 0:
+            bound = bound + G[:, 3:] @ b.x0[c, 3:]
+        else:
+            v = v - G[:, :3] @ (Q[0] - x0) - G[:, 3:] @ (sv * (Q[1] - Q[0]))
+        worst = max(worst, ((v - bound) / (1 + np.abs(bound))).max())
+    return worst
+
+
+@pytest.mark.parametrize("copies", [1, 32], ids=["one-pass", "two-pass"])
+@pytest.mark.parametrize("delta", [1e-3, 3e-5, 1e-6])
+def test_path_rows_hold(delta, copies):
+    from tests.test_gpu_chains import _opts, gpu_chains
+    from workloads import gen
+    base = gen.gen_cfg3(indices=range(64))
+    _, ref = gpu_chains(base, _opts(0))
+    use = np.flatnonzero(ref["status"] == 0)
+    b = _turned_paths(base, ref["P"].reshape(-1, 8, 3), use, delta)
+    big = gen.concat_chains([b] * copies)       # (more than four paths per CU take two passes)
+    for admm in (0, None):
+        _, out = gpu_chains(big, _opts(admm))
+        P = out["P"].reshape(-1, 8, 3)
+        ok = [c for c in range(b.n) if out["status"][c] == 0]
+        worst = max(_path_excess(b, c, P[b.seg_off[c]:b.seg_off[c + 1]]) for c in ok)
+        print(f"case: delta {delta}, admm_iters {admm}: {len(ok)} of {b.n} solved, largest excess {worst:.1e}", flush=True)
+        assert len(ok) >= 0.9 * b.n
+        assert worst <= 2e-11
