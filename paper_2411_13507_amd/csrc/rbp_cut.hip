@@ -450,8 +450,7 @@ __device__ V3 min_norm_point(const V3 (&pts)[NP], const double (&H)[6], V3 g, do
         for (int j = k + 1; j < 3; ++j) acc -= M[k][j] * y[j];
         y[k] = acc * ip[k];
       }
-      if (sing) {                                       // drop the last point, stop
-        --nc;
+      if (sing) {          // stop: al are convex weights of the corral as it stands
         done = true;
         break;
       }
@@ -467,13 +466,15 @@ __device__ V3 min_norm_point(const V3 (&pts)[NP], const double (&H)[6], V3 g, do
         for (int i = 0; i < 4; ++i) al[i] = be[i];
         break;
       }
-      // largest step from al towards be that keeps every weight >= 0
-      double th = 1.0;
+      // largest step from al towards be that keeps every weight >= 0, and the point
+      // whose weight it takes to 0 (some be is <= 0; where both weights are 0 the
+      // step is 0)
+      double th = 2.0;
       int kd = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (i < nc && be[i] <= 0.0) {
-          const double ti = al[i] * rcp_nr(al[i] - be[i]);
+          const double ti = al[i] > 0.0 ? fmin(al[i] * rcp_nr(al[i] - be[i]), 1.0) : 0.0;
           if (ti < th) { th = ti; kd = i; }
         }
       }
