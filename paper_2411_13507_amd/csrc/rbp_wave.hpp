@@ -4,7 +4,10 @@
 // across wave halves.  Every lane ends with the same value, computed with the
 // same operand order (each step combines a value with its partner's, and the
 // operations used are commutative), so results are bitwise identical across
-// lanes.
+// lanes.  Additions are kept apart from the products that may feed them: a
+// caller's a * b contracted into the first step would give lane i
+// fma(a_i, b_i, a_j b_j) and lane j fma(a_j, b_j, a_i b_i), which differ in the
+// last bit, and code that branches on a sum relies on lanes that agree.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
@@ -67,23 +70,27 @@ __device__ __forceinline__ double reduce_f64(double v, Op op) {
   return op(p.a, p.b);
 }
 
+__device__ __forceinline__ double add(double a, double b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
 __device__ __forceinline__ double sum(double v) {
-  return reduce_f64(v, [](double a, double b) { return a + b; });
+  return reduce_f64(v, [](double a, double b) { return add(a, b); });
 }
 // four sums at once (the stages of the four trees interleave)
 __device__ __forceinline__ void sum4(double (&v)[4]) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) v[u] = v[u] + dpp_f64<kXor1>(v[u]);
+  for (int u = 0; u < 4; ++u) v[u] = add(v[u], dpp_f64<kXor1>(v[u]));
 #pragma unroll
-  for (int u = 0; u < 4; ++u) v[u] = v[u] + dpp_f64<kXor2>(v[u]);
+  for (int u = 0; u < 4; ++u) v[u] = add(v[u], dpp_f64<kXor2>(v[u]));
 #pragma unroll
-  for (int u = 0; u < 4; ++u) v[u] = v[u] + dpp_f64<kHalfMirror>(v[u]);
+  for (int u = 0; u < 4; ++u) v[u] = add(v[u], dpp_f64<kHalfMirror>(v[u]));
 #pragma unroll
-  for (int u = 0; u < 4; ++u) v[u] = v[u] + dpp_f64<kMirror>(v[u]);
+  for (int u = 0; u < 4; ++u) v[u] = add(v[u], dpp_f64<kMirror>(v[u]));
 #pragma unroll
-  for (int u = 0; u < 4; ++u) { const PairD p = swap_f64(v[u], false); v[u] = p.a + p.b; }
+  for (int u = 0; u < 4; ++u) { const PairD p = swap_f64(v[u], false); v[u] = add(p.a, p.b); }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) { const PairD p = swap_f64(v[u], true); v[u] = p.a + p.b; }
+  for (int u = 0; u < 4; ++u) { const PairD p = swap_f64(v[u], true); v[u] = add(p.a, p.b); }
 }
 __device__ __forceinline__ double max(double v) {
   return reduce_f64(v, [](double a, double b) { return fmax(a, b); });

@@ -32,3 +32,36 @@ def test_box_as_polytope(degree):
     err = np.abs(a - b) / a
     print(f"case: degree {degree}, {free.sum()} values, largest relative difference {err.max():.1e}", flush=True)
     assert err.max() <= 1e-9
+
+
+def test_lanes_agree():
+    """A pair whose dual gap lands on the stopping bound: the wavefront goes on or
+    stops as one (where the lanes' sums differ in the last bit, one in twenty of
+    its copies, moved by 1e-13, ends at a value near 0)."""
+    import torch
+    from oracle.cut import cut_qp_poly
+    from paper_2411_13507_amd.api import CutGPU
+    P = np.array([[0.6258225018000105, -0.8665305072438529, 7.204433177859257],
+                  [0.8310452188788373, -0.4719735481173304, 0.6485768129302807],
+                  [0.7483986540828451, -2.257931254962589, 4.9519576763979725],
+                  [1.231659543823465, 0.03068490282195896, 8.943219434503847],
+                  [1.5160104932492184, 0.8034826711387901, 4.8872908030357785],
+                  [1.70266510176027, 0.22814663010662672, 2.595700930353898],
+                  [2.55861944502551, -0.3037201771566187, 2.7341606191380143],
+                  [1.4110871187217402, -0.6644989102349486, 4.910266135740609],
+                  [2.1056270632851875, -1.2444474079033425, 3.0978571895319225],
+                  [2.245857084255657, -2.826452161798948, 3.0841139542863214]])
+    A = np.array([[5.1787698410098555, 5.1787698410098555, 5.1787698410098555],
+                  [5.7248299060613475, -5.7248299060613475, -5.7248299060613475],
+                  [-1.812954810549594, 1.812954810549594, -1.812954810549594],
+                  [-0.195215212159489, -0.195215212159489, 0.195215212159489]])
+    b = np.array([24.09695237082329, -12.36115908031213, -2.0267513046806, 0.19140264532757648])
+    want = cut_qp_poly(P, A, b).value
+    rng = np.random.default_rng(0)
+    Q = np.concatenate([P[None], np.stack([P[rng.permutation(10)] for _ in range(50)]),
+                        P[None] + 1e-13 * rng.standard_normal((2000, 10, 3))])
+    prob = types.SimpleNamespace(box_lo=np.zeros((0, 3)), box_hi=np.zeros((0, 3)), degree=9,
+                                 pob_off=np.array([0, 4], np.int32), pob_A=A, pob_b=b)
+    v = CutGPU(prob, len(Q)).run(torch.as_tensor(Q, device="cuda")).qp_dist2.cpu().numpy().ravel()
+    # the move changes the value by less than 2 |A| 1e-12 sqrt(value)
+    assert np.abs(v - want).max() <= 1e-9 * want
