@@ -410,7 +410,9 @@ void rbp_destroy_cut(rbp_cut* cut);
  * and v_j are joined by the edge i -> j when F1 v_i + F2 v_j <= G (every
  * row); a node is not joined to itself.  Numbering the nodes along a
  * space-filling curve lets the kernel skip whole tiles of far-apart pairs
- * (an exact bound); the result does not depend on the numbering.
+ * (an exact bound); the result does not depend on the numbering, as long
+ * as every row value is a number: which edges a node with a NaN has depends on
+ * the nodes numbered beside it.  A NaN in F1, F2 or G leaves no edges.
  * ------------------------------------------------------------------------ */
 #define RBP_GRAPH_MAX_DIM 12
 #define RBP_GRAPH_MAX_ROWS 1024

@@ -11,7 +11,10 @@
 // min_i A_ik + min_j B_jk > 0 for some row k, and a single end node j if
 // min_i A_ik + B_jk > 0.  With nodes numbered along a space-filling curve most
 // far pairs go this way, so the work follows the number of near pairs rather
-// than N^2; the result never depends on it.
+// than N^2; the result does not depend on it where every row value is a number.
+// (The bounds pass over NaN: a NaN row value violates nothing in a pair that is
+// looked at, but its tile may be skipped for the other nodes' sake, and is
+// where none of them has a number in that row.)
 // Output: the adjacency as a row-major bitmask (bit j % 32 of word j / 32 of
 // row i) and out-degrees.
 //
@@ -85,8 +88,9 @@ __global__ __launch_bounds__(256) void graph_rows_kernel(GraphArgs a) {
       a.B[(int64_t)i * a.m + k] = s2;
       nan |= s1 != s1;
     }
-    const double ma = wave::min(live ? s1 : __builtin_huge_val());
-    const double mb = wave::min(live ? s2 : __builtin_huge_val());
+    // a NaN is passed over; a tile without a number in row k has the minimum inf
+    const double ma = wave::min(live && s1 == s1 ? s1 : __builtin_huge_val());
+    const double mb = wave::min(live && s2 == s2 ? s2 : __builtin_huge_val());
     if (lane == 0) {
       a.Amin[tile * a.m + k] = ma;
       a.Bmin[tile * a.m + k] = mb;
