@@ -89,10 +89,10 @@ struct CLds {
   int* cand;
   unsigned* actbits;
   // ADMM region
-  float *Kb, *zr, *yr, *accp, *Pf, *xt, *Cs;
+  float *Kb, *zr, *yr, *accp, *xt, *Cs;
   double* Wm;
   // polish region
-  double *W, *beta, *acte, *u, *w, *zv, *np, *cvec;
+  double *W, *beta, *acte, *u, *w, *zv, *np;
   int *actid, *actside, *actseg;
 };
 
@@ -123,7 +123,6 @@ __device__ CLds<P> ccarve(char* s, const ChainDims& D) {
   L.zr = (float*)(s + D.o_zr);
   L.yr = (float*)(s + D.o_yr);
   L.accp = (float*)(s + D.o_accp);
-  L.Pf = (float*)(s + D.o_Pf);
   L.xt = (float*)(s + D.o_xt);
   L.Cs = (float*)(s + D.o_Cs);
   L.Wm = (double*)(s + D.o_Wm);
@@ -134,7 +133,6 @@ __device__ CLds<P> ccarve(char* s, const ChainDims& D) {
   L.w = L.u + D.n_cap;
   L.zv = L.w + D.n_cap;
   L.np = L.zv + D.n_cap;
-  L.cvec = (double*)(s + D.o_cvec);
   L.actid = (int*)(s + D.o_actid);
   L.actside = L.actid + D.q_cap;
   L.actseg = L.actside + D.q_cap;
@@ -1642,7 +1640,6 @@ ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bo
   d.o_zr = take_a(d.m_cap * 4);
   d.o_yr = take_a(d.m_cap * 4);
   d.o_accp = take_a(d.s_cap * NC * 4);
-  d.o_Pf = take_a(d.s_cap * NC * 4);
   d.o_xt = take_a(d.n_cap * 4);
   d.o_Cs = take_a(NC * NC * 4);
   int b = region;
@@ -1651,7 +1648,6 @@ ChainDims make_chain_dims(int p, int s_cap, int nf_cap, int r_cap, int q_cap, bo
   d.o_beta = take_b(d.q_cap * (NC | 1) * 8);
   d.o_acte = take_b(d.q_cap * 8);
   d.o_u = take_b(4 * d.n_cap * 8);
-  d.o_cvec = take_b(d.q_cap * 8);
   d.o_actid = take_b(3 * d.q_cap * 4);
   // polish only: nothing of the ADMM part but the window Hessians is used
   if (!admm) a = setup_end;

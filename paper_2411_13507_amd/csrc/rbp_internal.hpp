@@ -134,8 +134,8 @@ struct ChainDims {
   int team, o_team;   // 1: four wavefronts per path; their mailbox
   int o_segi, o_seg64, o_Af, o_bfs, o_fan, o_rb, o_rn, o_Pseg, o_gfull, o_G1b, o_qv, o_x, o_scal,
       o_cand, o_bits;
-  int o_Kb, o_zr, o_yr, o_accp, o_Pf, o_xt, o_Cs, o_Wm;          // ADMM part of the region
-  int o_W, o_beta, o_acte, o_u, o_cvec, o_actid;          // polish part of the region
+  int o_Kb, o_zr, o_yr, o_accp, o_xt, o_Cs, o_Wm;          // ADMM part of the region
+  int o_W, o_beta, o_acte, o_u, o_actid;          // polish part of the region
   int bytes;
 };
 
