@@ -275,7 +275,11 @@ int rbp_build_batch(const rbp_problem_desc* d, hipStream_t stream, rbp_batch** o
     });
     // estimated work of a group: its instances' cost, scaled by how few of
     // its workgroups fit a CU (a group of large instances runs at low
-    // residency, so each instance takes longer)
+    // residency, so each instance takes longer).  At most eight count, two per
+    // SIMD: the shapes are not known here, and weighing the degrees up to 7 by the
+    // twelve that the default one fits moves times either way (polish only, launch
+    // shape 1, 16-128 rows: 3,000 edges of degrees 3-9 877 -> 765 us and 30,000 1,348
+    // -> 1,190, but degrees 3-6 alone 293 -> 338 and 1,070 -> 1,220)
     std::vector<int64_t> gcost;
     for (int k = 0; k < N; ++k) {
       const int i = order[k];
@@ -544,11 +548,15 @@ constexpr int kChainFirstPassRows = 32;
 // Batches of up to this many paths per CU are solved in one pass by the
 // four-wavefront kernel at the full cap: a CU works through its few paths one
 // after the other, each much faster, and no path waits for the first pass of
-// the others.  With two passes / one pass, polish only: 256 paths 5.3 / 3.2 ms,
-// 512 5.3 / 3.6, 1,024 5.6 / 4.3, 2,048 6.1 / 6.5, 8,192 12.4 / 17.8 (since the
-// inverse Schur factor: 256 paths 3.0, 1,024 4.2, 2,048 in two passes 6.0, 8,192
-// 12.1).  The ADMM warm start runs on one wavefront in either, so with it the line
-// is one path per CU: 256 paths 8.8 / 6.9 ms, 512 8.9 / 10.5, 1,024 13.8 / 17.3.
+// the others.  Two passes / one pass in ms, polish only, at 1,024 paths: 7.2 / 4.4
+// and 7.9 / 5.0 (4-12 segments, two batches), 1.2 / 1.0 and 1.4 / 1.0 (1-3), 3.7 /
+// 3.2 and 4.5 / 3.9 (6-8), 6.5 / 6.9 and 6.7 / 5.8 (12).  Which of the two is ahead
+// past the line depends on the paths: one pass takes 0.7-1.06 of two at 1,280 to
+// 1,792 paths (4-12 segments: 6.4 / 5.6 at 1,408, 6.3 / 6.7 and 7.7 / 6.4 at 1,792),
+// 0.8-1.1 at 2,048, 0.9-1.1 at 2,560 and more than 1.4 at 8,192; four per CU is where
+// it is ahead of two for all but the longest paths.  The ADMM warm start runs on
+// one wavefront in either, so with it the line is one path per CU: 256 paths 8.8 /
+// 6.9 ms, 512 8.9 / 10.5, 1,024 13.8 / 17.3.
 constexpr int kChainTeamPathsPerCu = 4;
 
 void free_chains(rbp_chains* c) {

@@ -19,8 +19,8 @@
 // Forward pass: FP32 ADMM warm start with the banded K = P + rho A^T D^2 A
 // factored in LDS; FP64 dual active-set polish (Goldfarb-Idnani in the
 // Hessian's metric) using products with L^-1 and L^-T, G1 = L L^T (one lane per
-// global point), and a dense Cholesky factor of the small Schur complement
-// N^T G^-1 N of the working set; Farkas vectors verified in FP64.
+// global point), and the inverse of the Cholesky factor of the small Schur
+// complement N^T G^-1 N of the working set; Farkas vectors verified in FP64.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

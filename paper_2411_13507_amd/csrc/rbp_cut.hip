@@ -604,7 +604,11 @@ __global__ __launch_bounds__(kCutBlock) void cut_value_kernel(CutArgs A) {
 // own.  Blocks of one wavefront spread a short list over the compute units.
 // 50,000 edges x 200 boxes (8,500 pairs listed, 3,800 of them to step 3): 38 us with
 // every face of the simplex tried and divisions, 23 us now; 20,000 edges x (200
-// boxes + 100 polytopes): 100 -> 50 us.
+// boxes + 100 polytopes): 100 -> 50 us.  With longer edges more pairs are near; the
+// list still pays then, since the branches of step 3 no longer hold up the lanes
+// that steps 1 and 2 decide.  50,000 x 200 with steps 1 and 2 on every pair / now,
+// whole runs, for edges of 0.5, 2, 6 and 10 m in a 10 m cube (0.1, 2, 19 and 45 % of
+// the pairs to step 3): 158 / 59, 1,332 / 146, 2,314 / 777 and 2,845 / 1,179 us.
 template <int P>
 __global__ __launch_bounds__(kWave) void cut_qp_kernel(CutArgs A) {
   constexpr int NP = P + 1;
@@ -805,7 +809,10 @@ void cut_plan(CutArgs& a, int n_cu) {
   a.n_blocks = 16 * n_cu;
   // two wavefronts per CU where few pairs are listed: the chain of the slowest
   // pair sets the time, and more wavefronts only share the instruction cache
-  // (50,000 x 200: 26.7 us with one region each, 1,225 wavefronts; 23.3 with three)
+  // (50,000 x 200: 26.7 us with one region each, 1,225 wavefronts; 23.3 with three).
+  // Whole runs with one / two / four / eight per CU: 50,000 x 200 boxes 50 / 50 / 52 /
+  // 55 us, x 300 55 / 57 / 61 / 60, 100,000 x 300 72 / 75 / 74 / 75, 20,000 x (200 + 100
+  // polytopes) 76 / 71 / 71 / 71, with values 132 / 127 / 126 / 127
   const int g = a.n_region / (2 * n_cu) + 1;
   a.group = g < kWave ? g : kWave;
 }

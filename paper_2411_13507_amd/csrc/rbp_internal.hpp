@@ -236,7 +236,7 @@ hipError_t graph_scratch(double** out);
 hipError_t launch_hyperplanes(int n, const double* X, int n_obst, const double* lo, const double* hi, int32_t* idx,
                               double* point, double* plane, hipStream_t s);
 
-// Batched MPC refinement (one wave per instance).  params: constants built
+// Batched MPC refinement (four wavefronts per instance).  params: constants built
 // on the host by the library (layout in mpc_param_layout).
 struct MpcLayout {
   int H1, H0, Qm, Cr, dr, T2, T1, Mi, pf, total;   // offsets in doubles

@@ -129,7 +129,7 @@ __device__ __forceinline__ int hft_stride(const LdsDims& D) { return D.r_cap | 1
 // The value of x, opaque to the optimiser at this point: values derived from
 // it (lane-dependent addresses and indices) are formed where they are used
 // instead of being hoisted out of the polish loop and held in registers for
-// its whole length (the loop runs at the 256-register limit).
+// its whole length (a third wavefront per SIMD leaves 168).
 __device__ __forceinline__ int opaque(int x) {
   asm volatile("" : "+v"(x));
   return x;
