@@ -10,8 +10,9 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("offset", [0.0, 1e6])
 @pytest.mark.parametrize("degree", [1, 2, 3, 5, 7, 9])
-def test_box_as_polytope(degree):
+def test_box_as_polytope(degree, offset):
     import torch
     from paper_2411_13507_amd.api import CutGPU
     rng = np.random.default_rng(degree)
@@ -21,6 +22,8 @@ def test_box_as_polytope(degree):
     P[300:600, :, 2] = 3.0
     lo = rng.integers(0, 6, (n_box, 3)).astype(float)
     hi = lo + rng.integers(1, 3, (n_box, 3))
+    # (multiples of 1/64: moved by an offset, every coordinate and difference stays exact)
+    P, lo, hi = (v + np.array([offset, -offset, offset]) for v in (np.round(P * 64) / 64, lo, hi))
     A = np.concatenate([np.eye(3), -np.eye(3)])
     prob = types.SimpleNamespace(box_lo=lo, box_hi=hi, degree=degree, pob_off=(6 * np.arange(n_box + 1)).astype(np.int32),
                                  pob_A=np.tile(A, (n_box, 1)), pob_b=np.concatenate([hi, -lo], 1).reshape(-1))
@@ -30,7 +33,7 @@ def test_box_as_polytope(degree):
     assert free.sum() > 100
     a, b = d2[:n_box][free], d2[n_box:][free]
     err = np.abs(a - b) / a
-    print(f"case: degree {degree}, {free.sum()} values, largest relative difference {err.max():.1e}", flush=True)
+    print(f"case: degree {degree}, offset {offset}, {free.sum()} values, largest relative difference {err.max():.1e}", flush=True)
     assert err.max() <= 1e-9
 
 
