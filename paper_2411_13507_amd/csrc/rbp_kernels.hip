@@ -7,13 +7,13 @@
 namespace rbp {
 namespace {
 
-// Wavefronts per SIMD that the registers are budgeted for.  The solve is bound
-// by the latency of each wavefront's chain of small steps, so a third
-// wavefront pays as long as nothing spills: up to degree 7 (140-158 of the 168
-// registers; 50,000 degree-7 edges, forward + backward: 792 us with two, 667
-// us with three).  Degrees 8 and 9 take 170 or 171 where they may, the iterations
-// in FP64 180-252 from degree 5 on (168 at degrees 3 and 4, which have a third
-// wavefront without being asked).
+// Wavefronts per SIMD that the registers are budgeted for.  A wavefront's chain of
+// small steps waits for itself a third of the time, so a third wavefront pays as
+// long as nothing spills: up to degree 7 (140-158 of the 168 registers; 50,000
+// degree-7 edges, forward + backward: 792 us with two, 667 us with three, whose
+// vector units then issue 75 % of the time).  Degrees 8 and 9 take 170 or 171 where
+// they may, the iterations in FP64 180-252 from degree 5 on (168 at degrees 3 and
+// 4, which have a third wavefront without being asked).
 template <typename Real, int P>
 constexpr int kWavesPerSimd = sizeof(Real) == 4 && P <= 7 ? 3 : 2;
 
