@@ -910,7 +910,8 @@ __device__ void solve_instance(const SolveArgs& A, const InstDesc& idesc, char* 
   // them.  Below it the errors stay under some 1e-14; ordinary rows hardly ever
   // reach it.  With pairs of rows 1e-6 apart in a warm start, the largest excess of
   // a returned point over a bound: 3.5e-8 without this, 6e-13 with it (4e-13 where R
-  // is rotated and inverted again at every drop).  Its price is 0-1 % of a solve.
+  // is rotated and inverted again at every drop).  Its price is 0-1 % of a solve, 12 %
+  // where every row has such a twin (7,812 edges of degree 7: 556 -> 622 us).
   constexpr double kMaxGrowth = 32.0;
   auto drop = [&](int kd) {
     {
