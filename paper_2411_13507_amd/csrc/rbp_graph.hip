@@ -43,7 +43,6 @@ static __device__ __align__(256) double scratch[kGraphScratchDoubles + kGraphFla
 namespace {
 
 constexpr int kTile = 64;       // nodes per tile side
-constexpr int kChunk = 16;      // rows of A a lane holds at a time
 constexpr int kWords = 4;       // words (of 32 end nodes) per block
 constexpr int kEnds = 16;       // end nodes per wavefront
 constexpr int kPairWaves = kWords * 32 / kEnds;
@@ -108,11 +107,18 @@ __global__ __launch_bounds__(256) void graph_rows_kernel(GraphArgs a) {
 // every lane has a violated row; before that the bound min_i A_ik + B_jk,
 // whose rows lie one per lane, drops the end nodes that no start node of the
 // tile can reach (it does not hold where an A is NaN).
+// kChunk: rows of A a lane holds at a time, m or fewer; with fewer rows more end
+// nodes are looked at together, up to 32 coefficients in flight.  (With 16 for every m
+// and rows loaded again per end node below it, 20,000 nodes in a random numbering
+// took 1,244 us with 8 rows; 526 now.)
 // A block's four words leave through LDS, 16 bytes per row at a time, and are
-// counted into the out-degrees on the way.
+// counted into the out-degrees on the way, one addition per row and block: where
+// most pairs are joined the additions bound the kernel (20,000 nodes x 1 row 1,898 us
+// with one per word, 422 now; 5,000 x 1 160 and 36).
 // 5,000 nodes x 64 rows: 95.2 us (64 x 64 tiles in LDS) + 41.7 us (degrees) -> 45 us.
 // What is left is the latency of the few wavefronts with many open end nodes;
 // blocks of four or sixteen wavefronts instead of eight take 62 and 64 us.
+template <int kChunk>
 __global__ __launch_bounds__(64 * kPairWaves) void graph_pairs_kernel(GraphArgs a, const double* __restrict__ gA,
                                                                  const double* __restrict__ gB) {
   static_assert(kEnds == 16, "two half-words per word");
@@ -150,42 +156,37 @@ __global__ __launch_bounds__(64 * kPairWaves) void graph_pairs_kernel(GraphArgs 
     uint32_t dead = 0u;                                   // per lane: violated end nodes
     uint32_t open = alive;
     for (int kk = 0; kk < m && open; kk += kChunk) {
-      // the last chunk ends at row m (rows seen twice change nothing); with
-      // fewer than kChunk rows the first one is repeated
-      const int k0 = kk + kChunk <= m ? kk : (m >= kChunk ? m - kChunk : 0);
+      // the last chunk ends at row m (rows seen twice change nothing)
+      const int k0 = kk + kChunk <= m ? kk : m - kChunk;
       double av[kChunk];
 #pragma unroll
-      for (int u = 0; u < kChunk; ++u)
-        av[u] = gA[(int64_t)(k0 + u < m ? k0 + u : 0) * n + (gi < n ? gi : n - 1)];
-      // two end nodes at a time: their scalar loads are in flight together
+      for (int u = 0; u < kChunk; ++u) av[u] = gA[(int64_t)(k0 + u) * n + (gi < n ? gi : n - 1)];
+      // several end nodes at a time: their scalar loads are in flight together
+      constexpr int kAtOnce = 32 / kChunk < kEnds ? 32 / kChunk : kEnds;
       for (uint32_t todo = open; todo;) {
-        const int j1 = __builtin_ctz(todo);
-        todo &= todo - 1u;
-        const int j2 = todo ? __builtin_ctz(todo) : j1;
-        todo &= todo - 1u;
-        const double* p1 = gB + (int64_t)(j0 + j1) * m + k0;
-        const double* p2 = gB + (int64_t)(j0 + j2) * m + k0;
-        unsigned long long v1 = 0ull, v2 = 0ull;
-        if (m >= kChunk) {
-          double b1[kChunk], b2[kChunk];
+        int j[kAtOnce];
+        double b[kAtOnce][kChunk];
+        unsigned long long v[kAtOnce];
 #pragma unroll
-          for (int u = 0; u < kChunk; ++u) { b1[u] = p1[u]; b2[u] = p2[u]; }
-#pragma unroll
-          for (int u = 0; u < kChunk; ++u) {
-            v1 |= __ballot(av[u] > -b1[u]);
-            v2 |= __ballot(av[u] > -b2[u]);
-          }
-        } else {
-          for (int u = 0; u < m; ++u) {
-            const double a1 = gA[(int64_t)u * n + (gi < n ? gi : n - 1)];
-            v1 |= __ballot(a1 > -p1[u]);
-            v2 |= __ballot(a1 > -p2[u]);
-          }
+        for (int e = 0; e < kAtOnce; ++e) {      // past the last one: the one before again
+          j[e] = e == 0 || todo ? __builtin_ctz(todo) : j[e > 0 ? e - 1 : 0];
+          todo &= todo - 1u;
         }
-        dead |= ((v1 >> lane) & 1ull) ? 1u << j1 : 0u;
-        dead |= ((v2 >> lane) & 1ull) ? 1u << j2 : 0u;
-        if ((__ballot((dead >> j1) & 1u) & lanes) == lanes) open &= ~(1u << j1);
-        if ((__ballot((dead >> j2) & 1u) & lanes) == lanes) open &= ~(1u << j2);
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e)
+#pragma unroll
+          for (int u = 0; u < kChunk; ++u) b[e][u] = gB[(int64_t)(j0 + j[e]) * m + k0 + u];
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e) v[e] = 0ull;
+#pragma unroll
+        for (int u = 0; u < kChunk; ++u)
+#pragma unroll
+          for (int e = 0; e < kAtOnce; ++e) v[e] |= __ballot(av[u] > -b[e][u]);
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e) dead |= ((v[e] >> lane) & 1ull) ? 1u << j[e] : 0u;
+#pragma unroll
+        for (int e = 0; e < kAtOnce; ++e)
+          if ((__ballot((dead >> j[e]) & 1u) & lanes) == lanes) open &= ~(1u << j[e]);
       }
     }
     bits = alive & ~dead;
@@ -194,11 +195,15 @@ __global__ __launch_bounds__(64 * kPairWaves) void graph_pairs_kernel(GraphArgs 
   half[lane][wv] = uint16_t(bits);
   __syncthreads();
   const int row = tid / kWords, wl = tid % kWords, gr = ti * kTile + row, gw = blockIdx.x * kWords + wl;
-  if (row < kTile && gr < n && gw < n_words) {
-    const uint32_t out = half[row][2 * wl] | (uint32_t(half[row][2 * wl + 1]) << 16);
-    a.adj[(int64_t)gr * n_words + gw] = out;
-    if (out) atomicAdd(&a.degree[gr], __popc(out));
-  }
+  const bool on = row < kTile && gr < n && gw < n_words;
+  const uint32_t out = on ? half[row][2 * wl] | (uint32_t(half[row][2 * wl + 1]) << 16) : 0u;
+  if (on) a.adj[(int64_t)gr * n_words + gw] = out;
+  // the four words of a row lie in four neighbouring lanes
+  static_assert(kWords == 4, "sums over four lanes");
+  int count = __popc(out);
+  count += wave::dpp_i32<wave::kXor1>(count);
+  count += wave::dpp_i32<wave::kXor2>(count);
+  if (wl == 0 && count) atomicAdd(&a.degree[gr], count);
 }
 
 // 64 nodes per block (one per lane), the boxes split over its wavefronts in
@@ -277,8 +282,11 @@ hipError_t launch_graph(const GraphArgs& a, hipStream_t s) {
   else if (a.dim == 6) hipLaunchKernelGGL(graph_rows_kernel<6>, rg, dim3(256), 0, s, a);
   else hipLaunchKernelGGL(graph_rows_kernel<0>, rg, dim3(256), 0, s, a);
   const int n_words = (a.n_nodes + 31) / 32;
-  hipLaunchKernelGGL(graph_pairs_kernel, dim3((n_words + kWords - 1) / kWords, n_tiles), dim3(64 * kPairWaves), 0, s, a,
-                     a.A, a.B);
+  const dim3 pg((n_words + kWords - 1) / kWords, n_tiles), pb(64 * kPairWaves);
+  if (a.m >= 16) hipLaunchKernelGGL(graph_pairs_kernel<16>, pg, pb, 0, s, a, a.A, a.B);
+  else if (a.m >= 8) hipLaunchKernelGGL(graph_pairs_kernel<8>, pg, pb, 0, s, a, a.A, a.B);
+  else if (a.m >= 4) hipLaunchKernelGGL(graph_pairs_kernel<4>, pg, pb, 0, s, a, a.A, a.B);
+  else hipLaunchKernelGGL(graph_pairs_kernel<1>, pg, pb, 0, s, a, a.A, a.B);
   return hipGetLastError();
 }
 
