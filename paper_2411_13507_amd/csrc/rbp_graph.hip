@@ -212,14 +212,16 @@ __global__ __launch_bounds__(64 * kPairWaves) void graph_pairs_kernel(GraphArgs 
 // compared in order, so the lowest index wins as in one loop over all boxes.
 // One thread per node left all but 79 of the chip's wavefronts idle at 5,000
 // nodes and walked the boxes one load after the other.
-// 5,000 nodes x 200 boxes: 33 -> 6.6 us.
+// 5,000 nodes x 200 boxes: 33 -> 6.6 us.  LDS is that of the wavefronts launched:
+// with room for sixteen, blocks of one (from 131,009 nodes on) fill a third of a CU's
+// wavefronts (1,000,000 x 200 166 us, 134 now).
 __global__ __launch_bounds__(64 * kPlaneWaves) void hyperplane_kernel(
     int n, const double* __restrict__ X, int n_obst, const double* __restrict__ lo, const double* __restrict__ hi,
     int32_t* __restrict__ idx, double* __restrict__ point, double* __restrict__ plane) {
-  __shared__ double sd[kPlaneWaves][64];
-  __shared__ int si[kPlaneWaves][64];
+  extern __shared__ double sd[];                     // 64 distances per wavefront, then 64 indices
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int nw = blockDim.x >> 6;
+  int* const si = reinterpret_cast<int*>(sd + 64 * nw);
   const int i = blockIdx.x * 64 + lane;
   const int64_t ic = i < n ? i : n - 1;
   const double x = X[3 * ic], y = X[3 * ic + 1], z = X[3 * ic + 2];
@@ -248,12 +250,12 @@ __global__ __launch_bounds__(64 * kPlaneWaves) void hyperplane_kernel(
     const double d2 = dist2(lo + 3 * (int64_t)o, hi + 3 * (int64_t)o);
     if (d2 < best) { best = d2; bi = o; }
   }
-  sd[wv][lane] = best;
-  si[wv][lane] = bi;
+  sd[64 * wv + lane] = best;
+  si[64 * wv + lane] = bi;
   __syncthreads();
   if (wv != 0 || i >= n) return;
   for (int w = 1; w < nw; ++w)
-    if (sd[w][lane] < best) { best = sd[w][lane]; bi = si[w][lane]; }
+    if (sd[64 * w + lane] < best) { best = sd[64 * w + lane]; bi = si[64 * w + lane]; }
   double px = x, py = y, pz = z;
   if (bi >= 0) {
     px = fmin(fmax(x, lo[3 * (int64_t)bi]), hi[3 * (int64_t)bi]);
@@ -318,7 +320,7 @@ hipError_t launch_hyperplanes(int n, const double* X, int n_obst, const double* 
   const int blocks = (n + 63) / 64;
   int waves = 1;
   while (waves < kPlaneWaves && blocks * waves < 2048 && 8 * waves <= n_obst) waves *= 2;
-  hipLaunchKernelGGL(hyperplane_kernel, dim3(blocks), dim3(64 * waves), 0, s, n, X, n_obst, lo, hi, idx, point, plane);
+  hipLaunchKernelGGL(hyperplane_kernel, dim3(blocks), dim3(64 * waves), 768 * waves, s, n, X, n_obst, lo, hi, idx, point, plane);
   return hipGetLastError();
 }
 
