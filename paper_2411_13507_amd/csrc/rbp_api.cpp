@@ -1145,6 +1145,7 @@ int rbp_adjacent_hyperplanes(int32_t n, const double* X, int32_t n_obst, const d
 struct rbp_mpc {
   int device = 0;
   rbp_mpc_desc desc{};
+  int n_cu = 1;
   double* params = nullptr;
   double ulo[3] = {0, 0, 0}, uhi[3] = {0, 0, 0};
   int ubox_ok = 0;
@@ -1345,6 +1346,7 @@ int rbp_build_mpc(const rbp_mpc_desc* d, hipStream_t stream, rbp_mpc** out) {
   if (!q) return RBP_E_ALLOC;
   q->device = dev;
   q->desc = *d;
+  if (hipDeviceGetAttribute(&q->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || q->n_cu < 1) q->n_cu = 1;
   q->ubox_ok = mpc_input_box(m, d->dt, F1, F2, G, q->ulo, q->uhi) ? 1 : 0;
   if ((rc = dalloc(&q->params, prm.size()))) { delete q; return rc; }
   if (hipMemcpyAsync(q->params, prm.data(), prm.size() * sizeof(double), hipMemcpyHostToDevice, stream) ||
@@ -1367,6 +1369,7 @@ int rbp_mpc_solve(rbp_mpc* q, const double* x0, const double* ref, const double*
   if (!x0 || !ref || !planes || !X || !U || !cost || !status || !kkt) return RBP_E_INVALID;
   rbp::MpcArgs a{};
   a.n = d.n_instances; a.N = d.horizon; a.m = d.n_reach;
+  a.n_cu = q->n_cu;
   a.max_iters = max_iters; a.tol = tol; a.dt = d.dt;
   a.params = q->params;
   a.x0 = x0; a.ref = ref; a.planes = planes;

@@ -236,7 +236,7 @@ hipError_t graph_scratch(double** out);
 hipError_t launch_hyperplanes(int n, const double* X, int n_obst, const double* lo, const double* hi, int32_t* idx,
                               double* point, double* plane, hipStream_t s);
 
-// Batched MPC refinement (four wavefronts per instance).  params: constants built
+// Batched MPC refinement (four wavefronts per instance, or one).  params: constants built
 // on the host by the library (layout in mpc_param_layout).
 struct MpcLayout {
   int H1, H0, Qm, Cr, dr, T2, T1, Mi, pf, total;   // offsets in doubles
@@ -262,6 +262,7 @@ __host__ __device__ inline MpcLayout mpc_param_layout(int m) {
 struct MpcArgs {
   int n;                     // instances
   int N, m;                  // horizon, reachable rows per step
+  int n_cu;                  // compute units of the device
   int max_iters;
   double tol;                // complementarity / residual target
   double dt;

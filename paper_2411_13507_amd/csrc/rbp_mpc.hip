@@ -1,5 +1,6 @@
 // Batched MPC refinement QP (eq. MPC, Sec. III-D): one workgroup of four
-// wavefronts per instance, primal-dual interior point (Mehrotra predictor-corrector), FP64.
+// wavefronts per instance (one for short horizons in large batches), primal-dual
+// interior point (Mehrotra predictor-corrector), FP64.
 //
 // Stage variables z_k = (x_k, u_k), k = 0..N-1, with x = (position, velocity)
 // and u = acceleration; x_{k+1} = A x_k + B u_k is the exact discretisation of
@@ -37,8 +38,8 @@ namespace rbp {
 namespace {
 
 constexpr int kW = 64;
-constexpr int kWaves = 4;              // wavefronts per instance
-constexpr int kT = kW * kWaves;
+constexpr int kWaves = 4;              // most wavefronts per instance
+constexpr int kOneSlots = 4;           // register slots per lane where one wavefront holds every row
 constexpr int kRing = 6;               // stages of barrier Hessians per batch of the factorisation
 constexpr int kSolved = 0, kInfeasible = 1, kMaxIter = 2, kNumerical = 4, kInvalid = 5;
 
@@ -136,7 +137,10 @@ __device__ inline double div_nr(double a, double b) {
 // a value that is the same in every lane, in scalar registers
 __device__ __forceinline__ double uni(double x) { return wave::bcast(x, 0); }
 
+// W: wavefronts per instance (1 or kWaves)
+template <int W>
 struct MpcCtx {
+  static constexpr int kT = kW * W;
   const MpcArgs& A;
   MpcSm S;
   MpcLayout Ly;
@@ -195,9 +199,11 @@ struct MpcCtx {
   // largest / smallest value over the instance's wavefronts
   __device__ __forceinline__ double bmax(double v) const {
     v = wave::max(v);
-    if (lane == 0) S.red[wv] = v;
-    __syncthreads();
-    v = fmax(fmax(S.red[0], S.red[1]), fmax(S.red[2], S.red[3]));
+    if constexpr (W > 1) {
+      if (lane == 0) S.red[wv] = v;
+      __syncthreads();
+      v = fmax(fmax(S.red[0], S.red[1]), fmax(S.red[2], S.red[3]));
+    }
     __syncthreads();
     return uni(v);
   }
@@ -205,23 +211,31 @@ struct MpcCtx {
   __device__ __forceinline__ void bmax2(double& a, double& b) const {
     a = wave::max(a);
     b = wave::max(b);
-    if (lane == 0) { S.red[wv] = a; S.red[kWaves + wv] = b; }
-    __syncthreads();
-    a = fmax(fmax(S.red[0], S.red[1]), fmax(S.red[2], S.red[3]));
-    b = fmax(fmax(S.red[4], S.red[5]), fmax(S.red[6], S.red[7]));
+    if constexpr (W > 1) {
+      if (lane == 0) { S.red[wv] = a; S.red[kWaves + wv] = b; }
+      __syncthreads();
+      a = fmax(fmax(S.red[0], S.red[1]), fmax(S.red[2], S.red[3]));
+      b = fmax(fmax(S.red[4], S.red[5]), fmax(S.red[6], S.red[7]));
+    }
     __syncthreads();
   }
   // Sum over the rows: add(acc) continues a lane's running sum over the rows
   // its wavefront holds, in order; the wavefronts take turns, so that the
   // order is that of one wavefront walking every slot (how far an unsolvable
-  // horizon gets depends on the last bits of these sums).
+  // horizon gets depends on the last bits of these sums).  The sums are written as
+  // fma: of two products added in registers the compiler may round either.
   template <typename F>
   __device__ __forceinline__ double chain_sum(F&& add) const {
-    for (int w = 0; w < kWaves; ++w) {
-      if (wv == w) S.part[lane] = add(w == 0 ? 0.0 : S.part[lane]);
-      __syncthreads();
+    double v;
+    if constexpr (W > 1) {
+      for (int w = 0; w < W; ++w) {
+        if (wv == w) S.part[lane] = add(w == 0 ? 0.0 : S.part[lane]);
+        __syncthreads();
+      }
+      v = wave::sum(S.part[lane]);
+    } else {
+      v = wave::sum(add(0.0));
     }
-    const double v = wave::sum(S.part[lane]);
     __syncthreads();
     return uni(v);
   }
@@ -297,9 +311,9 @@ struct MpcCtx {
     // The barrier Hessians do not depend on the recursion: they are formed
     // kRing stages at a time, the first batch by every wavefront, each next one
     // by wavefronts 1..3 while wavefront 0 runs the recursion over the batch
-    // before it.
+    // before it (one wavefront alone takes them in turn).
     auto batch = [&](int b, int first) {       // stages N-1 - kRing b, going down
-      for (int u = wv - first; u < kRing; u += kWaves - first) {
+      for (int u = wv - first; u < kRing; u += W - first) {
         const int k = N - 1 - (kRing * b + u);
         if (u >= 0 && k >= 0 && lane < 45) S.ring[((b & 1) * kRing + u) * 45 + lane] = ht_entry(k);
       }
@@ -317,9 +331,8 @@ struct MpcCtx {
           if (k < 0) break;
           stage(k, ring + u * 45);
         }
-      } else if (b + 1 < nb) {
-        batch(b + 1, 1);
       }
+      if ((W == 1 || wv > 0) && b + 1 < nb) batch(b + 1, W > 1 ? 1 : 0);
       __syncthreads();
     }
     return S.tmp[kTmpFlag] == 0.0;
@@ -540,7 +553,8 @@ struct MpcCtx {
   // right-hand side d e (a product that the caller's FMAs take unrounded).
   // Wavefronts 0..2 share the reachable rows (coefficient table): with row t in
   // lane t % 64 of pass t / 64, each takes spw consecutive passes; wavefront 3
-  // holds the plane rows.  The loops are unrolled, so slot is a constant
+  // holds the plane rows.  (One wavefront alone takes the plane rows after its
+  // spw passes.)  The loops are unrolled, so slot is a constant
   // wherever f indexes a register array with it.  c'z and c'dz are formed only
   // when CZ / CD ask for them.
   template <int NS, bool CZ, bool CD, typename F>
@@ -556,7 +570,7 @@ struct MpcCtx {
       bool on;
       int r = 0;
       double cz = 0.0, cd = 0.0, d = 0.0, de = 1.0;
-      if (wv < kWaves - 1) {
+      if (W > 1 ? wv < W - 1 : j < spw) {
         on = j < spw && t0 + kW * j < N * m;
         if (on) {
           const double* c = S.prm + Ly.Cr + ir;
@@ -575,8 +589,8 @@ struct MpcCtx {
         ir += rr;
         if (ir >= mm) { ir -= mm; ++kr; }
       } else {
-        const int t = ln + kW * j;
-        on = j < 4 && t < 4 * N;
+        const int t = ln + kW * (W > 1 ? j : j - spw);
+        on = (W == 1 || j < 4) && t < 4 * N;
         if (on) {
           const int k = t >> 2, jj = t & 3;
           const double* f3 = S.prm + Ly.pf + 3 * jj;
@@ -604,7 +618,9 @@ struct MpcCtx {
   __device__ __forceinline__ void for_slots(F&& f) const {
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
-      const bool on = wv < kWaves - 1 ? (j < spw && lane + kW * (wv * spw + j) < N * m) : (j < 4 && lane + kW * j < 4 * N);
+      const bool on = (W > 1 ? wv < W - 1 : j < spw)
+                          ? (j < spw && lane + kW * (wv * spw + j) < N * m)
+                          : ((W == 1 || j < 4) && lane + kW * (W > 1 ? j : j - spw) < 4 * N);
       if (on) f(j);
     }
   }
@@ -728,17 +744,18 @@ struct MpcCtx {
 // Registers for three wavefronts per SIMD (149; at 128, for four, it spills and
 // takes 8.4 ms); the kernel for more rows per lane needs 186.
 // NS: register slots per lane (reachable passes per wavefront, at least the
-// four of the plane rows)
-template <int NS>
-__global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 3 : 2))) void mpc_kernel(MpcArgs A) {
+// four of the plane rows; with W = 1 passes of reachable and of plane rows)
+template <int NS, int W>
+__global__ __launch_bounds__(kW * W) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 3 : 2))) void mpc_kernel(MpcArgs A) {
+  constexpr int kT = kW * W;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   const int inst = blockIdx.x;
   if (inst >= A.n) return;
   const int N = A.N, m = A.m, mr = m + 4, RT = N * mr, tid = threadIdx.x, lane = tid & (kW - 1);
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  MpcCtx C{A, carve_mpc(reinterpret_cast<double*>(smem_raw), N, m), mpc_param_layout(m), N, m, mr, RT, lane, wv, tid,
+  MpcCtx<W> C{A, carve_mpc(reinterpret_cast<double*>(smem_raw), N, m), mpc_param_layout(m), N, m, mr, RT, lane, wv, tid,
            A.dt};
-  C.spw = ((N * m + kW - 1) / kW + kWaves - 2) / (kWaves - 1);
+  C.spw = W > 1 ? ((N * m + kW - 1) / kW + W - 2) / (W - 1) : (N * m + kW - 1) / kW;
   C.init_lane();
   MpcSm& S = C.S;
   const MpcLayout& Ly = C.Ly;
@@ -851,7 +868,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 3 
     });
     __syncthreads();
     mu = C.chain_sum([&](double acc) {
-      C.template for_slots<NS>([&](int j) { acc += rs[j] * rl[j]; });
+      C.template for_slots<NS>([&](int j) { acc = fma(rs[j], rl[j], acc); });
       return acc;
     }) / RT;
     rpmax = C.bmax(rpm);
@@ -886,7 +903,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 3 
       S.X[r] = ds * dl;                         // affine product for the corrector
     });
     const double mua = C.chain_sum([&](double acc) {
-      C.template for_slots<NS>([&](int j) { acc += ma[j] * mb[j]; });
+      C.template for_slots<NS>([&](int j) { acc = fma(ma[j], mb[j], acc); });
       return acc;
     }) / RT;
     const double sc = (mua / mu) * (mua / mu) * (mua / mu);
@@ -995,12 +1012,12 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 3 
     }
     __syncthreads();
     const double phi = C.chain_sum([&](double acc) {
-      C.template for_rows<NS, true, false>([&](int, int r, double cz, double, double d, double de) { acc += S.X[r] * fma(-d, de, cz); });
+      C.template for_rows<NS, true, false>([&](int, int r, double cz, double, double d, double de) { acc = fma(S.X[r], fma(-d, de, cz), acc); });
       return acc;
     });
     const double pab = C.chain_sum([&](double acc) {
       C.template for_rows<NS, true, false>(
-          [&](int, int r, double cz, double, double d, double de) { acc += S.X[r] * (fabs(cz) + fabs(d * de)); });
+          [&](int, int r, double cz, double, double d, double de) { acc = fma(S.X[r], fabs(cz) + fabs(d * de), acc); });
       return acc;
     });
     double tn = 0.0, tnab = 0.0;
@@ -1041,6 +1058,19 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(NS <= 5 ? 3 
 
 size_t mpc_lds_bytes(int N, int m) { return sizeof(double) * size_t(mpc_lds_doubles(N, m)); }
 
+// One wavefront per instance where its few rows fit kOneSlots slots of a lane and the
+// batch holds more instances than CUs fit with four wavefronts each (three, by
+// registers; up to twelve with one): the other three are mostly idle there, and a
+// CU takes its instances in rounds.  Four / one, the same results bit for bit: 768
+// horizons of 4 steps 190 / 176 us, of 8 343 / 399, of 16 519 / 679 (12 rows); 1,024 of
+// 4, 8 (16 rows) and 16 893 / 710, 592 / 421 and 821 / 705; 4,096 of 2, 4, 8, 12 and
+// 16 2,965 / 948, 1,000 / 434, 1,375 / 768, 1,858 / 1,176 and 2,417 / 1,656 (12 rows), of 2 and 6
+// with 32 rows 3,962 / 1,568 and 3,343 / 2,190.  Past four slots the lead goes: 1,536 of 12
+// steps, 20 rows 1,757 / 1,935.
+static bool mpc_one_wave(const MpcArgs& a) {
+  return a.n > 3 * a.n_cu && (a.N * a.m + kW - 1) / kW + (4 * a.N + kW - 1) / kW <= kOneSlots;
+}
+
 hipError_t launch_mpc(const MpcArgs& a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
   const size_t lds = mpc_lds_bytes(a.N, a.m);
@@ -1049,10 +1079,12 @@ hipError_t launch_mpc(const MpcArgs& a, hipStream_t s) {
   const int rows = a.N * a.m;
   if (a.N < 2 || a.N > 64 || a.m < 0 || rows > 32 * kW) return hipErrorInvalidValue;
   const int slots = ((rows + kW - 1) / kW + kWaves - 2) / (kWaves - 1);
-  if (slots <= 5)
-    hipLaunchKernelGGL(mpc_kernel<5>, dim3(a.n), dim3(kT), lds, s, a);
+  if (mpc_one_wave(a))
+    hipLaunchKernelGGL((mpc_kernel<kOneSlots, 1>), dim3(a.n), dim3(kW), lds, s, a);
+  else if (slots <= 5)
+    hipLaunchKernelGGL((mpc_kernel<5, kWaves>), dim3(a.n), dim3(kW * kWaves), lds, s, a);
   else
-    hipLaunchKernelGGL(mpc_kernel<11>, dim3(a.n), dim3(kT), lds, s, a);
+    hipLaunchKernelGGL((mpc_kernel<11, kWaves>), dim3(a.n), dim3(kW * kWaves), lds, s, a);
   return hipGetLastError();
 }
 
