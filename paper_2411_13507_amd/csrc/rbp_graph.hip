@@ -115,7 +115,7 @@ __global__ __launch_bounds__(256) void graph_rows_kernel(GraphArgs a) {
 // counted into the out-degrees on the way, one addition per row and block: where
 // most pairs are joined the additions bound the kernel (20,000 nodes x 1 row 1,898 us
 // with one per word, 422 now; 5,000 x 1 160 and 36).
-// 5,000 nodes x 64 rows: 95.2 us (64 x 64 tiles in LDS) + 41.7 us (degrees) -> 45 us.
+// 5,000 nodes x 64 rows: 95.2 us (64 x 64 tiles in LDS) + 41.7 us (degrees) -> 40 us.
 // What is left is the latency of the few wavefronts with many open end nodes;
 // blocks of four or sixteen wavefronts instead of eight take 62 and 64 us.
 template <int kChunk>

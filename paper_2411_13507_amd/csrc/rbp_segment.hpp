@@ -251,26 +251,27 @@ struct Inst {
 // arrive in one or two HBM round trips instead of one per element).  What is left
 // for few edges is index arithmetic: a full-rate product instead of a division
 // (exact below 43,690), nothing per column, nothing for columns that are not kept.
-// One edge of degree 7 with 100 rows 14.2 -> 12.4 us (12.6 where all columns were
-// kept), with 32 10.9 -> 10.4 (10.1); 50,000 with 32, with the backward pass, 676 -> 665.
+// One edge of degree 7 with 100 rows 14.2 -> 12.5 us (12.6 where all columns were
+// kept), with 32 10.9 -> 10.4 (10.1); 50,000 with 32, with the backward pass, 1.3 % less.
 template <int RL, int LD>
 __device__ __forceinline__ void stage_rows(double* dst, const double* __restrict__ src, int r, int lane) {
   constexpr int M = RL - 6;
-  constexpr unsigned kInv = (1u << 20) / M + 1;
+  constexpr int kInv = (1 << 20) / M + 1;
   const int n = r * M;
   for (int base = 0; base < n; base += 8 * kWave) {
     double v[8];
-    unsigned row[8];
+    int row[8];
+    const int l = opaque(lane);   // nothing of this stays in (spilled) scalar registers for the ADMM loop
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const unsigned e = base + u * kWave + lane;
-      row[u] = __umul24(e, kInv) >> 20;
-      v[u] = e < unsigned(n) ? src[e + 3 + 6 * row[u]] : 0.0;
+      const int e = base + u * kWave + l;
+      row[u] = int(__umul24(e, kInv) >> 20);
+      v[u] = e < n ? src[e + 3 + 6 * row[u]] : 0.0;
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const unsigned e = base + u * kWave + lane;
-      if (e < unsigned(n)) dst[e + (LD - M) * row[u]] = v[u];
+      const int e = base + u * kWave + l;
+      if (e < n) dst[e + (LD - M) * row[u]] = v[u];
     }
   }
 }
